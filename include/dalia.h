@@ -160,9 +160,13 @@ dl_status dl_model_dims(const dl_model* model, int64_t* n, int64_t* b,
 /* Workspace flags. */
 enum {
   DL_WS_SELINV = 1,   /* keep the storage of the selected inversion        */
-  DL_WS_KEEP_QP = 2,  /* store Q_p in full (inspection); by default Q_p is
-                         assembled just in time into a ring of blocks, as
-                         only its log-determinant is needed                */
+  DL_WS_KEEP_QP = 2,  /* store Q_p in full (inspection); by default only its
+                         log-determinant is formed: DL_MODEL_SEPARABLE from
+                         the Cholesky factor of one diagonal block (the block
+                         factors of a sum of Kronecker products with AR1
+                         temporal factors repeat), other families (and
+                         coregional models with DL_WS_MIXED) by the sweep over
+                         blocks assembled just in time into a ring         */
   DL_WS_GRAPH = 4,    /* fobj_eval replays one captured HIP graph          */
   DL_WS_MIXED = 8     /* mixed precision: the off-diagonal blocks [B_t; R_t]
                          of Q_c (and Q_p) are stored in FP32 and their

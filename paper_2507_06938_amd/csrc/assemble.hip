@@ -87,6 +87,7 @@ __global__ void k_theta_coeffs(const ThetaJob* __restrict__ jobs) {
       for (int tt = 0; tt < 3; ++tt) wd[i][tt][c] = 0.0;
     }
   const bool diffusion = m.family == DL_MODEL_DIFFUSION;
+  double logt = 0.0;
   for (int i = 0; i < nv; ++i) {
     if (!isfinite(kap[i]) || !isfinite(tau[i])) bad = 1;
     if (diffusion) {
@@ -108,6 +109,7 @@ __global__ void k_theta_coeffs(const ThetaJob* __restrict__ jobs) {
       const double r = rho[i];
       const double den = 1.0 - r * r;
       if (!(den > 0.0)) bad = 1;
+      logt += log(den);
       const double Tend = 1.0 / den, Tmid = (1.0 + r * r) / den, Toff = -r / den;
       for (int c = 0; c < NPIECE; ++c) {
         wd[i][0][c] = Tend * q[c];
@@ -152,6 +154,7 @@ __global__ void k_theta_coeffs(const ThetaJob* __restrict__ jobs) {
   coef[C_LOGPRIOR] = lp;
   coef[C_LLCONST] = llc;
   coef[C_BAD] = bad ? 1.0 : 0.0;
+  coef[C_LOGT] = (double)m.ns * logt;
 }
 
 hipError_t launch_theta_coeffs(const ThetaJob* jobs, int count, hipStream_t s) {

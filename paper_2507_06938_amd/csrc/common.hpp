@@ -218,8 +218,9 @@ struct MiscJob {
 };
 hipError_t launch_misc(const MiscJob* jobs_dev, int count, hipStream_t s);
 
-// out[0] = scale * sum(src[0..n)) with a fixed reduction order; partial
-// holds SUM_BLOCKS doubles per job.
+// out[0] = scale * sum(src[0..n)) + scale2 * sum(src2[0..n2)) + add[0] with
+// a fixed reduction order (src2 and add may be null); partial holds SUM_BLOCKS
+// doubles per job.
 constexpr int SUM_BLOCKS = 128;
 struct SumJob {
   const double* src;
@@ -227,6 +228,10 @@ struct SumJob {
   double scale;
   double* dst;
   double* partial;
+  const double* src2;
+  int64_t n2;
+  double scale2;
+  const double* add;
 };
 hipError_t launch_sums(const SumJob* jobs_dev, int count, hipStream_t s);
 

@@ -228,11 +228,11 @@ DL_DAG_FN Task unpack(uint64_t w, int* block) {
               (int)((w >> 48) & 0xffff)};
 }
 
-// The task list of one launch over several blocks: all blocks' tasks
-// sorted by latest start level, then earliest start level, then block, then
+// The task list of one launch over several blocks (inverse[b]: block b's
+// inverse is formed too): all blocks' tasks sorted by latest start level, then earliest start level, then block, then
 // phase order.
-inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks, bool inverse,
-                                         bool chain = true) {
+inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks,
+                                         const std::vector<char>& inverse, bool chain = true) {
   struct Item {
     int alap, asap, block;
     size_t pos;
@@ -241,7 +241,7 @@ inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks, bool inve
   std::vector<Item> all;
   for (size_t b = 0; b < nbks.size(); ++b) {
     std::vector<int> lv, sl;
-    std::vector<Task> s = schedule(nbks[b], inverse, &lv, &sl, chain);
+    std::vector<Task> s = schedule(nbks[b], inverse[b] != 0, &lv, &sl, chain);
     for (size_t p = 0; p < s.size(); ++p) all.push_back({lv[p] + sl[p], lv[p], (int)b, p, s[p]});
   }
   std::stable_sort(all.begin(), all.end(), [](const Item& a, const Item& b) {
@@ -254,6 +254,10 @@ inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks, bool inve
   out.reserve(all.size());
   for (const Item& it : all) out.push_back(pack(it.t, it.block));
   return out;
+}
+inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks, bool inverse,
+                                         bool chain = true) {
+  return launch_list(nbks, std::vector<char>(nbks.size(), inverse ? 1 : 0), chain);
 }
 
 }  // namespace dag

@@ -851,7 +851,16 @@ __global__ __launch_bounds__(256) void k_sum_final(const SumJob* __restrict__ jo
   double acc = 0.0;
   for (int i = threadIdx.x; i < SUM_BLOCKS; i += 256) acc += J.partial[i];
   const double v = block_sum_256(acc, sh);
-  if (threadIdx.x == 0) J.dst[0] = J.scale * v;
+  double acc2 = 0.0;
+  if (J.src2)
+    for (int64_t i = threadIdx.x; i < J.n2; i += 256) acc2 += J.src2[i];
+  const double v2 = block_sum_256(acc2, sh);
+  if (threadIdx.x == 0) {
+    double r = J.scale * v;
+    if (J.src2) r += J.scale2 * v2;
+    if (J.add) r += J.add[0];
+    J.dst[0] = r;
+  }
 }
 
 hipError_t launch_sums(const SumJob* jobs, int count, hipStream_t s) {

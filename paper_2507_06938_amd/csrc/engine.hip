@@ -45,6 +45,7 @@ struct Step {
   PotrfTileArgs potrf{};
   PanelTask panel{};
   DagBlock dagb{};
+  bool dag_inv = true;  // the block's inverse is formed too
   MiscJob misc{};
   GemvN gn{};
   GemvT gt{};
@@ -183,12 +184,14 @@ static void merge(const std::vector<std::vector<Step>>& seqs, Descs& D,
         // tasks in one list (dag.hpp)
         L.off = (int)D.dagb.size();
         std::vector<int> nbks;
+        std::vector<char> inv;
         for (const Step* st : g) {
           D.dagb.push_back(st->dagb);
           nbks.push_back(st->dagb.nbk);
+          inv.push_back(st->dag_inv ? 1 : 0);
         }
         L.count = (int)D.dagb.size() - L.off;
-        const std::vector<uint64_t> tl = dag::launch_list(nbks, true);
+        const std::vector<uint64_t> tl = dag::launch_list(nbks, inv);
         L.gy = (int)D.dagt.size();
         D.dagt.insert(D.dagt.end(), tl.begin(), tl.end());
         L.gx = (int)tl.size();
@@ -282,7 +285,8 @@ static Step misc_step(uint64_t key, int cat, int kind, double* dst,
 static void seq_potrf(std::vector<Step>& q, uint64_t major, double* A, int64_t ld,
                       int n, double* logdiag, int64_t* info, int64_t row0,
                       int breal, double* tmp, bool count_inv, bool fold,
-                      double* lbuf = nullptr, int32_t* dctr = nullptr) {
+                      double* lbuf = nullptr, int32_t* dctr = nullptr,
+                      bool dag_inv = true) {
   const int nbk = n / 64;
   if (lbuf) {
     // the whole factorisation and inverse in one persistent launch (shared
@@ -293,6 +297,7 @@ static void seq_potrf(std::vector<Step>& q, uint64_t major, double* A, int64_t l
     s.cat = DL_CAT_PANEL_SYRK;
     const double b3 = (double)breal * breal * breal / 3.0;
     s.flops = b3 + (count_inv ? b3 : 0.0);
+    s.dag_inv = dag_inv;
     DagBlock& d = s.dagb;
     d.A = A;
     d.ld = ld;
@@ -433,6 +438,9 @@ struct Inst {
   // blocks assembled just in time (only log|Q_p| is needed)
   double *Dp = nullptr, *Bp = nullptr, *Pp = nullptr;
   bool qp_ring = true;
+  // separable family, not kept: log|Q_p| from one diagonal block (see
+  // seq_logdet_qp); Dp holds that block
+  bool qp_kron = false;
   // Q_c: full storage, [B_t; R_t] in nt+1 slots of (bp+ap) x bp (nt+2 when
   // two-sided: one spare slot per elimination chain)
   double *Dc = nullptr, *BRc = nullptr, *Pc = nullptr, *GPc = nullptr;
@@ -708,6 +716,80 @@ static void seq_assemble(dl_ws* W, Inst& I, bool p, bool c, std::vector<Step>& q
   }
 }
 
+// log|Q_p| of the separable family from one diagonal block.  Process i has
+// Q^i = T_i (x) Q_s,i with the unit-variance AR1 precision T_i, and Q_p =
+// (Lambda^-1 (x) I)^T diag_i(Q^i) (Lambda^-1 (x) I) mixes them.  The block
+// Cholesky of such a matrix has the same Schur complement at every step but
+// the last: with T_i's end entry e_i = 1/(1-rho_i^2), inner entry
+// (1+rho_i^2) e_i and off-diagonal entry -rho_i e_i,
+//   (1+rho_i^2) e_i - (rho_i e_i)^2 / e_i = e_i,
+// and e_i - rho_i^2 e_i = 1 at the last one.  So every pivot block but the
+// last is the assembled first block D_0, the last differs from it by the
+// factor 1/e_i per process, and
+//   log|Q_p| = nt log|D_0| + ns sum_i log(1-rho_i^2) + log|tip|.
+// One block is factored in the launches of the first step's blocks of Q_c
+// (no inverse) where the sweep factored nt of them with two products each: f_obj
+// with all variances of the 45 x 45, nt = 100 model went from 225 to 176 ms, a
+// 9-point gradient at 30 x 30, nt = 48 from 83.0 to 54.2 ms.  nt = 1
+// holds too: its single block is D_0 without the AR1 factor.  A pivot that
+// fails is reported at its row of D_0.  Q_p kept in full (DL_WS_KEEP_QP: its
+// blocks can be overwritten), the diffusion family (its temporal factors do
+// not share a recurrence) and what inst_layout names take the sweep.
+static void seq_logdet_qp(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
+  const ModelDev& m = I.m;
+  const int bp = m.bp;
+  int64_t* info = I.info2;
+  double* logdiag = I.logdiag[0];
+  q.push_back(misc_step(K(0, 0), DL_CAT_OTHER, MJ_ZERO_I64, (double*)info, nullptr, 1));
+  Step s;
+  s.key = K(0, 3);
+  s.kind = OP_ASM_COLS;
+  s.cat = DL_CAT_ASSEMBLE;
+  s.bytes = 8.0 * m.b * m.b;
+  s.asmj.m = I.model->dev;
+  s.asmj.coef = I.coef;
+  s.asmj.t0 = 0;
+  s.asmj.nt = 1;
+  s.asmj.o.Dp = I.Dp;
+  s.asmj.o.rhs = I.rhs;
+  s.gx = bp;
+  s.gy = 1;
+  q.push_back(s);
+  seq_potrf(q, 1, I.Dp, bp, bp, logdiag, info, 0, m.b, I.ttemp[0], false, false,
+            W->dag ? I.lbuf[0] : nullptr, W->dag ? I.dctr[0] : nullptr, false);
+  const uint64_t tail = (uint64_t)nt_max + 1;
+  double* ltip = logdiag + (int64_t)m.nt * bp;
+  if (m.ap > 0) {
+    Step p;
+    p.key = K(tail, 0);
+    p.kind = OP_POTRF;
+    p.cat = DL_CAT_POTRF_TILE;
+    p.flops = (double)m.a * m.a * m.a / 3.0;
+    p.potrf.A = I.Pp;
+    p.potrf.lda = m.ap;
+    p.potrf.Ginv = I.GPp;
+    p.potrf.logdiag = ltip;
+    p.potrf.info = info;
+    p.potrf.row0 = (int64_t)m.nt * m.b;
+    p.potrf.mode = 0;
+    q.push_back(p);
+  }
+  Step sl;
+  sl.key = K(tail, 1);
+  sl.kind = OP_SUM;
+  sl.cat = DL_CAT_OTHER;
+  sl.sum.src = logdiag;
+  sl.sum.n = bp;
+  sl.sum.scale = 2.0 * m.nt;
+  sl.sum.src2 = m.ap > 0 ? ltip : nullptr;
+  sl.sum.n2 = m.ap;
+  sl.sum.scale2 = 2.0;
+  sl.sum.add = m.nt > 1 ? I.coef + C_LOGT : nullptr;
+  sl.sum.dst = I.logdet2;
+  sl.sum.partial = I.sumpart;
+  q.push_back(sl);
+}
+
 // BTA Cholesky of Q_p (w = 0) or Q_c (w = 1) of instance I in its
 // elimination order.  Every block t other than the root is eliminated into
 // its successor (t+1 in chain A, t-1 in chain B): factor D_t, scale its
@@ -721,6 +803,10 @@ static void seq_assemble(dl_ws* W, Inst& I, bool p, bool c, std::vector<Step>& q
 // chain, 1 + nt_max for the tip.  The two chains' updates of the root block
 // fall in different launches because the chains differ in length.
 static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& q) {
+  if (w == 0 && I.qp_kron) {
+    seq_logdet_qp(W, I, nt_max, q);
+    return;
+  }
   const ModelDev& m = I.m;
   const int bp = m.bp;
   const int n = m.nt;
@@ -1386,6 +1472,12 @@ static void inst_layout(const dl_ws* W, Inst& I, const dl_model* model, bool two
   I.dim = I.m.dim_theta;
   const ModelDev& m = I.m;
   I.qp_ring = !W->keep_qp;
+  // without observations Q_c is Q_p and the two half log-determinants of Eq. 8
+  // cancel to the bit when both come from the same sweep; in mixed precision
+  // the sweep's log|Q_p| of a coregional model carries up to 6e-5 of FP32
+  // rounding (nv = 1: 8e-8), which f keeps as it was
+  I.qp_kron = I.qp_ring && m.family == DL_MODEL_SEPARABLE && m.m_total > 0 &&
+              (!W->mixed || m.nv == 1);
   I.ldbr = m.bp + m.ap;
   I.mixed = W->mixed;
   I.eb = I.mixed ? 4 : 8;
@@ -1404,7 +1496,9 @@ static void inst_buffers(const dl_ws* W, Inst& I, Alloc&& A) {
   const int64_t bb = (int64_t)bp * bp;
   const int xs = I.two ? 1 : 0;  // extra spare slot of chain B
   const size_t eb = I.eb;
-  if (I.qp_ring) {
+  if (I.qp_kron) {
+    A(sizeof(double) * bb, (void**)&I.Dp);
+  } else if (I.qp_ring) {
     A(sizeof(double) * (I.two ? 5 : 2) * bb, (void**)&I.Dp);
     A(eb * (I.two ? 7 : 3) * bb, (void**)&I.Bp);
   } else {
@@ -1455,7 +1549,7 @@ static void inst_buffers(const dl_ws* W, Inst& I, Alloc&& A) {
     for (int w = 0; w < 2; ++w) {
       A(sizeof(double) * bb, (void**)&I.lbuf[w]);
       A(nc, (void**)&I.dctr[w]);
-      if (I.two) {
+      if (I.two && !(w == 0 && I.qp_kron)) {
         A(sizeof(double) * bb, (void**)&I.lbufB[w]);
         A(nc, (void**)&I.dctrB[w]);
       }
@@ -1463,7 +1557,7 @@ static void inst_buffers(const dl_ws* W, Inst& I, Alloc&& A) {
   }
   if (I.two) {
     A(tip, (void**)&I.PcB);
-    for (int w = 0; w < 2; ++w) A(ftemp, (void**)&I.ttempB[w]);
+    for (int w = I.qp_kron ? 1 : 0; w < 2; ++w) A(ftemp, (void**)&I.ttempB[w]);
     A(sizeof(double) * I.ldbr, (void**)&I.uB);
     A(sizeof(double) * GEMV_KS * I.ldbr, (void**)&I.gpartB);
     A(sizeof(double) * (ap > 0 ? ap : 1), (void**)&I.xPB);

@@ -8,6 +8,7 @@ namespace dl {
 //   [C_LOGPRIOR]        log p(theta)
 //   [C_LLCONST]         sum_j m_j/2 log tau_j - m/2 log 2pi (Poisson: 0)
 //   [C_BAD]             1 if theta maps outside the model (NaN, |rho| = 1)
+//   [C_LOGT]            ns sum_i log(1 - rho_i^2) (separable family)
 //   [C_TAU + j]         tau_y of response j (Poisson: 1, unused)
 //   [C_D + ((tt*3 + k)*3 + j)*NPIECE + c]
 //                       weight of FEM piece c (0: C, 1: G, 2: G C^-1 G,
@@ -20,6 +21,7 @@ enum : int {
   C_LOGPRIOR = 0,
   C_LLCONST = 1,
   C_BAD = 2,
+  C_LOGT = 3,
   C_TAU = 4,
   C_D = 8,
   C_B = 8 + 27 * NPIECE,
