@@ -11,8 +11,7 @@ namespace {
 constexpr int NB = 64;
 constexpr int LDL = NB + 2;         // LDS row stride: 528 B, 16-byte aligned rows
 constexpr int TILE_LDS = NB * LDL;  // doubles of one staged 64 x 64 tile
-constexpr int POTRF_CW = 4;         // columns per wave (one panel) of the tile factor
-constexpr int POTRF_NT = NB / POTRF_CW * 64;  // threads of a tile-factor workgroup (16 waves)
+constexpr int POTRF_NT = 1024;      // threads of a tile-factor workgroup (16 waves)
 typedef double v4d __attribute__((ext_vector_type(4)));
 }
 
@@ -35,29 +34,21 @@ __device__ __forceinline__ void cstore(double* p, double v) {
 }
 // p must point to global memory
 __device__ __forceinline__ double global_load(const double* p) { return *(const gdouble*)p; }
-// COH: a device-coherent load of global memory; otherwise a plain load
-// through a generic pointer (the tile factor also reads LDS tiles this way)
-template <bool COH>
-__device__ __forceinline__ double gload(const double* p) {
-  if constexpr (COH) return cload(p);
-  else return *p;
-}
+__device__ __forceinline__ void global_store(double* p, double v) { *(gdouble*)p = v; }
 template <bool COH>
 __device__ __forceinline__ void gstore(double* p, double v) {
   if constexpr (COH) cstore(p, v);
   else *p = v;
 }
 
-// 1/sqrt(x) for x > 0: hardware estimate refined by two Newton steps
-// y <- y + (y/2)(1 - x y^2), each of which squares the relative error.
+// 1/sqrt(x) for x > 0: hardware estimate (relative error e0 below 2^-20)
+// refined by one cubic step y (1 + e/2 + 3/8 e^2), e = 1 - x y^2, which leaves
+// 5/16 e^3 = 5/2 e0^3 before rounding: four dependent operations where two
+// Newton steps take six.
 __device__ __forceinline__ double rsqrt_nr(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    const double e = __builtin_fma(-(x * y), y, 1.0);
-    y = __builtin_fma(0.5 * y, e, y);
-  }
-  return y;
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-(x * y), y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
 
 // One 16x16 block of a product of LDS tiles stored S[k*LDL + c]:
@@ -77,125 +68,225 @@ __device__ __forceinline__ void mfma1_k64(const double* P, int p0, const double*
   }
 }
 
-// S[k*LDL + r] = X[r + k*ldx] for the 64 x 64 tile X (column-major).
-template <int NT>
-__device__ __forceinline__ void stage_tile(const double* __restrict__ X, int64_t ldx,
-                                           double* S) {
-#pragma unroll
-  for (int idx = threadIdx.x; idx < NB * NB; idx += NT) {
-    const int r = idx & 63, k = idx >> 6;
-    S[k * LDL + r] = X[r + (int64_t)k * ldx];
+// threadIdx.x and this lane's index in its wave as values of their own at each
+// place: address arithmetic on them is then not kept in registers over the
+// long bodies around it (the tile kernels have 128 registers a lane)
+__device__ __forceinline__ int thread_index() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+__device__ __forceinline__ int lane_index() { return thread_index() & 63; }
+
+// ---- one 16-column panel of the tile factor, by one wave --------------------------------
+//
+// Lane i holds row i % 16 of the panel's 16 x 16 diagonal block in rd (every
+// group of 16 lanes has all of it) and one row of the panel's other rows in
+// rp: X L^T = B row by row.  The factor L(c, q) that the update of column c
+// needs is in lane c of each group's rd[q], and the FP64 FMA takes it from
+// there itself (DPP row_newbcast: lane N of a row of 16 to the whole row), one
+// instruction per update.  Reading it into a scalar (v_readlane, two per
+// factor) stalls the wave for about 16 cycles per use.  A VALU result must be
+// two wait states old when a DPP operand reads it; the statements are volatile
+// and so stay in order, and the ones that can come right after their operand's
+// definition carry the wait.
+template <int LANE>
+__device__ __forceinline__ double row_bcast(double x) {
+  double r;
+  asm volatile("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf"
+               : "=v"(r)
+               : "v"(x), "n"(LANE));
+  return r;
+}
+
+// rd[C] -= L(C, Q) rd[Q] and rp[C] -= L(C, Q) rp[Q]
+template <int Q, int C>
+__device__ __forceinline__ void panel_update(double (&rd)[16], double (&rp)[16]) {
+  if constexpr (C == Q + 1)
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f64_dpp %0, %2, -%2 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %2, -%3 row_newbcast:%4 row_mask:0xf bank_mask:0xf"
+                 : "+v"(rd[C]), "+v"(rp[C])
+                 : "v"(rd[Q]), "v"(rp[Q]), "n"(C));
+  else
+    asm volatile("v_fmac_f64_dpp %0, %2, -%2 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n\t"
+                 "v_fmac_f64_dpp %1, %2, -%3 row_newbcast:%4 row_mask:0xf bank_mask:0xf"
+                 : "+v"(rd[C]), "+v"(rp[C])
+                 : "v"(rd[Q]), "v"(rp[Q]), "n"(C));
+}
+template <int Q, int C>
+__device__ __forceinline__ void panel_updates(double (&rd)[16], double (&rp)[16]) {
+  if constexpr (C < 16) {
+    panel_update<Q, C>(rd, rp);
+    panel_updates<Q, C + 1>(rd, rp);
+  }
+}
+
+// Columns Q .. 15 of the panel, d the pivot of column Q.  A pivot that is not
+// positive makes its whole column NaN, and all later ones.  Column Q + 1 is
+// updated first, so that its pivot's chain overlaps the updates of the columns
+// after it.
+template <int Q>
+__device__ __forceinline__ void panel_columns(double (&rd)[16], double (&rp)[16], double d) {
+  const double rs = rsqrt_nr(d);
+  rd[Q] *= rs;
+  rp[Q] *= rs;
+  if constexpr (Q + 1 < 16) {
+    panel_update<Q, Q + 1>(rd, rp);
+    d = row_bcast<Q + 1>(rd[Q + 1]);
+    panel_updates<Q, Q + 2>(rd, rp);
+    panel_columns<Q + 1>(rd, rp, d);
   }
 }
 
 // Cholesky A = L L^T of one 64 x 64 SPD tile and G = L^{-1}, by one
-// workgroup of NB/CW waves.  Lane i of wave w keeps row i of the CW columns
-// CW*w .. CW*w+CW-1 (panel w) of the trailing matrix (r) and the same rows of
-// column i of the inverse being eliminated (g).  Panels are factored in
-// order, one barrier each.  Iteration k:
-//  * wave k factors panel k in its registers: per column s, the pivot from
-//    lane s (v_readlane), one reciprocal square root, L(:, s) = A(:, s) /
-//    sqrt(A(s, s)) (zero above the diagonal), and the update of the panel's
-//    later columns with L(c, s) taken from lane c; it then forms rows
-//    CW*k .. of G by the same eliminations on g, and publishes both to LDS;
-//  * after the barrier every later wave applies the rank-CW update of panel
-//    k to its columns and its rows of G (L and G rows read back from LDS).
-// Each element receives its updates one FMA per column, in column order, so
-// the results do not depend on CW.  Every LDS slot is written once, so one
-// barrier a panel suffices.
+// workgroup of 16 waves, in four panels of 16 columns.  What bounds it is the
+// chain of 64 pivots (each: broadcast, reciprocal square root, scaling, update
+// of the next column), so one wave runs a whole panel in its registers with
+// no barrier inside it, and everything that is a product runs on the matrix
+// cores of the other waves, where it hides behind the next panel:
+//  * panel p, wave 0 (panel_columns): the diagonal block, the rows below it and,
+//    as 16 more right-hand rows (those of the identity, solved to L_pp^-T), the
+//    block's inverse;
+//  * after it, one 16 x 16 block per wave: the trailing blocks A_IJ -= L_Ip
+//    L_Jp^T, and row p of the inverse, G_pj = -G_pp T_pj (j < p);
+//  * beside panel p + 1: T_rj += L_rp G_pj for the rows r > p below, and (p =
+//    2) the first 48 rows of G are stored.
+// A panel takes about 2 300 cycles (145 a pivot).  One 4-column panel per wave
+// and 16 hand-overs through LDS took 420 cycles a pivot: the launch of one tile
+// went from 12.7 to 10.0 us, a panel step's launch from 21.6 to 18.0 us, a
+// persistent launch over two blocks of 32 tiles from 783 to 693 us.
 //
-// src/lds: the tile (column-major, global or LDS); Lc, Gk: two LDS tiles of
-// TILE_LDS doubles (Lc[k*LDL + i] = L(i, k), Gk[k*LDL + c] = G(k, c)).
-// Outputs as described for PotrfTileArgs (A/lda: where mode 0 writes L and
-// mode 1 writes G).
-// COH: G (and L) are stored device-coherent; COH_SRC: src is global memory
-// read device-coherent (false: a plain load, for LDS or same-workgroup data).
-template <int CW, bool COH = false, bool COH_SRC = COH>
+// src/lds: the tile (column-major, global), copied to Lc first; null when the
+// caller has it in Lc already (Lc[k*LDL + i] = A(i, k), after a barrier).
+// Lc, Gk: two LDS tiles of TILE_LDS doubles; on return (after a barrier) Lc
+// holds L as it held A and Gk[k*LDL + c] = G(k, c), both in the lower triangle
+// (other entries are undefined).  Outputs as described for PotrfTileArgs (A/lda: where mode 0
+// writes L and mode 1 writes G).
+// COH: G (and L) are stored device-coherent.
+template <bool COH = false>
 __device__ __forceinline__ void potrf_body(const double* src, int64_t lds, double* Lc,
-                                           double* Gk, int* sbad, double* A, int64_t lda,
+                                           double* Gk, double* A, int64_t lda,
                                            double* Ginv, double* logdiag, int64_t* info,
                                            int64_t row0, int mode) {
-  constexpr int NW = NB / CW;
-  constexpr int NT = NW * 64;
-  const int i = threadIdx.x & 63;
+  constexpr int PW = 16, NP = NB / PW;  // panel width, panels
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (threadIdx.x == 0) *sbad = NB;
-  double r[CW], g[CW];
+  double* const dst = mode == 0 ? Ginv : A;
+  const int64_t ldd = mode == 0 ? NB : lda;
+  if (src) {
 #pragma unroll
-  for (int q = 0; q < CW; ++q) {
-    r[q] = gload<COH_SRC>(&src[(int64_t)i + (int64_t)(CW * wv + q) * lds]);
-    g[q] = (CW * wv + q == i) ? 1.0 : 0.0;
-  }
-  __syncthreads();
-#pragma unroll 1
-  for (int k = 0; k < NW; ++k) {
-    const int c0 = CW * k;
-    if (wv == k) {
-      double rsv[CW], Ls[CW][CW];
-      int bad = NB;
-#pragma unroll
-      for (int q = 0; q < CW; ++q) {
-        const int s = c0 + q;
-        const double d = readlane_f64(r[q], s);
-        const bool ok = d > 0.0;  // false for NaN too
-        bad = ok ? bad : min(bad, s);
-        const double rs = rsqrt_nr(ok ? d : __builtin_nan(""));
-        rsv[q] = rs;
-        r[q] = (i > s) ? r[q] * rs : (i == s ? d * rs : 0.0);
-#pragma unroll
-        for (int qq = q + 1; qq < CW; ++qq) {
-          Ls[qq][q] = readlane_f64(r[q], c0 + qq);  // L(c0 + qq, s)
-          r[qq] = __builtin_fma(-r[q], Ls[qq][q], r[qq]);
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < CW; ++q) Lc[(c0 + q) * LDL + i] = r[q];
-      // rows c0 .. of G: scale by 1/L(s, s), eliminate within the panel
-#pragma unroll
-      for (int q = 0; q < CW; ++q) {
-        g[q] *= rsv[q];
-#pragma unroll
-        for (int qq = q + 1; qq < CW; ++qq) g[qq] = __builtin_fma(-Ls[qq][q], g[q], g[qq]);
-      }
-#pragma unroll
-      for (int q = 0; q < CW; ++q) Gk[(c0 + q) * LDL + i] = g[q];
-      if (bad < NB && i == 0) atomicMin(sbad, bad);
+    for (int e = 0; e < NB * NB / POTRF_NT; ++e) {
+      const int idx = threadIdx.x + e * POTRF_NT;
+      Lc[(idx >> 6) * LDL + (idx & 63)] = src[(idx & 63) + (idx >> 6) * lds];
     }
     __syncthreads();
-    if (wv > k) {
-      double li[CW], gi[CW];
+  }
+  // 16 x 16 block (block row, block column) of a product of LDS operands
+  // stored k-major: acc[a][b] += sum_k P(k, a) Q(k, b) over 16 k
+  auto mm = [](const double* P, int ps, const double* Q, int qs, int lk, v4d acc) {
 #pragma unroll
-      for (int q = 0; q < CW; ++q) {
-        li[q] = Lc[(c0 + q) * LDL + i];
-        gi[q] = Gk[(c0 + q) * LDL + i];
+    for (int k0 = 0; k0 < PW; k0 += 4)
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(P[(k0 + lk) * ps], Q[(k0 + lk) * qs], acc, 0,
+                                                 0, 0);
+    return acc;
+  };
+#pragma unroll 1
+  for (int p = 0; p < NP; ++p) {
+    const int c0 = PW * p;
+    const int i = lane_index();
+    const int lr = i & 15, lk = i >> 4;
+    if (wv == 0) {
+      // lane group g: the identity (g = 0), rows 16 (p + g) .. below the
+      // diagonal block, or rows above it (whose results nobody reads)
+      const int row = PW * ((p + lk) & (NP - 1)) + lr;
+      double rd[PW], rp[PW];
+#pragma unroll
+      for (int q = 0; q < PW; ++q) rd[q] = Lc[(c0 + q) * LDL + c0 + lr];
+#pragma unroll
+      for (int q = 0; q < PW; ++q) rp[q] = Lc[(c0 + q) * LDL + row];
+      if (lk == 0) {
+#pragma unroll
+        for (int q = 0; q < PW; ++q) rp[q] = lr == q ? 1.0 : 0.0;
       }
+      panel_columns<0>(rd, rp, row_bcast<0>(rd[0]));
+      double* const out = (lk == 0 ? Gk : Lc) + c0 * LDL + row;
 #pragma unroll
-      for (int q = 0; q < CW; ++q) {
+      for (int q = 0; q < PW; ++q) out[q * LDL] = rp[q];
+      if (lk == 0) {
 #pragma unroll
-        for (int qq = 0; qq < CW; ++qq) {
-          const double ls = Lc[(c0 + q) * LDL + CW * wv + qq];  // L(CW*wv + qq, c0 + q)
-          r[qq] = __builtin_fma(-li[q], ls, r[qq]);
-          g[qq] = __builtin_fma(-ls, gi[q], g[qq]);
+        for (int q = 0; q < PW; ++q) Lc[(c0 + q) * LDL + row] = rd[q];
+      }
+    } else if (p > 0) {
+      // T_rj += L_r,p-1 G_p-1,j, r >= p, j < p (three or four blocks, on waves
+      // that share no SIMD with wave 0)
+      const int t = wv < 4 ? wv - 1 : (wv == 5 ? 3 : NB);
+      if (t < (NP - p) * p) {
+        const int up = p == 1 ? t : (p == 2 ? t >> 1 : 0);  // t / p
+        const int rb = PW * (p + up), jb = PW * (t - up * p), kb = c0 - PW;
+        double* T = Gk + rb * LDL + jb;
+        v4d acc = {0.0, 0.0, 0.0, 0.0};
+        if (jb < kb) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = T[(lk + 4 * e) * LDL + lr];
+        }
+        acc = mm(Lc + kb * LDL + rb + lr, LDL, Gk + kb * LDL + jb + lr, LDL, lk, acc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) T[(lk + 4 * e) * LDL + lr] = acc[e];
+      } else if (p == NP - 1 && wv >= 4 && dst) {
+        // the rows of G above the last panel's, by 12 waves
+        constexpr int R0 = NB - PW;
+        for (int idx = threadIdx.x - 256; idx < R0 * NB; idx += POTRF_NT - 256) {
+          const int rr = idx % R0, cc = idx / R0;
+          gstore<COH>(&dst[rr + cc * ldd], (rr >= cc) ? Gk[rr * LDL + cc] : 0.0);
         }
       }
     }
+    __syncthreads();
+    const int nt = NP - 1 - p, nu = nt * (nt + 1) / 2;
+    if (wv < nu) {
+      // trailing block (I, J), the next panel's column first
+      int J = 0, u = wv;
+      while (u >= nt - J) {
+        u -= nt - J;
+        ++J;
+      }
+      const int ib = PW * (p + 1 + J + u), jb = PW * (p + 1 + J);
+      double* C = Lc + jb * LDL + ib;
+      v4d old, acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) old[e] = C[(lk + 4 * e) * LDL + lr];
+      acc = mm(Lc + c0 * LDL + jb + lr, LDL, Lc + c0 * LDL + ib + lr, LDL, lk, acc);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) C[(lk + 4 * e) * LDL + lr] = old[e] - acc[e];
+    } else if (wv < nu + p) {
+      const int jb = PW * (wv - nu);
+      double* T = Gk + c0 * LDL + jb;
+      v4d acc = {0.0, 0.0, 0.0, 0.0};
+      acc = mm(Gk + (c0 + lr) * LDL + c0, 1, T + lr, LDL, lk, acc);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) T[(lk + 4 * e) * LDL + lr] = -acc[e];
+    }
+    __syncthreads();
   }
-  if (wv == 0 && logdiag) logdiag[i] = log(Lc[i * LDL + i]);
-  if (threadIdx.x == 0 && *sbad < NB && info)
-    atomicCAS((unsigned long long*)info, 0ull, (unsigned long long)(row0 + *sbad + 1));
+  const int i = lane_index();
+  if (wv == 15) {
+    // the first column that is not a number is the first bad pivot
+    const double d = Lc[i * LDL + i];
+    if (logdiag) logdiag[i] = log(d);
+    const unsigned long long nan = __ballot(!(d > 0.0));
+    if (nan && info && i == 0)
+      atomicCAS((unsigned long long*)info, 0ull, (unsigned long long)(row0 + __ffsll(nan)));
+  }
   if (mode == 0) {
-    for (int idx = threadIdx.x; idx < NB * NB; idx += NT) {
+    for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT) {
       const int rr = idx & 63, cc = idx >> 6;
-      A[rr + (int64_t)cc * lda] = Lc[cc * LDL + rr];
+      A[rr + (int64_t)cc * lda] = (rr >= cc) ? Lc[cc * LDL + rr] : 0.0;
     }
   }
-  double* dst = mode == 0 ? Ginv : A;
-  const int64_t ldd = mode == 0 ? NB : lda;
   if (dst) {
-    for (int idx = threadIdx.x; idx < NB * NB; idx += NT) {
-      const int rr = idx & 63, cc = idx >> 6;
-      gstore<COH>(&dst[rr + cc * ldd], (rr >= cc) ? Gk[rr * LDL + cc] : 0.0);
-    }
+    constexpr int R0 = NB - PW;
+    const int rr = R0 + (threadIdx.x & 15), cc = threadIdx.x >> 4;
+    gstore<COH>(&dst[rr + cc * ldd], (rr >= cc) ? Gk[rr * LDL + cc] : 0.0);
   }
 }
 
@@ -203,9 +294,7 @@ __global__ __launch_bounds__(POTRF_NT) void k_potrf_tile(const PotrfTileArgs* __
   const PotrfTileArgs a = args[blockIdx.x];
   __shared__ __align__(16) double Lc[TILE_LDS];
   __shared__ __align__(16) double Gk[TILE_LDS];
-  __shared__ int sbad;
-  potrf_body<POTRF_CW>(a.A, a.lda, Lc, Gk, &sbad, a.A, a.lda, a.Ginv, a.logdiag, a.info,
-                       a.row0, a.mode);
+  potrf_body(a.A, a.lda, Lc, Gk, a.A, a.lda, a.Ginv, a.logdiag, a.info, a.row0, a.mode);
 }
 
 hipError_t launch_potrf_tiles(const PotrfTileArgs* args, int count,
@@ -213,6 +302,41 @@ hipError_t launch_potrf_tiles(const PotrfTileArgs* args, int count,
   if (count <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_potrf_tile, dim3(count), dim3(POTRF_NT), 0, s, args);
   return hipGetLastError();
+}
+
+constexpr int DPER = NB * NB / POTRF_NT;  // elements of a tile per lane
+
+// The lane's DPER elements of the 64 x 64 tile X (global, ld): element idx =
+// threadIdx.x + e * POTRF_NT is X(idx & 63, idx >> 6).  All loads are issued
+// before any is used.
+template <bool COH>
+__device__ __forceinline__ void tile_regs(const double* __restrict__ X, int64_t ld,
+                                          double (&v)[DPER]) {
+  const int tid = thread_index();
+#pragma unroll
+  for (int e = 0; e < DPER; ++e) {
+    const int idx = tid + e * POTRF_NT;
+    const double* p = &X[(idx & 63) + (int64_t)(idx >> 6) * ld];
+    v[e] = COH ? cload(p) : global_load(p);
+  }
+}
+// S[k*LDL + r] = X(r, k)
+__device__ __forceinline__ void regs_to_cols(const double (&v)[DPER], double* S) {
+  const int tid = thread_index();
+#pragma unroll
+  for (int e = 0; e < DPER; ++e) {
+    const int idx = tid + e * POTRF_NT;
+    S[(idx >> 6) * LDL + (idx & 63)] = v[e];
+  }
+}
+// S[k*LDL + r] = X(k, r) (the transpose)
+__device__ __forceinline__ void regs_to_rows(const double (&v)[DPER], double* S) {
+  const int tid = thread_index();
+#pragma unroll
+  for (int e = 0; e < DPER; ++e) {
+    const int idx = tid + e * POTRF_NT;
+    S[(idx & 63) * LDL + (idx >> 6)] = v[e];
+  }
 }
 
 // ---- fused panel step ---------------------------------------------------------------
@@ -230,24 +354,6 @@ hipError_t launch_potrf_tiles(const PotrfTileArgs* args, int count,
 // in place of its tile.  The inverse's workgroups form one or two tile
 // products each (see PanelTask).
 
-// S[k*LDL + r] = X(r, k) for the 64 x 64 tile X (ld), coalesced along r.
-template <bool COH = false>
-__device__ __forceinline__ void stage_cols(const double* __restrict__ X, int64_t ld, double* S) {
-  for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT) {
-    const int r = idx & 63, k = idx >> 6;
-    S[k * LDL + r] = gload<COH>(&X[r + (int64_t)k * ld]);
-  }
-}
-
-// S[k*LDL + r] = X(k, r) (the transpose), coalesced along k.
-template <bool COH = false>
-__device__ __forceinline__ void stage_rows(const double* __restrict__ X, int64_t ld, double* S) {
-  for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT) {
-    const int k = idx & 63, r = idx >> 6;
-    S[k * LDL + r] = gload<COH>(&X[k + (int64_t)r * ld]);
-  }
-}
-
 __device__ __forceinline__ double* stage_tile(const PanelTask& T, int r, int c) {
   return T.stage + ((int64_t)(r * (r - 1) / 2 + c)) * (NB * NB);
 }
@@ -258,7 +364,7 @@ __device__ __forceinline__ double* stage_tile(const PanelTask& T, int r, int c) 
 __device__ void panel_inverse(const PanelTask& T, int role, int loc, double* S0, double* S1) {
   const int j = T.j;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int l = threadIdx.x & 63;
+  const int l = lane_index();
   const int lr = l & 15, lk = l >> 4;
   const int p0 = 16 * (wv >> 2), q0 = 16 * (wv & 3);
   const int64_t ld = T.ld;
@@ -266,13 +372,6 @@ __device__ void panel_inverse(const PanelTask& T, int role, int loc, double* S0,
   auto tileA = [&](int r, int c) { return A + (int64_t)r * NB + (int64_t)c * NB * ld; };
   const int r = (role == 2) ? j : j + 1 + loc / j;
   const int c = (role == 2) ? loc : loc % j;
-  if (role == 2 && c == 0 && j >= 2) {
-    // G(j-1, j-2) from stage into place (L(j-1, j-2) is read no more)
-    const double* src = stage_tile(T, j - 1, j - 2);
-    double* dst = tileA(j - 1, j - 2);
-    for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT)
-      dst[(idx & 63) + (int64_t)(idx >> 6) * ld] = src[idx];
-  }
   // G(j-1, c): the diagonal tile, the staged G(j-1, j-2), or in place
   const double* Gk;
   int64_t ldg;
@@ -283,25 +382,36 @@ __device__ void panel_inverse(const PanelTask& T, int role, int loc, double* S0,
   if (c <= j - 2) {
     const double* Sp = stage_tile(T, r, c);
 #pragma unroll
-    for (int rg = 0; rg < 4; ++rg) prev[rg] = Sp[(q0 + lr) + (p0 + lk + 4 * rg) * NB];
+    for (int rg = 0; rg < 4; ++rg) prev[rg] = global_load(&Sp[(q0 + lr) + (p0 + lk + 4 * rg) * NB]);
   }
-  stage_cols(tileA(r, j - 1), ld, S0);  // Y = L(r, j-1)
-  stage_rows(Gk, ldg, S1);              // X = G(j-1, c)^T
+  double vy[DPER], vx[DPER], vg[DPER];
+  tile_regs<false>(tileA(r, j - 1), ld, vy);  // Y = L(r, j-1)
+  tile_regs<false>(Gk, ldg, vx);              // X = G(j-1, c)^T
+  // G_jj, for the second product: from the side ring during the panel steps,
+  // in place for the closing launch
+  if (role == 2) tile_regs<false>(T.last ? tileA(j, j) : T.gside + (int64_t)(j & 1) * NB * NB,
+                                  T.last ? ld : NB, vg);
+  if (role == 2 && c == 0 && j >= 2) {
+    // G(j-1, j-2) from stage into place (L(j-1, j-2) is read no more)
+    const double* src = stage_tile(T, j - 1, j - 2);
+    double* dst = tileA(j - 1, j - 2);
+    for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT)
+      global_store(&dst[(idx & 63) + (int64_t)(idx >> 6) * ld], global_load(&src[idx]));
+  }
+  regs_to_cols(vy, S0);
+  regs_to_rows(vx, S1);
   __syncthreads();
   v4d t = {prev[0], prev[1], prev[2], prev[3]};
   mfma1_k64(S1, p0, S0, q0, t);         // t = S(r, c) + L(r, j-1) G(j-1, c)
   if (role == 3) {
     double* Sd = stage_tile(T, r, c);
 #pragma unroll
-    for (int rg = 0; rg < 4; ++rg) Sd[(q0 + lr) + (p0 + lk + 4 * rg) * NB] = t[rg];
+    for (int rg = 0; rg < 4; ++rg) global_store(&Sd[(q0 + lr) + (p0 + lk + 4 * rg) * NB], t[rg]);
     return;
   }
-  // G(j, c) = -G_jj t: G_jj from the side ring during the panel steps, in
-  // place for the closing launch
-  const double* Gjj = T.last ? tileA(j, j) : T.gside + (int64_t)(j & 1) * NB * NB;
-  const int64_t ldj = T.last ? ld : NB;
+  // G(j, c) = -G_jj t
   __syncthreads();  // S0, S1 are read no more
-  stage_cols(Gjj, ldj, S0);             // Y = G_jj
+  regs_to_cols(vg, S0);                 // Y = G_jj
 #pragma unroll
   for (int rg = 0; rg < 4; ++rg) S1[(q0 + lr) * LDL + p0 + lk + 4 * rg] = t[rg];  // X = t^T
   __syncthreads();
@@ -312,13 +422,13 @@ __device__ void panel_inverse(const PanelTask& T, int role, int loc, double* S0,
   if (c == j - 1) { dst = stage_tile(T, j, j - 1); ldd = NB; }
   else { dst = tileA(j, c); ldd = ld; }
 #pragma unroll
-  for (int rg = 0; rg < 4; ++rg) dst[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * ldd] = -g[rg];
+  for (int rg = 0; rg < 4; ++rg)
+    global_store(&dst[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * ldd], -g[rg]);
 }
 
 __global__ __launch_bounds__(POTRF_NT) void k_panel_update(const PanelTask* __restrict__ tasks,
                                                            int ntask) {
   __shared__ __align__(16) double pool[3 * TILE_LDS];
-  __shared__ int sbad;
   double* S0 = pool;
   double* S1 = pool + TILE_LDS;
   double* S2 = pool + 2 * TILE_LDS;
@@ -357,46 +467,36 @@ __global__ __launch_bounds__(POTRF_NT) void k_panel_update(const PanelTask* __re
   const int64_t ti0 = (int64_t)(T.j + 1 + I) * NB, tj0 = (int64_t)(T.j + 1 + J) * NB;
   const int64_t pc = (int64_t)T.j * NB * T.ld;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int l = threadIdx.x & 63;
+  const int l = lane_index();
   const int lr = l & 15, lk = l >> 4;
   const int p0 = 16 * (wv >> 2), q0 = 16 * (wv & 3);  // this wave's 16 x 16 block
   double* C = T.A + ti0 + tj0 * T.ld;
   const bool diag = (I == J);
-  constexpr int PER = NB * NB / POTRF_NT;
-  double vp[PER], vq[PER], cpre[4], dpre[4];
-  {
-    const double* Li = T.A + ti0 + pc;
-    const double* Lj = T.A + tj0 + pc;
+  const int64_t co = (q0 + lr) + (int64_t)(p0 + lk) * T.ld;  // element rg at co + 4 rg ld
+  double vp[DPER], vq[DPER], cpre[4], dpre[4];
+  // every load is issued before the first is used: a tile on the diagonal
+  // reads its one operand twice rather than branch, and the factoring and
+  // column workgroups load the diagonal tile j+1 into registers of their own
+  // (left undefined elsewhere).  With loads through generic pointers and a
+  // branch that kept them apart the widest launches took 1.5 times as long
+  tile_regs<false>(T.A + ti0 + pc, T.ld, vp);
+  tile_regs<false>(T.A + tj0 + pc, T.ld, vq);
 #pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int idx = threadIdx.x + e * POTRF_NT;
-      const int64_t o = (idx & 63) + (int64_t)(idx >> 6) * T.ld;
-      vp[e] = Li[o];
-      vq[e] = diag ? 0.0 : Lj[o];
-    }
+  for (int rg = 0; rg < 4; ++rg) cpre[rg] = global_load(&C[co + (int64_t)(4 * rg) * T.ld]);
+  if (role <= 1) {
+    const double* Dj = T.A + (int64_t)(T.j + 1) * NB * (T.ld + 1);
 #pragma unroll
-    for (int rg = 0; rg < 4; ++rg) cpre[rg] = C[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * T.ld];
-    if (role == 1) {
-      const double* Dj = T.A + (int64_t)(T.j + 1) * NB * (T.ld + 1);
-#pragma unroll
-      for (int rg = 0; rg < 4; ++rg)
-        dpre[rg] = Dj[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * T.ld];
-    }
-    if (role == 0 && T.j >= 1) {
-      // G_j from the side ring into diagonal tile j (read by nobody now)
-      const double* src = T.gside + (int64_t)(T.j & 1) * NB * NB;
-      double* dst = T.A + (int64_t)T.j * NB * (T.ld + 1);
-      for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT)
-        dst[(idx & 63) + (int64_t)(idx >> 6) * T.ld] = src[idx];
-    }
-#pragma unroll
-    for (int e = 0; e < PER; ++e) {
-      const int idx = threadIdx.x + e * POTRF_NT;
-      const int o = (idx >> 6) * LDL + (idx & 63);
-      S0[o] = vp[e];
-      if (!diag) S2[o] = vq[e];
-    }
+    for (int rg = 0; rg < 4; ++rg) dpre[rg] = global_load(&Dj[co + (int64_t)(4 * rg) * T.ld]);
   }
+  if (role == 0 && T.j >= 1) {
+    // G_j from the side ring into diagonal tile j (read by nobody now)
+    const double* src = T.gside + (int64_t)(T.j & 1) * NB * NB;
+    double* dst = T.A + (int64_t)T.j * NB * (T.ld + 1);
+    for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT)
+      global_store(&dst[(idx & 63) + (int64_t)(idx >> 6) * T.ld], global_load(&src[idx]));
+  }
+  regs_to_cols(vp, S0);
+  if (!diag) regs_to_cols(vq, S2);
   __syncthreads();
   // (L_I L_J^T)^T = L_J L_I^T: D[n][m] = sum_c L_J(n, c) L_I(m, c)
   const double* LJ = diag ? S0 : S2;
@@ -405,45 +505,42 @@ __global__ __launch_bounds__(POTRF_NT) void k_panel_update(const PanelTask* __re
   if (role == 4) {
 #pragma unroll
     for (int rg = 0; rg < 4; ++rg)
-      C[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * T.ld] = cpre[rg] - u0[rg];
+      global_store(&C[co + (int64_t)(4 * rg) * T.ld], cpre[rg] - u0[rg]);
     return;
   }
-  if (role == 1) {
-    // the diagonal tile j+1 updated exactly as the factoring workgroup does
-    v4d v0 = {0.0, 0.0, 0.0, 0.0};
-    mfma1_k64(S2, p0, S2, q0, v0);
-    __syncthreads();  // S0, S2 are read no more
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) S1[(p0 + lk + 4 * rg) * LDL + q0 + lr] = dpre[rg] - v0[rg];
-    __syncthreads();
-    potrf_body<POTRF_CW>(S1, LDL, S0, S2, &sbad, nullptr, 0, nullptr, nullptr, nullptr, 0, 1);
-    __syncthreads();
-    // G staged as S1[k][r] = G(r, k) (zero above the diagonal); the updated
-    // panel tile as S0[c][m] = A(m, c)
-    for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT) {
-      const int r = idx & 63, k = idx >> 6;
-      S1[k * LDL + r] = (r >= k) ? S2[r * LDL + k] : 0.0;
-    }
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg) S0[(p0 + lk + 4 * rg) * LDL + q0 + lr] = cpre[rg] - u0[rg];
-    __syncthreads();
-    // L^T = G A^T: D[c][m] = sum_k G(c, k) A(m, k), k <= c < p0 + 16
-    v4d a0 = {0.0, 0.0, 0.0, 0.0};
-    mfma1_k64(S1, p0, S0, q0, a0, p0 + 16);  // L(m = q0 + lr, c = p0 + lk + 4r)
-#pragma unroll
-    for (int rg = 0; rg < 4; ++rg)
-      C[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * T.ld] = a0[rg];
-    return;
-  }
-  __syncthreads();  // S0 is read no more
-#pragma unroll
-  for (int rg = 0; rg < 4; ++rg) S1[(p0 + lk + 4 * rg) * LDL + q0 + lr] = cpre[rg] - u0[rg];
-  __syncthreads();
-  // while column j+1 below reads diagonal tile j+1, G_{j+1} goes to the ring
+  // the diagonal tile j+1, updated by the column workgroups exactly as by the
+  // factoring one, and its factor.  While column j+1 below reads diagonal tile
+  // j+1, G_{j+1} goes to the ring
   const bool side = T.j + 2 < T.nbk;
   double* dst = side ? T.gside + (int64_t)((T.j + 1) & 1) * NB * NB : C;
-  potrf_body<POTRF_CW>(S1, LDL, S0, S2, &sbad, dst, side ? NB : T.ld, nullptr, T.logdiag,
-                       T.info, T.row0, 1);
+  v4d v0 = u0;
+  if (role == 1) {
+    v0 = (v4d){0.0, 0.0, 0.0, 0.0};
+    mfma1_k64(S2, p0, S2, q0, v0);
+  }
+  __syncthreads();  // S0, S2 are read no more
+#pragma unroll
+  for (int rg = 0; rg < 4; ++rg)
+    S1[(p0 + lk + 4 * rg) * LDL + q0 + lr] = dpre[rg] - v0[rg];
+  __syncthreads();
+  const bool own = role == 0;
+  potrf_body(nullptr, 0, S1, S2, own ? dst : nullptr, side ? NB : T.ld, nullptr,
+             own ? T.logdiag : nullptr, own ? T.info : nullptr, T.row0, 1);
+  if (own) return;
+  // G staged as S1[k][r] = G(r, k) (zero above the diagonal); the updated
+  // panel tile as S0[c][m] = A(m, c)
+  for (int idx = threadIdx.x; idx < NB * NB; idx += POTRF_NT) {
+    const int r = idx & 63, k = idx >> 6;
+    S1[k * LDL + r] = (r >= k) ? S2[r * LDL + k] : 0.0;
+  }
+#pragma unroll
+  for (int rg = 0; rg < 4; ++rg) S0[(p0 + lk + 4 * rg) * LDL + q0 + lr] = cpre[rg] - u0[rg];
+  __syncthreads();
+  // L^T = G A^T: D[c][m] = sum_k G(c, k) A(m, k), k <= c < p0 + 16
+  v4d a0 = {0.0, 0.0, 0.0, 0.0};
+  mfma1_k64(S1, p0, S0, q0, a0, p0 + 16);  // L(m = q0 + lr, c = p0 + lk + 4r)
+#pragma unroll
+  for (int rg = 0; rg < 4; ++rg) global_store(&C[co + (int64_t)(4 * rg) * T.ld], a0[rg]);
 }
 
 int finalize_panels(PanelTask* t, int n) {
@@ -503,7 +600,6 @@ hipError_t launch_panel_updates(const PanelTask* tasks, int ntask, int grid,
 
 namespace {
 constexpr long long kDagWaitTicks = 50000000;  // 0.5 s of the 100 MHz constant clock
-constexpr int DPER = NB * NB / POTRF_NT;        // elements of a tile per lane
 
 typedef __attribute__((address_space(1))) int32_t gint;
 __device__ __forceinline__ int dag_load(const int32_t* p) {
@@ -529,35 +625,6 @@ __device__ bool dag_wait(const int32_t* p, int value, int32_t* abort) {
   }
 }
 
-// The lane's DPER elements of the 64 x 64 tile X (global, ld): element idx =
-// threadIdx.x + e * POTRF_NT is X(idx & 63, idx >> 6).  All loads are issued
-// before any is used.
-template <bool COH>
-__device__ __forceinline__ void tile_regs(const double* __restrict__ X, int64_t ld,
-                                          double (&v)[DPER]) {
-#pragma unroll
-  for (int e = 0; e < DPER; ++e) {
-    const int idx = threadIdx.x + e * POTRF_NT;
-    const double* p = &X[(idx & 63) + (int64_t)(idx >> 6) * ld];
-    v[e] = COH ? cload(p) : global_load(p);
-  }
-}
-// as stage_cols: S[k*LDL + r] = X(r, k)
-__device__ __forceinline__ void regs_to_cols(const double (&v)[DPER], double* S) {
-#pragma unroll
-  for (int e = 0; e < DPER; ++e) {
-    const int idx = threadIdx.x + e * POTRF_NT;
-    S[(idx >> 6) * LDL + (idx & 63)] = v[e];
-  }
-}
-// as stage_rows: S[k*LDL + r] = X(k, r)
-__device__ __forceinline__ void regs_to_rows(const double (&v)[DPER], double* S) {
-#pragma unroll
-  for (int e = 0; e < DPER; ++e) {
-    const int idx = threadIdx.x + e * POTRF_NT;
-    S[(idx & 63) * LDL + (idx >> 6)] = v[e];
-  }
-}
 }  // namespace
 
 __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restrict__ tasks,
@@ -565,15 +632,15 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
                                                        const DagBlock* __restrict__ blocks,
                                                        int nblocks, int32_t* head) {
   __shared__ __align__(16) double pool[3 * TILE_LDS];
-  __shared__ int s_task, s_bad, s_last;
+  __shared__ int s_task, s_last;
   double* S0 = pool;
   double* S1 = pool + TILE_LDS;
   double* S2 = pool + 2 * TILE_LDS;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int l = threadIdx.x & 63;
-  const int lr = l & 15, lk = l >> 4;
   const int p0 = 16 * (wv >> 2), q0 = 16 * (wv & 3);  // this wave's 16 x 16 block
   for (;;) {
+    const int l = lane_index();
+    const int lr = l & 15, lk = l >> 4;
     if (threadIdx.x == 0) s_task = atomicAdd(head, 1);
     __syncthreads();
     const int ti = s_task;
@@ -594,12 +661,14 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
         atomicCAS((unsigned long long*)B.info, 0ull, (unsigned long long)(int64_t)DL_INFO_TIMEOUT);
     }
     __syncthreads();
+    int fk = -1;  // tile to factor, staged in S0
     switch (t.type) {
       case dag::T_F: {
-        double* Akk = tile(B.A, t.k, t.k);
-        potrf_body<POTRF_CW, true>(Akk, ld, S0, S1, &s_bad, Akk, ld, nullptr,
-                                   B.logdiag + (int64_t)t.k * NB, B.info,
-                                   B.row0 + (int64_t)t.k * NB, 1);
+        double va[DPER];
+        tile_regs<true>(tile(B.A, t.k, t.k), ld, va);
+        regs_to_cols(va, S0);
+        __syncthreads();
+        fk = t.k;
         break;
       }
       case dag::T_C: {
@@ -637,9 +706,7 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
           dag::mid_set(t, &m);
           dag_store(B.ctr + m.ctr, m.value);
         }
-        potrf_body<POTRF_CW, true, false>(S0, LDL, S1, S2, &s_bad, Ad, ld, nullptr,
-                                          B.logdiag + (int64_t)k1 * NB, B.info,
-                                          B.row0 + (int64_t)k1 * NB, 1);
+        fk = k1;
         break;
       }
       case dag::T_S: {
@@ -716,6 +783,9 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
         break;
       }
     }
+    if (fk >= 0)
+      potrf_body<true>(nullptr, 0, S0, S2, tile(B.A, fk, fk), ld, nullptr,
+                       B.logdiag + (int64_t)fk * NB, B.info, B.row0 + (int64_t)fk * NB, 1);
     // every lane's stores complete before the counter is set
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();

@@ -440,6 +440,7 @@ struct Inst {
   bool qp_ring = true;
   // separable family, not kept: log|Q_p| from one diagonal block (see
   // seq_logdet_qp); Dp holds that block
+  bool kron = false;     // the model and precision allow it
   bool qp_kron = false;
   // Q_c: full storage, [B_t; R_t] in nt+1 slots of (bp+ap) x bp (nt+2 when
   // two-sided: one spare slot per elimination chain)
@@ -525,6 +526,7 @@ struct dl_ws {
   // (solve with the factor, x += correction unless converged), fin (mu <- x
   // and the final residual), resid (the final residual of mu alone)
   Plan theta_p, asm_p[3], fac_p[3], solve_p, selinv_p, post_p, eval_p;
+  Plan qpsum_p;  // log|Q_p| after fac_p of an evaluation that keeps Q_p
   Plan ref_init_p, ref_res_p, ref_corr_p, ref_fin_p, resid_p;
   bool assembled[2] = {false, false}, factored[2] = {false, false};
   bool solved = false;
@@ -716,6 +718,26 @@ static void seq_assemble(dl_ws* W, Inst& I, bool p, bool c, std::vector<Step>& q
   }
 }
 
+// log|Q_p| from the first diagonal block's and the tip's log L_ii (see
+// seq_logdet_qp).
+static Step qp_logdet_sum(Inst& I, uint64_t key) {
+  const ModelDev& m = I.m;
+  Step sl;
+  sl.key = key;
+  sl.kind = OP_SUM;
+  sl.cat = DL_CAT_OTHER;
+  sl.sum.src = I.logdiag[0];
+  sl.sum.n = m.bp;
+  sl.sum.scale = 2.0 * m.nt;
+  sl.sum.src2 = m.ap > 0 ? I.logdiag[0] + (int64_t)m.nt * m.bp : nullptr;
+  sl.sum.n2 = m.ap;
+  sl.sum.scale2 = 2.0;
+  sl.sum.add = m.nt > 1 ? I.coef + C_LOGT : nullptr;
+  sl.sum.dst = I.logdet2;
+  sl.sum.partial = I.sumpart;
+  return sl;
+}
+
 // log|Q_p| of the separable family from one diagonal block.  Process i has
 // Q^i = T_i (x) Q_s,i with the unit-variance AR1 precision T_i, and Q_p =
 // (Lambda^-1 (x) I)^T diag_i(Q^i) (Lambda^-1 (x) I) mixes them.  The block
@@ -733,7 +755,9 @@ static void seq_assemble(dl_ws* W, Inst& I, bool p, bool c, std::vector<Step>& q
 // 9-point gradient at 30 x 30, nt = 48 from 83.0 to 54.2 ms.  nt = 1
 // holds too: its single block is D_0 without the AR1 factor.  A pivot that
 // fails is reported at its row of D_0.  Q_p kept in full (DL_WS_KEEP_QP: its
-// blocks can be overwritten), the diffusion family (its temporal factors do
+// blocks can be overwritten before bta_factor; an f_obj evaluation, which
+// assembles them itself, forms the same sum from the sweep's first block), the
+// diffusion family (its temporal factors do
 // not share a recurrence) and what inst_layout names take the sweep.
 static void seq_logdet_qp(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
   const ModelDev& m = I.m;
@@ -774,20 +798,7 @@ static void seq_logdet_qp(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
     p.potrf.mode = 0;
     q.push_back(p);
   }
-  Step sl;
-  sl.key = K(tail, 1);
-  sl.kind = OP_SUM;
-  sl.cat = DL_CAT_OTHER;
-  sl.sum.src = logdiag;
-  sl.sum.n = bp;
-  sl.sum.scale = 2.0 * m.nt;
-  sl.sum.src2 = m.ap > 0 ? ltip : nullptr;
-  sl.sum.n2 = m.ap;
-  sl.sum.scale2 = 2.0;
-  sl.sum.add = m.nt > 1 ? I.coef + C_LOGT : nullptr;
-  sl.sum.dst = I.logdet2;
-  sl.sum.partial = I.sumpart;
-  q.push_back(sl);
+  q.push_back(qp_logdet_sum(I, K(tail, 1)));
 }
 
 // BTA Cholesky of Q_p (w = 0) or Q_c (w = 1) of instance I in its
@@ -1322,6 +1333,12 @@ static dl_status build_plans(dl_ws* W) {
   }
   {
     std::vector<std::vector<Step>> seqs;
+    for (auto& I : W->inst)
+      if (I.kron && !I.qp_kron) seqs.push_back({qp_logdet_sum(I, K(0, 0))});
+    merge(seqs, H, W->table, W->qpsum_p);
+  }
+  {
+    std::vector<std::vector<Step>> seqs;
     for (auto& I : W->inst) {
       seqs.emplace_back();
       seqs.back().push_back(misc_step(K(0, 0), DL_CAT_SOLVE, MJ_COPY, I.x, I.rhs, I.m.Np));
@@ -1368,6 +1385,7 @@ static dl_status build_plans(dl_ws* W) {
   W->eval_p.idx.clear();
   append(W->eval_p, W->asm_p[2]);
   append(W->eval_p, W->fac_p[2]);
+  append(W->eval_p, W->qpsum_p);
   append(W->eval_p, W->solve_p);
   if (W->mixed) {
     // a captured graph runs a fixed number of correction steps (instances
@@ -1476,8 +1494,8 @@ static void inst_layout(const dl_ws* W, Inst& I, const dl_model* model, bool two
   // cancel to the bit when both come from the same sweep; in mixed precision
   // the sweep's log|Q_p| of a coregional model carries up to 6e-5 of FP32
   // rounding (nv = 1: 8e-8), which f keeps as it was
-  I.qp_kron = I.qp_ring && m.family == DL_MODEL_SEPARABLE && m.m_total > 0 &&
-              (!W->mixed || m.nv == 1);
+  I.kron = m.family == DL_MODEL_SEPARABLE && m.m_total > 0 && (!W->mixed || m.nv == 1);
+  I.qp_kron = I.kron && I.qp_ring;
   I.ldbr = m.bp + m.ap;
   I.mixed = W->mixed;
   I.eb = I.mixed ? 4 : 8;
@@ -2001,6 +2019,7 @@ static dl_status laplace_pass(dl_ws* W, int nk, hipStream_t s) {
   DL_HIP_CHECK(launch_lap_weights(W->d_lap, B, s));
   DL_HIP_CHECK(run(W, W->asm_p[2], s));
   DL_HIP_CHECK(run(W, W->fac_p[2], s));
+  DL_HIP_CHECK(run(W, W->qpsum_p, s));
   // state: 0 iterating, 1 converged, -1 failed, 2 idle (k >= nk)
   std::vector<int> state(B, 0), steps(B, 0), nh(B, 0);
   std::vector<double> alpha(B, 0.0), out(4 * B, 0.0), hcur(B, 0.0);
@@ -2098,6 +2117,7 @@ static dl_status run_eval(dl_ws* W, hipStream_t s) {
   if (!W->use_graph) {
     DL_HIP_CHECK(run(W, W->asm_p[2], s));
     DL_HIP_CHECK(run(W, W->fac_p[2], s));
+    DL_HIP_CHECK(run(W, W->qpsum_p, s));
     DL_HIP_CHECK(run(W, W->solve_p, s));
     if ((st = refine_eager(W, s, W->mixed ? DL_REFINE_MAX : 0, DL_REFINE_TOL, nullptr)) !=
         DL_OK)
@@ -2191,6 +2211,7 @@ extern "C" dl_status fobj_selinv_eval(dl_ws* W, const double* theta_dev, int32_t
     if ((st = set_refine_tol(W, DL_REFINE_TOL, s)) != DL_OK) return st;
     DL_HIP_CHECK(run(W, W->asm_p[2], s));
     DL_HIP_CHECK(run(W, W->fac_p[2], s));
+    DL_HIP_CHECK(run(W, W->qpsum_p, s));
     DL_HIP_CHECK(hipEventRecord(W->ev_fork, s));
     DL_HIP_CHECK(hipStreamWaitEvent(W->aux_stream, W->ev_fork, 0));
   }
