@@ -541,9 +541,12 @@ hipError_t launch_combine(const CombineJob* jobs, int count, hipStream_t s) {
   return hipGetLastError();
 }
 
-// padded (t*bp + i, arrow at nt*bp) <-> packed (t*b + i, arrow at nt*b)
+// padded (t*bp + i, arrow at nt*bp) <-> packed (t*b + i, arrow at nt*b), vector
+// blockIdx.y of several: padded ones Np apart, packed ones `stride`
 __global__ void k_pack(ModelDev m, const double* __restrict__ in,
-                       double* __restrict__ out) {
+                       double* __restrict__ out, int64_t stride) {
+  in += (int64_t)blockIdx.y * m.Np;
+  out += (int64_t)blockIdx.y * stride;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m.N;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t t = i / m.b;
@@ -554,7 +557,9 @@ __global__ void k_pack(ModelDev m, const double* __restrict__ in,
 }
 
 __global__ void k_unpack(ModelDev m, const double* __restrict__ in,
-                         double* __restrict__ out) {
+                         double* __restrict__ out, int64_t stride) {
+  in += (int64_t)blockIdx.y * stride;
+  out += (int64_t)blockIdx.y * m.Np;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m.Np;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t t = i / m.bp;
@@ -571,14 +576,14 @@ __global__ void k_unpack(ModelDev m, const double* __restrict__ in,
 }
 
 hipError_t launch_pack(const ModelDev& m, const double* padded, double* out,
-                       hipStream_t s) {
-  hipLaunchKernelGGL(k_pack, dim3(1024), dim3(256), 0, s, m, padded, out);
+                       hipStream_t s, int nvec, int64_t stride) {
+  hipLaunchKernelGGL(k_pack, dim3(1024, nvec), dim3(256), 0, s, m, padded, out, stride);
   return hipGetLastError();
 }
 
 hipError_t launch_unpack(const ModelDev& m, const double* in, double* padded,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(k_unpack, dim3(1024), dim3(256), 0, s, m, in, padded);
+                         hipStream_t s, int nvec, int64_t stride) {
+  hipLaunchKernelGGL(k_unpack, dim3(1024, nvec), dim3(256), 0, s, m, in, padded, stride);
   return hipGetLastError();
 }
 

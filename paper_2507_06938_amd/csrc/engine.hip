@@ -461,6 +461,8 @@ struct Inst {
   double *lbuf[2] = {nullptr, nullptr}, *lbufB[2] = {nullptr, nullptr};
   int32_t *dctr[2] = {nullptr, nullptr}, *dctrB[2] = {nullptr, nullptr};
   double *uB = nullptr, *gpartB = nullptr, *xPB = nullptr;
+  int32_t *gcnt = nullptr, *gcntB = nullptr;  // GEMV row-block counters (zero between launches)
+  double *xm = nullptr, *mum = nullptr;       // SOLVE_RHS right-hand sides and solutions
   double *YB = nullptr, *XCB[2] = {nullptr, nullptr};
   double *theta = nullptr, *coef = nullptr, *logdiag[2] = {nullptr, nullptr};
   double *logdet2 = nullptr, *quad2 = nullptr, *sumpart = nullptr, *qpart = nullptr;
@@ -526,6 +528,7 @@ struct dl_ws {
   // (solve with the factor, x += correction unless converged), fin (mu <- x
   // and the final residual), resid (the final residual of mu alone)
   Plan theta_p, asm_p[3], fac_p[3], solve_p, selinv_p, post_p, eval_p;
+  Plan solve_m_p;  // SOLVE_RHS right-hand sides at once (I.xm -> I.mum)
   Plan qpsum_p;  // log|Q_p| after fac_p of an evaluation that keeps Q_p
   Plan ref_init_p, ref_res_p, ref_corr_p, ref_fin_p, resid_p;
   bool assembled[2] = {false, false}, factored[2] = {false, false};
@@ -629,8 +632,8 @@ static hipError_t run_launch(dl_ws* W, const Launch& L, hipStream_t s) {
                             std::min(L.gx, W->dag_workers), s);
         break;
       case OP_MISC: e = launch_misc(d.misc + L.off, L.count, s); break;
-      case OP_GEMV_N: e = launch_gemv_n(d.gn + L.off, L.count, L.gx, s); break;
-      case OP_GEMV_T: e = launch_gemv_t(d.gt + L.off, L.count, L.gx, s); break;
+      case OP_GEMV_N: e = launch_gemv_n(d.gn + L.off, L.count, L.gx, L.gy, s); break;
+      case OP_GEMV_T: e = launch_gemv_t(d.gt + L.off, L.count, L.gx, L.gy, s); break;
       case OP_SUM: e = launch_sums(d.sum + L.off, L.count, s); break;
       case OP_FINISH: e = launch_selinv_finish(d.fin + L.off, L.count, L.gx, s); break;
       case OP_ASM_COLS:
@@ -991,7 +994,7 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
   if (w == 1) I.slot_final.assign(slot.begin(), slot.begin() + m.nt);
 }
 
-static Step gn_step(uint64_t key, GemvN g, double bytes) {
+static Step gn_step(uint64_t key, GemvN g, double bytes, int nrhs) {
   Step s;
   s.key = key;
   s.kind = OP_GEMV_N;
@@ -1000,10 +1003,11 @@ static Step gn_step(uint64_t key, GemvN g, double bytes) {
   s.bytes = bytes;
   s.flops = bytes / 4.0;
   s.gx = g.M;
+  s.gy = nrhs;
   return s;
 }
 
-static Step gt_step(uint64_t key, GemvT g, double bytes) {
+static Step gt_step(uint64_t key, GemvT g, double bytes, int nrhs) {
   Step s;
   s.key = key;
   s.kind = OP_GEMV_T;
@@ -1012,6 +1016,7 @@ static Step gt_step(uint64_t key, GemvT g, double bytes) {
   s.bytes = bytes;
   s.flops = bytes / 4.0;
   s.gx = g.N;
+  s.gy = nrhs;
   return s;
 }
 
@@ -1023,7 +1028,9 @@ static Step gt_step(uint64_t key, GemvT g, double bytes) {
 // tip part (chain B into a tip accumulator of its own, added before the
 // tip solve).  Backward runs from the tip and the root outward:
 // mu_t = G_t^T (z_t - C_t^T mu_succ(t) - R_t^T mu_P).
-static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
+// nrhs = 1: I.x -> I.mu; SOLVE_RHS: the vectors of I.xm -> I.mum, every block
+// of the factor read once for all of them.
+static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q, int nrhs = 1) {
   const ModelDev& m = I.m;
   const int bp = m.bp, ap = m.ap;
   const int64_t ldbr = I.ldbr;
@@ -1035,9 +1042,11 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
   };
   auto G = [&](int t) { return I.Dc + (int64_t)t * bp * bp; };
   const int a32 = I.mixed ? 1 : 0;
-  double* x = I.x;
+  // strides between right-hand sides: x and mu, u, chain B's tip accumulator
+  const int64_t sv = m.Np, su = ldbr, st = ap;
+  double* x = nrhs > 1 ? I.xm : I.x;
   double* xP = x + (int64_t)m.nt * bp;
-  double* mu = I.mu;
+  double* mu = nrhs > 1 ? I.mum : I.mu;
   double* muP = mu + (int64_t)m.nt * bp;
   auto xt = [&](int t) { return x + (int64_t)t * bp; };
   const int n = m.nt, mid = I.mid;
@@ -1045,12 +1054,41 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
   const int steps = std::max(lenA, lenB);
   const uint64_t root_major = (uint64_t)steps + 1;
   // per chain (0: A and the root, 1: B): temporary, GEMV partial sums and
-  // tip accumulator
+  // their counters, and tip accumulator
   double* u[2] = {I.u, I.two ? I.uB : I.u};
   double* part[2] = {I.gpart, I.two ? I.gpartB : I.gpart};
+  int32_t* cnt[2] = {I.gcnt, I.two ? I.gcntB : I.gcnt};
   double* tipacc[2] = {xP, I.two ? I.xPB : xP};
+  const int64_t stip[2] = {sv, I.two ? st : sv};
+  auto gn = [&](uint64_t key, int ci, int M, int K_, const double* A, int64_t lda,
+                const double* xv, int64_t sx, int tri, double alpha, double beta, int split,
+                const double* base1, int64_t sb1, double* out1, int64_t so1, double* tip,
+                int64_t s2, int f32, double bytes) {
+    GemvN g{};
+    g.M = M; g.K = K_; g.A = A; g.lda = lda; g.x = xv; g.sx = sx; g.tri = tri;
+    g.alpha = alpha; g.beta = beta; g.split = split;
+    g.base1 = base1; g.sb1 = sb1; g.out1 = out1; g.so1 = so1;
+    g.base2 = tip; g.out2 = tip; g.s2 = s2;
+    g.partial = part[ci]; g.cnt = cnt[ci]; g.a32 = f32;
+    q.push_back(gn_step(key, g, bytes, nrhs));
+  };
+  auto gt = [&](uint64_t key, int M, int N, const double* A, int64_t lda, const double* x1,
+                int64_t sx1, int split, const double* x2, int tri, double alpha, double beta,
+                const double* base, double* y, int64_t sy, int f32, double bytes) {
+    GemvT g{};
+    g.M = M; g.N = N; g.A = A; g.lda = lda; g.x1 = x1; g.sx1 = sx1; g.split = split;
+    g.x2 = x2; g.sx2 = sv; g.tri = tri; g.alpha = alpha; g.beta = beta;
+    g.base = base; g.sb = sv; g.y = y; g.sy = sy; g.a32 = f32;
+    q.push_back(gt_step(key, g, bytes, nrhs));
+  };
+  auto vec_step = [&](uint64_t key, int kind, double* dst, int64_t sd, const double* src,
+                      int64_t ss, int64_t len) {
+    for (int r = 0; r < nrhs; ++r)
+      q.push_back(misc_step(key, DL_CAT_SOLVE, kind, dst + r * sd, src + r * ss, len));
+  };
   if (I.two && ap > 0)
-    q.push_back(misc_step(K(0, 0), DL_CAT_SOLVE, MJ_FILL, I.xPB, nullptr, ap, 0.0));
+    q.push_back(misc_step(K(0, 0), DL_CAT_SOLVE, MJ_FILL, I.xPB, nullptr, (int64_t)nrhs * ap,
+                          0.0));
   auto fwd = [&](int t, uint64_t major, int chain) {
     const int ci = chain == 1 ? 1 : 0;
     int preds[2][2];
@@ -1062,17 +1100,18 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
       if (lenB > 0) { preds[np][0] = mid + 1; preds[np][1] = 1; ++np; }
     }
     const double* base = xt(t);
+    int64_t sb = sv;
     for (int k = 0; k < np; ++k) {
       const int pb = preds[k][0], pc = preds[k][1];
-      q.push_back(gn_step(K(major, 0, 0, k), {bp + ap, bp, BRs(pb), ldbr, xt(pb), 0, -1.0,
-                                              1.0, bp, base, u[ci], tipacc[pc], tipacc[pc],
-                                              part[ci], a32},
-                          8.0 * (b + a) * b));
+      gn(K(major, 0, 0, k), ci, bp + ap, bp, BRs(pb), ldbr, xt(pb), sv, 0, -1.0, 1.0, bp, base,
+         sb, u[ci], su, tipacc[pc], stip[pc], a32, 8.0 * (b + a) * b);
       base = u[ci];
+      sb = su;
     }
-    q.push_back(gn_step(K(major, 1), {bp, bp, G(t), bp, np > 0 ? u[ci] : xt(t), 1, 1.0,
-                                      0.0, -1, nullptr, xt(t), nullptr, nullptr, part[ci]},
-                        4.0 * b * b));
+    // a product's input and output must not overlap
+    if (np == 0) vec_step(K(major, 0), MJ_COPY, u[ci], su, xt(t), sv, bp);
+    gn(K(major, 1), ci, bp, bp, G(t), bp, u[ci], su, 1, 1.0, 0.0, -1, nullptr, 0, xt(t), sv,
+       nullptr, 0, 0, 4.0 * b * b);
   };
   for (int k = 0; k < steps; ++k) {
     if (k < lenA) fwd(k, (uint64_t)k + 1, 0);
@@ -1081,37 +1120,29 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
   fwd(mid, root_major, 2);
   const uint64_t tk = (uint64_t)nt_max + 1;
   if (ap > 0) {
-    q.push_back(gn_step(K(tk, 0), {ap, bp, BRo(mid, bp), ldbr, xt(mid), 0, -1.0, 1.0, -1,
-                                   xP, xP, nullptr, nullptr, part[0], a32},
-                        8.0 * a * b));
-    if (I.two)
-      q.push_back(misc_step(K(tk, 0, 0, 1), DL_CAT_SOLVE, MJ_AXPY, xP, I.xPB, ap));
-    q.push_back(gn_step(K(tk, 1), {ap, ap, I.GPc, ap, xP, 1, 1.0, 0.0, -1, nullptr,
-                                   xP, nullptr, nullptr, part[0]},
-                        4.0 * a * a));
-    q.push_back(gt_step(K(tk, 2), {ap, ap, I.GPc, ap, xP, -1, nullptr, 1, 1.0, 0.0,
-                                   nullptr, muP},
-                        4.0 * a * a));
+    gn(K(tk, 0), 0, ap, bp, BRo(mid, bp), ldbr, xt(mid), sv, 0, -1.0, 1.0, -1, xP, sv, xP, sv,
+       nullptr, 0, a32, 8.0 * a * b);
+    if (I.two) vec_step(K(tk, 0, 0, 1), MJ_AXPY, xP, sv, I.xPB, st, ap);
+    gn(K(tk, 1), 0, ap, ap, I.GPc, ap, xP, sv, 1, 1.0, 0.0, -1, nullptr, 0, u[0], su, nullptr, 0,
+       0, 4.0 * a * a);
+    gt(K(tk, 2), ap, ap, I.GPc, ap, u[0], su, -1, nullptr, 1, 1.0, 0.0, nullptr, muP, sv, 0,
+       4.0 * a * a);
   }
   auto bwd = [&](int t, uint64_t major, int chain) {
     const int ci = chain == 1 ? 1 : 0;
     if (chain == 2) {
       if (ap > 0)
-        q.push_back(gt_step(K(major, 0), {ap, bp, BRo(t, bp), ldbr, muP, -1, nullptr, 0,
-                                          -1.0, 1.0, xt(t), u[0], a32},
-                            8.0 * a * b));
+        gt(K(major, 0), ap, bp, BRo(t, bp), ldbr, muP, sv, -1, nullptr, 0, -1.0, 1.0, xt(t),
+           u[0], su, a32, 8.0 * a * b);
       else
-        q.push_back(misc_step(K(major, 0), DL_CAT_SOLVE, MJ_COPY, u[0], xt(t), bp));
+        vec_step(K(major, 0), MJ_COPY, u[0], su, xt(t), sv, bp);
     } else {
       const int succ = chain == 0 ? t + 1 : t - 1;
-      q.push_back(gt_step(K(major, 0), {bp + ap, bp, BRs(t), ldbr,
-                                        mu + (int64_t)succ * bp, bp, muP, 0, -1.0, 1.0,
-                                        xt(t), u[ci], a32},
-                          8.0 * (b + a) * b));
+      gt(K(major, 0), bp + ap, bp, BRs(t), ldbr, mu + (int64_t)succ * bp, sv, bp, muP, 0, -1.0,
+         1.0, xt(t), u[ci], su, a32, 8.0 * (b + a) * b);
     }
-    q.push_back(gt_step(K(major, 1), {bp, bp, G(t), bp, u[ci], -1, nullptr, 1, 1.0, 0.0,
-                                      nullptr, mu + (int64_t)t * bp},
-                        4.0 * b * b));
+    gt(K(major, 1), bp, bp, G(t), bp, u[ci], su, -1, nullptr, 1, 1.0, 0.0, nullptr,
+       mu + (int64_t)t * bp, sv, 0, 4.0 * b * b);
   };
   bwd(mid, tk + 1, 2);
   for (int k = 0; k < steps; ++k) {
@@ -1350,6 +1381,14 @@ static dl_status build_plans(dl_ws* W) {
     merge(seqs, H, W->table, W->solve_p);
   }
   {
+    std::vector<std::vector<Step>> seqs;
+    for (auto& I : W->inst) {
+      seqs.emplace_back();
+      seq_solve(W, I, nt_max, seqs.back(), SOLVE_RHS);
+    }
+    merge(seqs, H, W->table, W->solve_m_p);
+  }
+  {
     std::vector<std::vector<Step>> init, res, corr, fin, resid;
     for (auto& I : W->inst) {
       init.push_back({misc_step(K(0, 0), DL_CAT_SOLVE, MJ_COPY, I.mu_acc, I.mu, I.m.Np)});
@@ -1505,6 +1544,9 @@ static void inst_layout(const dl_ws* W, Inst& I, const dl_model* model, bool two
   I.poisson = W->poisson;
 }
 
+// One counter per 128 rows of the largest matrix-vector product.
+static size_t gemv_counters(const Inst& I) { return (size_t)I.ldbr / 128 + 1; }
+
 // The device buffers of instance I (laid out by inst_layout): A(bytes, &ptr)
 // allocates them, or only counts them when the workspace is being sized.
 template <typename Alloc>
@@ -1553,8 +1595,11 @@ static void inst_buffers(const dl_ws* W, Inst& I, Alloc&& A) {
   A(sizeof(double) * m.Np, (void**)&I.rhs);
   A(sizeof(double) * m.Np, (void**)&I.x);
   A(sizeof(double) * m.Np, (void**)&I.mu);
-  A(sizeof(double) * I.ldbr, (void**)&I.u);
-  A(sizeof(double) * GEMV_KS * I.ldbr, (void**)&I.gpart);
+  A(sizeof(double) * SOLVE_RHS * m.Np, (void**)&I.xm);
+  A(sizeof(double) * SOLVE_RHS * m.Np, (void**)&I.mum);
+  A(sizeof(double) * SOLVE_RHS * I.ldbr, (void**)&I.u);
+  A(sizeof(double) * GEMV_KS * SOLVE_RHS * I.ldbr, (void**)&I.gpart);
+  A(sizeof(int32_t) * gemv_counters(I), (void**)&I.gcnt);
   if (I.poisson) {
     A(sizeof(double) * (m.m_total + 1), (void**)&I.obs_d);
     A(sizeof(double) * (m.m_total + 1), (void**)&I.obs_z);
@@ -1576,9 +1621,10 @@ static void inst_buffers(const dl_ws* W, Inst& I, Alloc&& A) {
   if (I.two) {
     A(tip, (void**)&I.PcB);
     for (int w = I.qp_kron ? 1 : 0; w < 2; ++w) A(ftemp, (void**)&I.ttempB[w]);
-    A(sizeof(double) * I.ldbr, (void**)&I.uB);
-    A(sizeof(double) * GEMV_KS * I.ldbr, (void**)&I.gpartB);
-    A(sizeof(double) * (ap > 0 ? ap : 1), (void**)&I.xPB);
+    A(sizeof(double) * SOLVE_RHS * I.ldbr, (void**)&I.uB);
+    A(sizeof(double) * GEMV_KS * SOLVE_RHS * I.ldbr, (void**)&I.gpartB);
+    A(sizeof(int32_t) * gemv_counters(I), (void**)&I.gcntB);
+    A(sizeof(double) * SOLVE_RHS * (ap > 0 ? ap : 1), (void**)&I.xPB);
   }
   if (W->sel) {
     // [W_t; V_t] = [B_t; R_t] G_t of every time step (formed up front)
@@ -1687,6 +1733,12 @@ extern "C" dl_status dl_ws_create_batch(const dl_model* const* models,
         (hipMemset(I.obs_d, 0, sizeof(double) * (I.m.m_total + 1)) != hipSuccess ||
          hipMemset(I.obs_z, 0, sizeof(double) * (I.m.m_total + 1)) != hipSuccess))
       st = DL_EHIP;
+    if (st == DL_OK && hipMemset(I.xm, 0, sizeof(double) * SOLVE_RHS * I.m.Np) != hipSuccess)
+      st = DL_EHIP;
+    for (int32_t* c : {I.gcnt, I.gcntB})
+      if (c && st == DL_OK &&
+          hipMemset(c, 0, sizeof(int32_t) * gemv_counters(I)) != hipSuccess)
+        st = DL_EHIP;
     if (W->dag && st == DL_OK) {
       const size_t nc = sizeof(int32_t) * (size_t)dag::counters_per_block(I.m.bp / 64);
       for (int w = 0; w < 2 && st == DL_OK; ++w)
@@ -1932,7 +1984,31 @@ extern "C" dl_status bta_solve(dl_ws* W, double* rhs_inout_dev, int32_t nrhs,
   } else {
     int64_t ntot = 0;
     for (auto& I : W->inst) ntot += I.m.N;
-    for (int c = 0; c < nrhs; ++c) {
+    int c = 0;
+    // without refinement up to SOLVE_RHS vectors share a pass over the factor
+    while (steps == 0 && nrhs - c > 1) {
+      const int k = std::min(nrhs - c, SOLVE_RHS);
+      double* col = rhs_inout_dev + (int64_t)c * ntot;
+      c += k;
+      int64_t off = 0;
+      for (auto& I : W->inst) {
+        DL_HIP_CHECK(launch_unpack(I.m, col + off, I.xm, s, k, ntot));
+        // the workspace keeps the last right-hand side and its solution
+        if (c == nrhs)
+          DL_HIP_CHECK(launch_unpack(I.m, col + off + (int64_t)(k - 1) * ntot, I.rhs, s));
+        off += I.m.N;
+      }
+      DL_HIP_CHECK(run(W, W->solve_m_p, s));
+      off = 0;
+      for (auto& I : W->inst) {
+        DL_HIP_CHECK(launch_pack(I.m, I.mum, col + off, s, k, ntot));
+        if (c == nrhs)
+          DL_HIP_CHECK(hipMemcpyAsync(I.mu, I.mum + (int64_t)(k - 1) * I.m.Np,
+                                      sizeof(double) * I.m.Np, hipMemcpyDeviceToDevice, s));
+        off += I.m.N;
+      }
+    }
+    for (; c < nrhs; ++c) {
       double* col = rhs_inout_dev + (int64_t)c * ntot;
       // the plan copies rhs -> x first, so stage the caller's vectors in rhs
       int64_t off = 0;

@@ -174,9 +174,10 @@ struct TrialJob {
 };
 hipError_t launch_trial(const TrialJob* jobs, int count, hipStream_t s);
 hipError_t launch_trial_gather(const TrialJob* jobs, int count, hipStream_t s);
+// nvec vectors: padded ones Np apart, packed ones `stride` apart
 hipError_t launch_pack(const ModelDev& m, const double* padded, double* out,
-                       hipStream_t s);
+                       hipStream_t s, int nvec = 1, int64_t stride = 0);
 hipError_t launch_unpack(const ModelDev& m, const double* in, double* padded,
-                         hipStream_t s);
+                         hipStream_t s, int nvec = 1, int64_t stride = 0);
 
 }  // namespace dl
