@@ -26,7 +26,9 @@ namespace dl {
 // work):
 //   F_LOWER   : only tiles/elements with row >= col of C are computed;
 //   F_KLO_COL : k >= first column of the C tile; F_KHI_COL : k < last col+1;
-//   F_KLO_ROW : k >= first row of the C tile;    F_KHI_ROW : k < last row+1.
+//   F_KLO_ROW : k >= first row of the C tile;    F_KHI_ROW : k < last row+1;
+//   F_BAND_ROW: op(A) is a banded coupling product (see Band): k >= its
+//               rows' first column;  F_BAND_COL: the same for op(B)'s columns.
 enum : int {
   F_TA = 1,
   F_TB = 2,
@@ -47,6 +49,26 @@ enum : int {
   // of such a task are ordered longest first and the launch's workgroups are
   // dealt to the XCDs in turn, so each XCD gets the same mix of lengths
   F_KVAR = 4096,
+  F_BAND_ROW = 8192,
+  F_BAND_COL = 16384,
+};
+
+// First nonzero column of the rows of [C_t; R_t], C_t = B_t G_t^T: row
+// r = k period + s of the sparse B_t starts `reach` nodes before node s in
+// each response's columns, hence in those of the first response, and G_t^T is
+// upper triangular.  Rows from `rows` up to `end` are zero (padding), rows from
+// `end` on dense (the arrow).  period 0: every row is dense.
+struct Band {
+  int32_t period, reach, rows, end;
+  // first column of the rows [r0, r0 + n) (`cols` when they are all zero)
+  __host__ __device__ int lo(int r0, int n, int cols) const {
+    if (period <= 0 || r0 + n > end) return 0;
+    const int r1 = r0 + n < rows ? r0 + n : rows;
+    if (r0 >= r1) return cols;
+    const int s = r0 % period;
+    if (s + (r1 - r0) > period) return 0;
+    return s > reach ? s - reach : 0;
+  }
 };
 
 // Split k.  For an F_SPLIT task with K > ksplit (the task's piece length,
@@ -79,6 +101,7 @@ struct GemmTask {
   int32_t ksplit;            // split-k piece length (0: GEMM_KSPLIT; resolved
                              // by finalize_tasks)
   int32_t pad_;
+  Band band;                 // of the F_BAND_ROW / F_BAND_COL operands
 };
 
 constexpr int GEMM_BM = 64;

@@ -22,6 +22,7 @@
 #include <new>
 #include <vector>
 
+#include "couple.hpp"
 #include "engine.hpp"
 #include "selinv.hpp"
 #include "solve.hpp"
@@ -32,7 +33,7 @@ namespace dl {
 enum OpKind : int {
   OP_GEMM, OP_POTRF, OP_MISC, OP_GEMV_N, OP_GEMV_T, OP_SUM, OP_FINISH,
   OP_ASM_COLS, OP_ASM_TIPS, OP_THETA, OP_QUAD, OP_COMBINE, OP_GEMM32, OP_RES,
-  OP_PANEL, OP_DAG, OP_NKIND
+  OP_PANEL, OP_DAG, OP_COUPLE, OP_NKIND
 };
 
 // One step of one sequence (before merging).
@@ -56,6 +57,7 @@ struct Step {
   QuadJob quad{};
   CombineJob comb{};
   ResJob res{};
+  CoupleJob couple{};
   int gx = 0, gy = 0, gz = 0;  // grid bounds contributed by this step
 };
 
@@ -106,6 +108,7 @@ struct Descs {
   std::vector<QuadJob> quad;
   std::vector<CombineJob> comb;
   std::vector<ResJob> res;
+  std::vector<CoupleJob> couple;
 };
 
 struct DevDescs {
@@ -124,6 +127,7 @@ struct DevDescs {
   QuadJob* quad = nullptr;
   CombineJob* comb = nullptr;
   ResJob* res = nullptr;
+  CoupleJob* couple = nullptr;
 };
 
 // key = (((major * 16 + group) * 256 + j) * 4 + sub)
@@ -209,6 +213,13 @@ static void merge(const std::vector<std::vector<Step>>& seqs, Descs& D,
       case OP_QUAD: PUSH(quad, quad)
       case OP_COMBINE: PUSH(comb, comb)
       case OP_RES: PUSH(res, res)
+      case OP_COUPLE: {
+        L.off = (int)D.couple.size();
+        for (const Step* st : g) D.couple.push_back(st->couple);
+        L.count = (int)D.couple.size() - L.off;
+        L.gx = finalize_couple(D.couple.data() + L.off, L.count);
+        break;
+      }
 #undef PUSH
       default: continue;
     }
@@ -485,7 +496,30 @@ struct Inst {
   double *tpart = nullptr, *alpha = nullptr, *out4 = nullptr;
 };
 
-struct dl_ws {
+// The launches of a workspace's plans and their descriptors.
+struct PlanSet {
+  Descs H;
+  DevDescs Dd;
+  std::vector<Launch> table;
+  // refinement plans: init (x <- mu), res (residual of x and its norms), corr
+  // (solve with the factor, x += correction unless converged), fin (mu <- x
+  // and the final residual), resid (the final residual of mu alone)
+  Plan theta_p, asm_p[3], fac_p[3], solve_p, selinv_p, post_p, eval_p;
+  Plan solve_m_p;  // SOLVE_RHS right-hand sides at once (I.xm -> I.mum)
+  Plan qpsum_p;  // log|Q_p| after fac_p of an evaluation that keeps Q_p
+  Plan ref_init_p, ref_res_p, ref_corr_p, ref_fin_p, resid_p;
+  int32_t* dag_heads = nullptr;  // [4 x launches] task head, finished workgroups, abort
+};
+
+struct dl_ws : PlanSet {
+  // Plans that take the sub-diagonal blocks as dense ones, for a caller's own
+  // (dl_ws_set_block, until the next assembly); built when first needed.
+  // `dense` says that they are the active ones and `other` the assembled
+  // blocks' plans.
+  bool dense = false;
+  bool caller_b[2] = {false, false};  // Q_p / Q_c holds a caller's sub-diagonal block
+  PlanSet other;
+  bool have_other = false;
   std::vector<Inst> inst;
   std::vector<void*> allocs;
   size_t bytes = 0;
@@ -494,7 +528,6 @@ struct dl_ws {
   bool splitk = false;
   bool fold_inv = false;  // inverses inside the panel launches (DL_WS_FOLD_INV)
   bool dag = false;       // one persistent launch per diagonal block (DL_WS_DAG)
-  int32_t* dag_heads = nullptr;  // [4 x launches] task head, finished workgroups, abort
   int dag_workers = 0;           // grid of the persistent launches
   double* partials = nullptr;  // split-k partial tiles (shared by all launches)
   int64_t partials_cap = 0;    // doubles allocated at `partials`
@@ -521,16 +554,6 @@ struct dl_ws {
   double tol2_host = 0.0;
   std::vector<double> rnorm_host;
   MiscJob* d_io = nullptr;  // one descriptor for dl_ws_get_block / set_block
-  Descs H;
-  DevDescs Dd;
-  std::vector<Launch> table;
-  // refinement plans: init (x <- mu), res (residual of x and its norms), corr
-  // (solve with the factor, x += correction unless converged), fin (mu <- x
-  // and the final residual), resid (the final residual of mu alone)
-  Plan theta_p, asm_p[3], fac_p[3], solve_p, selinv_p, post_p, eval_p;
-  Plan solve_m_p;  // SOLVE_RHS right-hand sides at once (I.xm -> I.mum)
-  Plan qpsum_p;  // log|Q_p| after fac_p of an evaluation that keeps Q_p
-  Plan ref_init_p, ref_res_p, ref_corr_p, ref_fin_p, resid_p;
   bool assembled[2] = {false, false}, factored[2] = {false, false};
   bool solved = false;
   int max_shmem = 0;
@@ -634,6 +657,7 @@ static hipError_t run_launch(dl_ws* W, const Launch& L, hipStream_t s) {
       case OP_MISC: e = launch_misc(d.misc + L.off, L.count, s); break;
       case OP_GEMV_N: e = launch_gemv_n(d.gn + L.off, L.count, L.gx, L.gy, s); break;
       case OP_GEMV_T: e = launch_gemv_t(d.gt + L.off, L.count, L.gx, L.gy, s); break;
+      case OP_COUPLE: e = launch_couple(d.couple + L.off, L.count, L.gx, W->mixed, s); break;
       case OP_SUM: e = launch_sums(d.sum + L.off, L.count, s); break;
       case OP_FINISH: e = launch_selinv_finish(d.fin + L.off, L.count, L.gx, s); break;
       case OP_ASM_COLS:
@@ -804,6 +828,28 @@ static void seq_logdet_qp(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
   q.push_back(qp_logdet_sum(I, K(tail, 1)));
 }
 
+// Where the rows of a block's coupling product [C_t; R_t] begin.
+static Band coupling_band(const Inst& I) {
+  const ModelDev& m = I.m;
+  return Band{m.ns, m.band, m.b, m.bp};
+}
+
+// Operations of the Schur update of one block: the symmetric product C C^T over
+// the columns both rows have, and the arrow rows' product with C^T.
+static double update_flops(const dl_ws* W, const Inst& I, double b, double ar) {
+  if (W->dense) return b * b * b + 2.0 * ar * b * b;
+  const ModelDev& m = I.m;
+  // m.nv rows start at each node's first column lo: those that start earlier
+  // meet them from lo on
+  double f = 0.0, before = 0.0;
+  for (int s = 0; s < m.ns; ++s) {
+    const double len = b - std::max(0, s - m.band), nv = m.nv;
+    f += len * (nv * (2.0 * before + nv) + 2.0 * ar * nv);
+    before += nv;
+  }
+  return f;
+}
+
 // BTA Cholesky of Q_p (w = 0) or Q_c (w = 1) of instance I in its
 // elimination order.  Every block t other than the root is eliminated into
 // its successor (t+1 in chain A, t-1 in chain B): factor D_t, scale its
@@ -892,6 +938,12 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
     return I.mixed ? gemm32_step(key, cat, fl, std::move(ts))
                    : gemm_step(key, cat, fl, std::move(ts));
   };
+  auto banded = [&](GemmTask t, int flags) {
+    if (W->dense) return t;
+    t.flags |= flags;
+    t.band = coupling_band(I);
+    return t;
+  };
   // chain 0: A, 1: B, 2: root
   auto eliminate = [&](int t, uint64_t major, int chain) {
     const bool root = chain == 2;
@@ -917,20 +969,42 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
     const int nw = ring ? (ci ? 5 : 2) : spare[ci];
     // [C_t; R_t] <- [C_t; R_t] L_tt^{-T} = [C_t; R_t] G_t^T, C_t the coupling
     const int fl = F_TB | F_KHI_COL | F_BETA0 | x64 | xf;
+    const double* Cin = nullptr;
+    if (chain == 1) Cin = ring ? BRs(t - 1 == mid ? 6 : 3 + (t - 1) % 2) : BRs(slot[t - 1]);
+    if (chain == 0) Cin = BRs(ring ? t % 2 : slot[t]);
+    const double* Rin = apr ? BRo(slot[t], bp) : nullptr;
     std::vector<GemmTask> tr;
-    if (chain == 1) {
-      const double* C = ring ? BRs(t - 1 == mid ? 6 : 3 + (t - 1) % 2) : BRs(slot[t - 1]);
-      tr.push_back(mk(C, ldbr, Dt(t), bp, BRs(nw), ldbr, bp, bp, bp, fl, 1.0, 0.0));
-      if (apr)
-        tr.push_back(mk(BRo(slot[t], bp), ldbr, Dt(t), bp, BRo(nw, bp), ldbr, apr, bp, bp,
-                        fl, 1.0, 0.0));
-    } else {
-      const int rows_lo = root ? bp : 0;
-      const int src = ring ? (t % 2) : slot[t];
-      tr.push_back(mk(BRo(src, rows_lo), ldbr, Dt(t), bp, BRo(nw, rows_lo), ldbr, M, bp,
-                      bp, fl, 1.0, 0.0));
+    if (W->dense && Cin && Rin && chain == 0)  // one operand
+      tr.push_back(mk(Cin, ldbr, Dt(t), bp, BRs(nw), ldbr, M, bp, bp, fl, 1.0, 0.0));
+    else if (W->dense && Cin)
+      tr.push_back(mk(Cin, ldbr, Dt(t), bp, BRs(nw), ldbr, bp, bp, bp, fl, 1.0, 0.0));
+    // a mixed coregional factor is as sensitive as FP32 is to how the dense
+    // rows are summed: those stay with the matrix product
+    const bool rgemm = W->dense || (I.mixed && m.nv > 1);
+    if (Rin && rgemm && !(W->dense && chain == 0))
+      tr.push_back(mk(Rin, ldbr, Dt(t), bp, BRo(nw, bp), ldbr, apr, bp, bp, fl, 1.0, 0.0));
+    if (!tr.empty())
+      q.push_back(gs(K(major, 3), DL_CAT_TRSM, (W->dense ? mreal : ar) * b * b, std::move(tr)));
+    if (!W->dense && (Cin || (Rin && !rgemm))) {
+      Step s;
+      s.key = K(major, 3);
+      s.kind = OP_COUPLE;
+      s.cat = DL_CAT_TRSM;
+      s.flops = (Cin ? (double)m.cp_w * m.nv * b * b : 0.0) + (rgemm ? 0.0 : ar * b * b);
+      s.bytes = 4.0 * b * b + eb * mreal * b;
+      CoupleJob& c = s.couple;
+      c.col = m.cp_col;
+      c.b = m.b; c.a = m.a; c.bp = bp; c.ap = m.ap;
+      c.ns = m.ns; c.nv = m.nv; c.w = m.cp_w;
+      c.B = Cin;
+      c.G = Dt(t);
+      c.C = BRs(nw);
+      c.R = rgemm ? nullptr : Rin;
+      c.RC = BRo(nw, bp);
+      c.ldb = ldbr;
+      c.band = coupling_band(I);
+      q.push_back(s);
     }
-    q.push_back(gs(K(major, 3), DL_CAT_TRSM, mreal * b * b, std::move(tr)));
     if (!ring) {
       // the block's old slot is free: its coupling rows were read by this
       // step (chain A, root) or by the previous step of chain B, its arrow
@@ -944,16 +1018,19 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
     double* Ptip = (chain == 1) ? I.PcB : P;
     std::vector<GemmTask> up;
     if (!root) {
-      up.push_back(mk(BRt, ldbr, BRt, ldbr, Dt(succ), bp, bp, bp, bp,
-                      F_TB | F_LOWER | c64 | xf, -1.0, 1.0));
+      // the long sums of the arrow rows first
       if (apr)
-        up.push_back(mk(RRt, ldbr, BRt, ldbr, BRo(slot[succ], bp), ldbr, apr, bp, bp,
-                        F_TB | xf, -1.0, 1.0));
+        up.push_back(banded(mk(RRt, ldbr, BRt, ldbr, BRo(slot[succ], bp), ldbr, apr, bp, bp,
+                               F_TB | xf, -1.0, 1.0),
+                            F_BAND_COL));
+      up.push_back(banded(mk(BRt, ldbr, BRt, ldbr, Dt(succ), bp, bp, bp, bp,
+                             F_TB | F_LOWER | c64 | xf, -1.0, 1.0),
+                          F_BAND_ROW | F_BAND_COL));
     }
     if (apr)
       up.push_back(mk(RRt, ldbr, RRt, ldbr, Ptip, m.ap, apr, apr, bp,
                       F_TB | F_LOWER | c64 | xf, -1.0, 1.0));
-    const double upd = (root ? 0.0 : b * b * b + 2.0 * ar * b * b) + ar * ar * b;
+    const double upd = (root ? 0.0 : update_flops(W, I, b, ar)) + ar * ar * b;
     q.push_back(gs(K(major, 4), DL_CAT_UPDATE, upd, std::move(up)));
   };
   for (int k = 0; k < std::max(lenA, lenB); ++k) {
@@ -1070,6 +1147,7 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q, int n
     g.base1 = base1; g.sb1 = sb1; g.out1 = out1; g.so1 = so1;
     g.base2 = tip; g.out2 = tip; g.s2 = s2;
     g.partial = part[ci]; g.cnt = cnt[ci]; g.a32 = f32;
+    if (split >= 0 && !W->dense) g.band = coupling_band(I);
     q.push_back(gn_step(key, g, bytes, nrhs));
   };
   auto gt = [&](uint64_t key, int M, int N, const double* A, int64_t lda, const double* x1,
@@ -1079,6 +1157,7 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q, int n
     g.M = M; g.N = N; g.A = A; g.lda = lda; g.x1 = x1; g.sx1 = sx1; g.split = split;
     g.x2 = x2; g.sx2 = sv; g.tri = tri; g.alpha = alpha; g.beta = beta;
     g.base = base; g.sb = sv; g.y = y; g.sy = sy; g.a32 = f32;
+    if (split >= 0 && !W->dense) g.band = coupling_band(I);
     q.push_back(gt_step(key, g, bytes, nrhs));
   };
   auto vec_step = [&](uint64_t key, int kind, double* dst, int64_t sd, const double* src,
@@ -1220,8 +1299,13 @@ static void seq_selinv(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
           fl += a * b * b;
         }
       } else {
-        wv.push_back(mk(BRs(t), ld, G(t), bp, WVt(t), ld, bp + ap, bp, bp,
-                        F_KLO_COL | F_BETA0 | fB64 | xf, 1.0, 0.0));
+        GemmTask g = mk(BRs(t), ld, G(t), bp, WVt(t), ld, bp + ap, bp, bp,
+                        F_KLO_COL | F_BETA0 | fB64 | xf, 1.0, 0.0);
+        if (!W->dense) {
+          g.flags |= F_BAND_ROW;
+          g.band = coupling_band(I);
+        }
+        wv.push_back(g);
         fl += (b + a) * b * b;
       }
     }
@@ -1337,6 +1421,31 @@ static void seq_post(dl_ws* W, Inst& I, int k, std::vector<Step>& q) {
 
 static void append(Plan& dst, const Plan& src) {
   dst.idx.insert(dst.idx.end(), src.idx.begin(), src.idx.end());
+}
+
+// Make the plans for dense (caller's) or assembled sub-diagonal blocks of Q_c
+// or Q_p the active ones.
+static dl_status build_plans(dl_ws* W);
+static dl_status use_plans(dl_ws* W, bool dense) {
+  if (W->dense == dense) return DL_OK;
+  std::swap(static_cast<PlanSet&>(*W), W->other);
+  W->dense = dense;
+  if (W->have_other) return DL_OK;
+  const dl_status st = build_plans(W);
+  if (st != DL_OK) {
+    std::swap(static_cast<PlanSet&>(*W), W->other);
+    W->dense = !dense;
+    W->other = PlanSet{};
+    return st;
+  }
+  W->have_other = true;
+  return DL_OK;
+}
+
+// The matrices w0..w1 (0: Q_p, 1: Q_c) are about to be assembled.
+static dl_status assembled_plans(dl_ws* W, int w0, int w1) {
+  for (int w = w0; w <= w1; ++w) W->caller_b[w] = false;
+  return use_plans(W, W->caller_b[0] || W->caller_b[1]);
 }
 
 static dl_status build_plans(dl_ws* W) {
@@ -1491,6 +1600,7 @@ static dl_status build_plans(dl_ws* W) {
   up(H.quad, W->Dd.quad);
   up(H.comb, W->Dd.comb);
   up(H.res, W->Dd.res);
+  up(H.couple, W->Dd.couple);
   if (W->poisson) {
     std::vector<LapJob> lap;
     std::vector<TrialJob> trial;
@@ -1930,6 +2040,8 @@ extern "C" dl_status bta_assemble(dl_ws* W, const double* theta_dev,
   hipStream_t s = (hipStream_t)stream;
   dl_status st = copy_theta_in(W, theta_dev, (int)W->inst.size(), s);
   if (st != DL_OK) return st;
+  if ((st = assembled_plans(W, which == DL_QC ? 1 : 0, which == DL_QP ? 0 : 1)) != DL_OK)
+    return st;
   DL_HIP_CHECK(run(W, W->asm_p[which], s));
   if (which != DL_QC) { W->assembled[0] = true; W->factored[0] = false; }
   if (which != DL_QP) { W->assembled[1] = true; W->factored[1] = false; }
@@ -2091,6 +2203,7 @@ static dl_status laplace_pass(dl_ws* W, int nk, hipStream_t s) {
       DL_HIP_CHECK(hipMemsetAsync(I.xcur, 0, sizeof(double) * I.m.Np, s));
     DL_HIP_CHECK(hipMemsetAsync(I.xN, 0, sizeof(double) * I.m.Np, s));
   }
+  if (const dl_status st = assembled_plans(W, 0, 1); st != DL_OK) return st;
   // Q_p and the first step's Q_c(x0) share their launches
   DL_HIP_CHECK(launch_lap_weights(W->d_lap, B, s));
   DL_HIP_CHECK(run(W, W->asm_p[2], s));
@@ -2188,8 +2301,8 @@ extern "C" dl_status dl_ws_newton_steps(const dl_ws* W, int32_t* steps_host) {
 }
 
 static dl_status run_eval(dl_ws* W, hipStream_t s) {
-  dl_status st = set_refine_tol(W, DL_REFINE_TOL, s);
-  if (st != DL_OK) return st;
+  dl_status st = assembled_plans(W, 0, 1);
+  if (st != DL_OK || (st = set_refine_tol(W, DL_REFINE_TOL, s)) != DL_OK) return st;
   if (!W->use_graph) {
     DL_HIP_CHECK(run(W, W->asm_p[2], s));
     DL_HIP_CHECK(run(W, W->fac_p[2], s));
@@ -2284,7 +2397,9 @@ extern "C" dl_status fobj_selinv_eval(dl_ws* W, const double* theta_dev, int32_t
     if ((st = laplace_pass(W, ntheta, s)) != DL_OK) return st;
     DL_HIP_CHECK(hipEventRecord(W->ev_join, s));
   } else {
-    if ((st = set_refine_tol(W, DL_REFINE_TOL, s)) != DL_OK) return st;
+    if ((st = assembled_plans(W, 0, 1)) != DL_OK ||
+        (st = set_refine_tol(W, DL_REFINE_TOL, s)) != DL_OK)
+      return st;
     DL_HIP_CHECK(run(W, W->asm_p[2], s));
     DL_HIP_CHECK(run(W, W->fac_p[2], s));
     DL_HIP_CHECK(run(W, W->qpsum_p, s));
@@ -2411,8 +2526,13 @@ extern "C" dl_status dl_ws_set_block(dl_ws* W, dl_which which, int32_t kind, int
     return DL_OK;
   }
   MiscJob J;
-  const dl_status st = block_job(W, which, kind, t, true, const_cast<double*>(in_dev), &J);
+  dl_status st = block_job(W, which, kind, t, true, const_cast<double*>(in_dev), &J);
   if (st != DL_OK) return st;
+  // a caller's coupling may be dense
+  if (kind == 1) {
+    if ((st = use_plans(W, true)) != DL_OK) return st;
+    W->caller_b[w] = true;
+  }
   return block_copy(W, J, s);
 }
 

@@ -186,6 +186,21 @@ struct VStage {
 // rows and columns are reused from that XCD's L2.
 constexpr int GROUP = 8;
 
+// k range [kb, ke) of the BT x BT tile at (m0, n0), kb on a chunk.
+template <int BT>
+__device__ __forceinline__ void tile_k_range(const GemmTask& T, int m0, int n0, int& kb,
+                                             int& ke) {
+  kb = 0;
+  ke = T.K;
+  if (T.flags & F_KLO_COL) kb = max(kb, n0);
+  if (T.flags & F_KHI_COL) ke = min(ke, n0 + BT);
+  if (T.flags & F_KLO_ROW) kb = max(kb, m0);
+  if (T.flags & F_KHI_ROW) ke = min(ke, m0 + BT);
+  if (T.flags & F_BAND_ROW) kb = max(kb, T.band.lo(m0, min(BT, T.M - m0), T.K));
+  if (T.flags & F_BAND_COL) kb = max(kb, T.band.lo(n0, min(BT, T.N - n0), T.K));
+  kb = (kb / BK) * BK;
+}
+
 __device__ __forceinline__ void tile_coords(const GemmTask& T, int lt, int& tm,
                                             int& tn) {
   constexpr int KCOL = F_KLO_COL | F_KHI_COL, KROW = F_KLO_ROW | F_KHI_ROW;
@@ -334,12 +349,8 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
   const bool ta = T.flags & F_TA;
   const bool tb = T.flags & F_TB;
 
-  int kb = 0, ke = T.K;
-  if (T.flags & F_KLO_COL) kb = max(kb, n0);
-  if (T.flags & F_KHI_COL) ke = min(ke, n0 + BT);
-  if (T.flags & F_KLO_ROW) kb = max(kb, m0);
-  if (T.flags & F_KHI_ROW) ke = min(ke, m0 + BT);
-  kb = (kb / BK) * BK;
+  int kb, ke;
+  tile_k_range<BT>(T, m0, n0, kb, ke);
   int slot = -1;  // partial tile of this piece (split tiles only)
   if (T.kslices > 1 && ke > kb) {
     const int ks = T.ksplit;
@@ -474,12 +485,8 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(const GemmTask* __restrict_
   int tm, tn;
   tile_coords(T, lt, tm, tn);
   const int m0 = tm * BT, n0 = tn * BT;
-  int kb = 0, ke = T.K;
-  if (T.flags & F_KLO_COL) kb = max(kb, n0);
-  if (T.flags & F_KHI_COL) ke = min(ke, n0 + BT);
-  if (T.flags & F_KLO_ROW) kb = max(kb, m0);
-  if (T.flags & F_KHI_ROW) ke = min(ke, m0 + BT);
-  kb = (kb / BK) * BK;
+  int kb, ke;
+  tile_k_range<BT>(T, m0, n0, kb, ke);
   if (ke <= kb) return;
   const int npieces = (ke - 1) / T.ksplit - kb / T.ksplit + 1;
   if (npieces < 2) return;  // written directly by the product launch
@@ -503,7 +510,8 @@ int finalize_tasks(GemmTask* t, int n, int tile, int* nred, int64_t* nslots) {
   int64_t slots = 0;
   bool kvar = false;
   for (int i = 0; i < n; ++i)
-    kvar = kvar || (t[i].flags & (F_KLO_COL | F_KHI_COL | F_KLO_ROW | F_KHI_ROW));
+    kvar = kvar || (t[i].flags & (F_KLO_COL | F_KHI_COL | F_KLO_ROW | F_KHI_ROW |
+                                F_BAND_ROW | F_BAND_COL));
   for (int i = 0; i < n; ++i) {
     t[i].flags = kvar ? (t[i].flags | F_KVAR) : (t[i].flags & ~F_KVAR);
     t[i].tiles_m = (t[i].M + tile - 1) / tile;
@@ -783,12 +791,8 @@ __global__ __launch_bounds__(256) void k_gemm32_tasks(
   const bool a64 = T.flags & F_A64;
   const bool b64 = T.flags & F_B64;
 
-  int kb = 0, ke = T.K;
-  if (T.flags & F_KLO_COL) kb = max(kb, n0);
-  if (T.flags & F_KHI_COL) ke = min(ke, n0 + BT);
-  if (T.flags & F_KLO_ROW) kb = max(kb, m0);
-  if (T.flags & F_KHI_ROW) ke = min(ke, m0 + BT);
-  kb = (kb / BK) * BK;
+  int kb, ke;
+  tile_k_range<BT>(T, m0, n0, kb, ke);
   const int nchunks = ke > kb ? (ke - kb + BK - 1) / BK : 0;
 
   const int lane = tid & 63;

@@ -138,6 +138,15 @@ extern "C" dl_status dl_model_create(const dl_model_desc* desc,
         }
       ptr[s + 1] = (int)col.size();
     }
+  // the sub-diagonal blocks hold C, G and (separable) G C^-1 G only
+  const int creach = family == DL_MODEL_DIFFUSION ? 1 : 2;
+  d.cp_w = creach == 1 ? 5 : CPW_MAX;
+  d.band = creach * nx;
+  std::vector<int> ccol((size_t)ns * d.cp_w, -1);
+  for (int s = 0; s < ns; ++s)
+    for (int e = ptr[s], q = 0; e < ptr[s + 1]; ++e)
+      if (abs(col[e] / nx - s / nx) + abs(col[e] % nx - s % nx) <= creach)
+        ccol[(size_t)s * d.cp_w + q++] = col[e];
 
   // observations, concatenated; node -> rows index per (response, time, node)
   int64_t mt = 0;
@@ -187,6 +196,7 @@ extern "C" dl_status dl_model_create(const dl_model_desc* desc,
   dl_status st = DL_OK;
   if ((st = upload(M->allocs, ptr, &d.sp_ptr)) != DL_OK ||
       (st = upload(M->allocs, col, &d.sp_col)) != DL_OK ||
+      (st = upload(M->allocs, ccol, &d.cp_col)) != DL_OK ||
       (st = upload(M->allocs, vC, &d.sp_C)) != DL_OK ||
       (st = upload(M->allocs, vG, &d.sp_G)) != DL_OK ||
       (st = upload(M->allocs, vG2, &d.sp_G2)) != DL_OK ||

@@ -28,6 +28,9 @@ enum : int {
   C_SIZE = 8 + 36 * NPIECE + 4
 };
 
+// Most points of the coupling stencil.
+constexpr int CPW_MAX = 13;
+
 struct ModelDev {
   int nx, nt, nv, nr, ns, b, a, bp, ap, dim_theta;
   int family;             // DL_MODEL_SEPARABLE or DL_MODEL_DIFFUSION
@@ -42,6 +45,11 @@ struct ModelDev {
   const double* sp_G;
   const double* sp_G2;
   const double* sp_G3;
+  // stencil of the sub-diagonal blocks (13 points, or 5 for the diffusion
+  // model): cp_w columns per node in increasing order, padded with -1; none is
+  // more than `band` nodes before its row
+  int cp_w, band;
+  const int* cp_col;
   // observations of all responses, concatenated
   int64_t m_total;
   int64_t m_off[4];

@@ -53,8 +53,11 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
   if (rb * RB >= g.M) return;
   const int len = max(64, (g.K + GEMV_KS - 1) / GEMV_KS);
   const int kend = g.tri ? min(g.K, rb * RB + RB) : g.K;
-  const int nsl = (kend + len - 1) / len;
-  if (sl >= nsl) return;
+  // A's zeros before its rows' first column are skipped by whole slices and
+  // by whole 128 columns of a slice
+  const int klo = min(g.band.lo(rb * RB, min(RB, g.M - rb * RB), g.K), kend - 1);
+  const int sl0 = klo / len, nsl = (kend + len - 1) / len - sl0;
+  if (sl < sl0 || sl >= sl0 + nsl) return;
   const int k0 = sl * len, k1 = min(kend, k0 + len);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = rb * RB + lane * V;
@@ -70,7 +73,8 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
     for (int v = 0; v < V; ++v) acc[r][v] = 0.0;
   // the slice's x, R values a column (at most 128 columns a slice, or
   // ks_len for very wide blocks, staged 128 at a time)
-  for (int kb = 0; kb < n; kb += 128) {
+  const int kb0 = max(klo - k0, 0) & ~127;
+  for (int kb = kb0; kb < n; kb += 128) {
     const int nb = min(128, n - kb);
     // two batches of columns: the second is in flight while the first is used
     vec_t a[2][UN];
@@ -99,7 +103,7 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
     };
     load(a[0], 0);
     load(a[1], 4 * UN);
-    if (kb) __syncthreads();
+    if (kb > kb0) __syncthreads();
     for (int e = threadIdx.x; e < nb * R; e += NT)
       xs[e] = g.x[k0 + kb + e / R + (int64_t)(e % R) * g.sx];
     __syncthreads();
@@ -139,7 +143,8 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
       double v[GEMV_KS];
 #pragma unroll
       for (int q = 0; q < GEMV_KS; ++q)
-        v[q] = q < nsl ? cload(&g.partial[((int64_t)q * R + r) * g.M + m]) : 0.0;
+        v[q] = q >= sl0 && q < sl0 + nsl ? cload(&g.partial[((int64_t)q * R + r) * g.M + m])
+                                         : 0.0;
       s = v[0];
 #pragma unroll
       for (int q = 1; q < GEMV_KS; ++q) s += v[q];
@@ -198,6 +203,8 @@ __device__ void gemv_t_body(const GemvT& g, double* sh) {
   if (g.tri && i < (j0 & ~63)) i += 4 * RB;  // above the columns' diagonal tile
 #pragma unroll 2
   for (; i < g.M; i += 4 * RB) {
+    const int ib = __builtin_amdgcn_readfirstlane(i - lane * V);
+    if (g.band.lo(ib, min(RB, g.M - ib), g.N) >= j0 + TC) continue;  // zeros here
     vec_t a[TC];
 #pragma unroll
     for (int c = 0; c < TC; ++c)

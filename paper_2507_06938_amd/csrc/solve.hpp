@@ -28,6 +28,7 @@ struct GemvN {
   int32_t* cnt;
   int a32;  // A stored in FP32
   int64_t sx, sb1, so1, s2;
+  Band band;  // of A's rows (period 0: dense)
 };
 
 // y = beta*base + alpha*A^T*x with x = [x1 (rows < split); x2], for the
@@ -46,6 +47,7 @@ struct GemvT {
   double* y;
   int a32;  // A stored in FP32
   int64_t sx1, sx2, sb, sy;
+  Band band;  // of A's rows (period 0: dense)
 };
 
 // Batched launches over job arrays in device memory; max_M / max_N bound the

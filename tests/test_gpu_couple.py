@@ -1,0 +1,107 @@
+"""The product of the sparse coupling blocks and what follows from its zeros.
+
+The assembled sub-diagonal blocks are stencils, and the factorisation, the
+solves and the selected inversion skip what is zero in them and in their
+product with G_t^T.  A caller's own block (set_block) may be dense and takes
+the general products.  Setting a block to the value it already has therefore
+runs both on the same matrix: their results must agree to rounding (the
+diagonal blocks' sums are the same sums in another order: 1e-13 of the largest
+entry, times the growth over the chain), in mixed precision bit for bit where
+only FP32 products are involved.  The sizes put a response's first row inside
+a tile (ns not a multiple of 32), the padding in a tile of its own, the band
+over the whole block, and more than one group of arrow rows.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import fobj as OF
+from oracle import model as OM
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def D():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2507_06938_amd import dalia
+    dalia.lib()
+    return dalia
+
+
+def run(ws, wl, D, rhs, set_value):
+    ws.assemble(wl.theta)
+    if set_value:
+        ws.set_block(D.DL_QC, 1, 0, ws.get_block(D.DL_QC, 1, 0).clone())
+    ld, info = ws.factor()
+    out = {"logdet": ld[-1:], "x": ws.solve(rhs.clone(), refine_max=0)}
+    for t in range(wl.nt):
+        for kind in (0, 1, 2):
+            if (kind == 1 and t == wl.nt - 1) or (kind == 2 and wl.nr == 0):
+                continue
+            B = ws.get_block(D.DL_QC, kind, t)
+            out["%d,%d" % (kind, t)] = torch.tril(B) if kind == 0 else B
+    out["var"] = ws.selinv()
+    torch.cuda.synchronize()
+    assert (info == 0).all()
+    return {k: v.cpu() for k, v in out.items()}
+
+
+# (nx, nt, nv, nr, two chains, mixed, family)
+SHAPES = [(5, 3, 1, 1, True, False, "separable"),    # the band covers the block
+          (13, 4, 1, 3, True, False, "separable"),
+          (20, 3, 1, 0, False, False, "separable"),  # no arrow
+          (9, 4, 2, 2, True, False, "separable"),    # responses start inside a tile
+          (11, 3, 3, 3, False, False, "separable"),  # nine arrow rows
+          (17, 3, 2, 1, True, False, "diffusion"),
+          (12, 4, 1, 2, True, True, "separable"),
+          (10, 3, 3, 1, False, True, "separable")]
+
+
+@pytest.mark.parametrize("nx,nt,nv,nr,two,mixed,family", SHAPES)
+def test_stencil_products_equal_dense_ones(D, nx, nt, nv, nr, two, mixed, family):
+    wl = W.scaled("couple", nx, nt, nv, nr, 90, seed=7, model=family)
+    ws = D.Workspace(D.Model.from_workload(wl), mixed=mixed, two_sided=two, selinv=True)
+    rng = np.random.default_rng(5)
+    rhs = torch.tensor(rng.standard_normal((2, wl.N)), device="cuda")
+    a = run(ws, wl, D, rhs, False)
+    b = run(ws, wl, D, rhs, True)
+    for k in a:
+        # the arrow rows of a mixed univariate factor are rounded once, not per term
+        tol = 2e-5 if mixed else 1e-10
+        scale = max(b[k].abs().max().item(), 1e-300)
+        assert (a[k] - b[k]).abs().max().item() <= tol * scale, k
+        if mixed and nv > 1:
+            assert torch.equal(a[k], b[k]) or k in ("var",), k
+    # and the assembled plans are back after the next assembly
+    c = run(ws, wl, D, rhs, False)
+    for k in a:
+        assert torch.equal(a[k], c[k]), k
+
+
+def test_dense_caller_block(D):
+    """A caller's dense sub-diagonal block against a dense factorisation."""
+    wl = W.scaled("couple_dense", 12, 3, 1, 1, 60, seed=9)
+    ref = OF.fobj_parts(wl, wl.theta, return_factors=True)
+    perm = OM.bta_permutation(wl.nv, wl.ns, wl.nt, wl.nr)
+    Q = ref["Qc"].toarray()[np.ix_(perm, perm)]
+    ws = D.Workspace(D.Model.from_workload(wl), selinv=True)
+    ws.assemble(wl.theta)
+    b = wl.b
+    rng = np.random.default_rng(6)
+    E = 1e-3 * np.abs(np.diag(Q)).min() * rng.standard_normal((b, b))
+    B = Q[b:2 * b, :b] + E
+    Q[b:2 * b, :b] = B
+    Q[:b, b:2 * b] = B.T
+    ws.set_block(D.DL_QC, 1, 0, torch.tensor(B, device="cuda"))
+    ld, info = ws.factor(D.DL_QC)
+    r = rng.standard_normal((3, wl.N))
+    x = ws.solve(torch.tensor(r, device="cuda"), refine_max=0).cpu().numpy()
+    var = ws.selinv().cpu().numpy()
+    assert int(info[0]) == 0
+    assert abs(ld[0].item() - np.linalg.slogdet(Q)[1]) <= 1e-9 * abs(ld[0].item())
+    xs = np.linalg.solve(Q, r.T).T
+    np.testing.assert_allclose(x, xs, rtol=0, atol=1e-9 * np.abs(xs).max())
+    np.testing.assert_allclose(var, np.diag(np.linalg.inv(Q)), rtol=1e-8)
