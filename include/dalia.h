@@ -195,15 +195,12 @@ enum {
                          differ from the one-sided order by rounding only.
                          Relies on symmetric sub-diagonal blocks, which
                          every model of this library has                    */,
-  DL_WS_FOLD_INV = 64 /* form each diagonal block's inverse L_tt^-1 inside
-                         the launches of its blocked factorisation (one row
-                         of 64 x 64 tiles per panel step, left-looking)
-                         instead of by recursive GEMM halving after it:
-                         about 12 fewer dependent launches per block, faster
-                         when few blocks are factored at once (single
-                         evaluations); for wide batches the recursive
-                         inversion is faster.  Results differ from the
-                         default by rounding only                           */,
+  DL_WS_FOLD_INV = 64 /* kept for callers that set it: how the diagonal
+                         blocks were inverted.  Every workspace now forms
+                         G_t = L_tt^-1 beside the factor as described for
+                         DL_WS_DAG, which is the faster way at every block
+                         size, and gives the same results with and
+                         without this flag                                  */,
   DL_WS_WARM_START = 128 /* DL_LIK_POISSON: start each instance's inner
                          Newton search from its mode of the previous pass
                          (when that pass converged) instead of x = 0.  For
@@ -211,20 +208,16 @@ enum {
                          it takes fewer steps; the mode is unique, so results
                          differ from a cold start by rounding only, but they
                          depend on the call history                        */,
-  DL_WS_DAG = 256     /* factor each step's diagonal blocks in one persistent
-                         launch (a tile-task graph, Sec. III-A's Cholesky
-                         of the diagonal block with its inverse formed
-                         alongside): workgroups take 64 x 64 tile tasks --
-                         tile factor, panel solve, trailing update, inverse
-                         accumulation and inverse row -- in a fixed order and
-                         wait on per-tile readiness counters, so the next
-                         tile factor starts as soon as its tile is final
-                         instead of after a whole panel launch.  Holds the
-                         inverse like DL_WS_FOLD_INV; needs one bp x bp
-                         block of doubles per matrix and elimination chain
-                         for the L tiles.
-                         Results differ from the panel path by rounding
-                         only                                               */
+  DL_WS_DAG = 256     /* kept for callers that set it: every workspace
+                         factors each step's diagonal blocks of two or more
+                         64 x 64 tiles in one persistent launch (a tile-task
+                         graph, Sec. III-A's Cholesky of the diagonal block
+                         with its inverse formed alongside): workgroups take
+                         64 x 64 tile tasks -- tile factor, panel solve,
+                         trailing update, inverse accumulation and inverse
+                         row -- in a fixed order and wait on per-tile
+                         readiness counters, so the next tile factor starts
+                         as soon as its tile is final                       */
 };
 /* FP64 iterative refinement of the mean (DL_WS_MIXED workspaces; any
  * workspace through bta_solve on request): x <- x + c, where c solves
@@ -242,7 +235,7 @@ enum {
 #define DL_REFINE_MAX 10
 #define DL_REFINE_STEPS_GRAPH 3
 #define DL_INFO_NOTCONV (-1)
-/* info value of a factorisation whose persistent launch (DL_WS_DAG) gave up
+/* info value of a factorisation whose persistent launch gave up
  * waiting for a tile (it never should; f is then -inf). */
 #define DL_INFO_TIMEOUT (-2)
 

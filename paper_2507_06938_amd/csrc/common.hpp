@@ -206,7 +206,7 @@ hipError_t launch_panel_updates(const PanelTask* tasks_dev, int ntask, int grid,
 struct DagBlock {
   double* A;          // the block (bp x bp, ld)
   int64_t ld;
-  double* L;          // tiles L(i, k), i > k, same layout and ld as A
+  double* L;          // tiles L(i, k), i > k, at ((i (i-1)) / 2 + k) * 4096, ld 64
   double* stage;      // inverse accumulators: tile (r, c) at ((r (r-1)) / 2 + c) * 4096, ld 64
   double* logdiag;    // 64 * nbk entries
   int64_t* info;
@@ -215,11 +215,21 @@ struct DagBlock {
                       // the launch's last workgroup zeroes them again
   int32_t nbk, pad_;
 };
+// A task with its waits decoded (dag::waits_of): lane e of a worker waits until
+// counter wait[e][0] reaches wait[e][1] (value 0: no wait).  Decoded on the
+// device, the waits passed through scratch memory before every task.
+struct DagTask {
+  uint64_t word;       // dag::pack
+  int32_t wait[4][2];
+  int32_t set[2];      // set when the task completes
+  int32_t mid[2];      // C: set once L(k+1, k) is stored
+  int32_t pad_[2];
+};
 // head[0]: next task, head[1]: finished workgroups, head[2]: set when a wait
 // gave up (then every later wait gives up at once, so the launch ends
 // quickly); all zero before the launch and reset by its last workgroup.
 // workers: the grid size.
-hipError_t launch_dag_chol(const uint64_t* tasks, int ntask, const DagBlock* blocks,
+hipError_t launch_dag_chol(const DagTask* tasks, int ntask, const DagBlock* blocks,
                            int nblocks, int32_t* head, int workers, hipStream_t s);
 
 // ---- small batched element-wise jobs ------------------------------------------

@@ -60,6 +60,7 @@ struct Task {
   int type;
   int i, k, j;  // F: (k, k, k); S: (i, k, k); U: (i, k, j); A: (r, c, m); R: (j, c, c);
                 // C: (k + 1, k, k)
+  int n = 1;    // U, A: the tasks of j, j + 1, .., j + n - 1 in one (see join)
 };
 
 // Counter indices within a block: tiles first, then accumulators.
@@ -79,6 +80,7 @@ struct Wait {
 // when it completes.
 DL_DAG_FN int waits_of(int nbk, const Task& t, Wait* w, Wait* sets) {
   int n = 0;
+  const int last = t.j + t.n - 1;
   auto gfinal = [&](int m, int c) {  // G(m, c) final
     if (m == c) w[n++] = {tile_ctr(c, c), c + 1};
     else w[n++] = {tile_ctr(m, c), c + 2};
@@ -95,15 +97,16 @@ DL_DAG_FN int waits_of(int nbk, const Task& t, Wait* w, Wait* sets) {
       break;
     case T_U:
       w[n++] = {tile_ctr(t.i, t.k), t.j};
-      w[n++] = {tile_ctr(t.i, t.j), t.j + 1};
-      if (t.k != t.i) w[n++] = {tile_ctr(t.k, t.j), t.j + 1};
-      *sets = {tile_ctr(t.i, t.k), t.j + 1};
+      // L(i, last) final: so are the row's tiles before it, its updates
+      w[n++] = {tile_ctr(t.i, last), last + 1};
+      if (t.k != t.i) w[n++] = {tile_ctr(t.k, last), last + 1};
+      *sets = {tile_ctr(t.i, t.k), last + 1};
       break;
-    case T_A:  // (r, c, m) = (i, k, j)
+    case T_A:  // (r, c, m) = (i, k, j); G(last, c) needed every G(m, c) before it
       if (t.j > t.k) w[n++] = {acc_ctr(nbk, t.i, t.k), t.j - t.k};
-      w[n++] = {tile_ctr(t.i, t.j), t.j + 1};
-      gfinal(t.j, t.k);
-      *sets = {acc_ctr(nbk, t.i, t.k), t.j - t.k + 1};
+      w[n++] = {tile_ctr(t.i, last), last + 1};
+      gfinal(last, t.k);
+      *sets = {acc_ctr(nbk, t.i, t.k), last - t.k + 1};
       break;
     case T_R:  // (j, c) = (i, k)
       w[n++] = {tile_ctr(t.i, t.i), t.i + 1};
@@ -216,16 +219,16 @@ inline std::vector<Task> schedule(int nbk, bool inverse, std::vector<int>* level
   return out;
 }
 
-// A task word: type (4 bits), block within the launch (12), and the three
-// tile indices (16 bits each).
+// A task word: type and n - 1 (4 bits each), the three tile indices (12 bits
+// each) and the block within the launch (20).
 DL_DAG_FN uint64_t pack(const Task& t, int block) {
-  return (uint64_t)t.type | ((uint64_t)block << 4) | ((uint64_t)t.i << 16) |
-         ((uint64_t)t.k << 32) | ((uint64_t)t.j << 48);
+  return (uint64_t)t.type | ((uint64_t)(t.n - 1) << 4) | ((uint64_t)t.i << 8) |
+         ((uint64_t)t.k << 20) | ((uint64_t)t.j << 32) | ((uint64_t)block << 44);
 }
 DL_DAG_FN Task unpack(uint64_t w, int* block) {
-  *block = (int)((w >> 4) & 0xfff);
-  return Task{(int)(w & 0xf), (int)((w >> 16) & 0xffff), (int)((w >> 32) & 0xffff),
-              (int)((w >> 48) & 0xffff)};
+  *block = (int)(w >> 44);
+  return Task{(int)(w & 0xf), (int)((w >> 8) & 0xfff), (int)((w >> 20) & 0xfff),
+              (int)((w >> 32) & 0xfff), (int)((w >> 4) & 0xf) + 1};
 }
 
 // The task list of one launch over several blocks (inverse[b]: block b's
@@ -239,9 +242,11 @@ inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks,
     Task t;
   };
   std::vector<Item> all;
+  std::vector<int> lv, sl;
+  std::vector<Task> s;
   for (size_t b = 0; b < nbks.size(); ++b) {
-    std::vector<int> lv, sl;
-    std::vector<Task> s = schedule(nbks[b], inverse[b] != 0, &lv, &sl, chain);
+    if (b == 0 || nbks[b] != nbks[b - 1] || inverse[b] != inverse[b - 1])
+      s = schedule(nbks[b], inverse[b] != 0, &lv, &sl, chain);
     for (size_t p = 0; p < s.size(); ++p) all.push_back({lv[p] + sl[p], lv[p], (int)b, p, s[p]});
   }
   std::stable_sort(all.begin(), all.end(), [](const Item& a, const Item& b) {
@@ -255,6 +260,54 @@ inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks,
   for (const Item& it : all) out.push_back(pack(it.t, it.block));
   return out;
 }
+// The list with the updates of a tile, and the terms of an accumulator, joined
+// `most` (up to 16) at a time (j from one multiple of it to the next) into the
+// word of the last of them: the tile is then read and written once for all of
+// them, and their operands are loaded while the product before is formed.  Only
+// the next task of the same tile waits on what a joined task would have set, so
+// the list still only waits on earlier tasks.  The last update of a tile near
+// the diagonal (i - k <= 4) stays alone: the chain waits for it.
+inline std::vector<uint64_t> join(const std::vector<uint64_t>& list, int most) {
+  std::vector<uint64_t> out;
+  out.reserve(list.size());
+  for (uint64_t w : list) {
+    int b = 0;
+    Task t = unpack(w, &b);
+    if (t.type == T_U || t.type == T_A) {
+      // one past the last index of the task's tile or accumulator that may join
+      const int own = t.i == t.k ? t.k - 1 : t.k;  // C has the diagonal's last
+      const int end = t.type == T_A ? t.i - 1 : (t.i - t.k <= 4 ? own - 1 : own);
+      const int lo0 = t.j / most * most, lo = t.type == T_A && lo0 < t.k ? t.k : lo0;
+      const int hi = lo0 + most < end ? lo0 + most : end;
+      if (t.j < hi) {
+        if (t.j + 1 < hi) continue;
+        t.n = hi - lo;
+        t.j = lo;
+      }
+    }
+    out.push_back(pack(t, b));
+  }
+  return out;
+}
+
+// How many tasks to join in a launch of `words` tasks whose longest block has
+// `nbk` tiles (the results are the same bits for any number).  By the tasks
+// per step of the chain, with what 1 / 2 / 4 / 8 took in us:
+//   * below 400 the workers mostly wait, and fewer of them take part in a tile's
+//     updates: 2 x 15 tiles 274 / 250 / 243 / 264, 2 x 19 409 / 360 / 337 / 369,
+//     1 x 32 701 / 667 / 614 / 684;
+//   * then the chain competes with the updates, and the shortest tasks let it
+//     through first: 15 x 10 216 / 227 / 246 / 273, 4 x 19 408 / 432 / 440 / 496,
+//     2 x 32 690 / 724 / 742 / 802;
+//   * from 850 on the updates' memory traffic counts: 9 x 19 620 / 541 / 520 / 607,
+//     17 x 15 566 / 488 / 456 / 504, 2 x 43 1300 / 1193 / 1142 / 1229;
+//   * from 2000 on it is all that does: 9 x 32 2826 / 2237 / 1932 / 1816, 31 x 19
+//     2138 / 1743 / 1533 / 1435, 1 x 95 7806 / 6026 / 5153 / 4895.
+inline int join_count(size_t words, int nbk) {
+  const size_t per = words / (size_t)nbk;
+  return per < 400 ? 4 : (per < 850 ? 1 : (per < 2000 ? 4 : 8));
+}
+
 inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks, bool inverse,
                                          bool chain = true) {
   return launch_list(nbks, std::vector<char>(nbks.size(), inverse ? 1 : 0), chain);

@@ -582,8 +582,8 @@ hipError_t launch_panel_updates(const PanelTask* tasks, int ntask, int grid,
 //
 // Workgroups of 16 waves take task words from the launch's list in order
 // (one atomic add on head[0] each), wait until the counters the task depends
-// on are set (one lane polls, 0.5 s limit), run the task on 64 x 64 tiles
-// staged in two LDS tiles and set the task's counter.  The tile operations
+// on are set (a lane polls each, 2 s limit), run the task on 64 x 64 tiles
+// staged in LDS and set the task's counter.  The tile operations
 // are those of the panel path: the same staging, the same MFMA products
 // (mfma1_k64), the same tile factor (potrf_body).
 //
@@ -599,7 +599,7 @@ hipError_t launch_panel_updates(const PanelTask* tasks, int ntask, int grid,
 // counter is set; the counters themselves are relaxed device-scope atomics.
 
 namespace {
-constexpr long long kDagWaitTicks = 50000000;  // 0.5 s of the 100 MHz constant clock
+constexpr long long kDagWaitTicks = 200000000;  // 2 s of the 100 MHz constant clock
 
 typedef __attribute__((address_space(1))) int32_t gint;
 __device__ __forceinline__ int dag_load(const int32_t* p) {
@@ -627,37 +627,38 @@ __device__ bool dag_wait(const int32_t* p, int value, int32_t* abort) {
 
 }  // namespace
 
-__global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restrict__ tasks,
+__global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const DagTask* __restrict__ tasks,
                                                        int ntask,
                                                        const DagBlock* __restrict__ blocks,
                                                        int nblocks, int32_t* head) {
-  __shared__ __align__(16) double pool[3 * TILE_LDS];
+  __shared__ __align__(16) double pool[4 * TILE_LDS];
   __shared__ int s_task, s_last;
   double* S0 = pool;
   double* S1 = pool + TILE_LDS;
   double* S2 = pool + 2 * TILE_LDS;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int p0 = 16 * (wv >> 2), q0 = 16 * (wv & 3);  // this wave's 16 x 16 block
+  if (threadIdx.x == 0) s_task = atomicAdd(head, 1);
+  __syncthreads();
   for (;;) {
     const int l = lane_index();
     const int lr = l & 15, lk = l >> 4;
-    if (threadIdx.x == 0) s_task = atomicAdd(head, 1);
-    __syncthreads();
-    const int ti = s_task;
+    const int ti = __builtin_amdgcn_readfirstlane(s_task);
     if (ti >= ntask) break;
     int bi = 0;
-    const dag::Task t = dag::unpack(tasks[ti], &bi);
+    const DagTask* rec = tasks + ti;
+    const dag::Task t = dag::unpack(rec->word, &bi);
     const DagBlock B = blocks[bi];
     const int64_t ld = B.ld;
     auto tile = [&](double* base, int r, int c) {
       return base + (int64_t)r * NB + (int64_t)c * NB * ld;
     };
-    if (threadIdx.x == 0) {
-      dag::Wait w[4], set;
-      const int nw = dag::waits_of(B.nbk, t, w, &set);
-      bool ok = true;
-      for (int e = 0; e < nw; ++e) ok = dag_wait(B.ctr + w[e].ctr, w[e].value, head + 2) && ok;
-      if (!ok)
+    auto tileL = [&](int r, int c) {
+      return B.L + ((int64_t)r * (r - 1) / 2 + c) * (NB * NB);
+    };
+    if (threadIdx.x < 4) {  // a lane per wait: their polls overlap
+      const int wc = rec->wait[threadIdx.x][0], wval = rec->wait[threadIdx.x][1];
+      if (wval > 0 && !dag_wait(B.ctr + wc, wval, head + 2))
         atomicCAS((unsigned long long*)B.info, 0ull, (unsigned long long)(int64_t)DL_INFO_TIMEOUT);
     }
     __syncthreads();
@@ -685,10 +686,10 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
         __syncthreads();
         v4d a0 = {0.0, 0.0, 0.0, 0.0};
         mfma1_k64(S1, p0, S0, q0, a0, p0 + 16);  // L(m = q0 + lr, c = p0 + lk + 4r)
-        double* Lo = tile(B.L, k1, k);
+        double* Lo = tileL(k1, k);
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) {
-          cstore(&Lo[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * ld], a0[rg]);
+          cstore(&Lo[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * NB], a0[rg]);
           S2[(p0 + lk + 4 * rg) * LDL + q0 + lr] = a0[rg];  // S2[c][m] = L(m, c)
         }
         __syncthreads();
@@ -701,11 +702,7 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
         // latency overlaps the update above)
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
-        if (threadIdx.x == 0) {
-          dag::Wait m;
-          dag::mid_set(t, &m);
-          dag_store(B.ctr + m.ctr, m.value);
-        }
+        if (threadIdx.x == 0) dag_store(B.ctr + rec->mid[0], rec->mid[1]);
         fk = k1;
         break;
       }
@@ -719,28 +716,44 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
         __syncthreads();
         v4d a0 = {0.0, 0.0, 0.0, 0.0};
         mfma1_k64(S1, p0, S0, q0, a0, p0 + 16);  // L(m = q0 + lr, c = p0 + lk + 4r)
-        double* Lo = tile(B.L, t.i, t.k);
+        double* Lo = tileL(t.i, t.k);
 #pragma unroll
-        for (int rg = 0; rg < 4; ++rg) cstore(&Lo[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * ld], a0[rg]);
+        for (int rg = 0; rg < 4; ++rg) cstore(&Lo[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * NB], a0[rg]);
         break;
       }
       case dag::T_U: {
-        // A(i, k) -= L(i, j) L(k, j)^T
+        // A(i, k) -= L(i, j) L(k, j)^T for n j's, the next one's tiles in flight
         const bool diag = t.i == t.k;
         double vp[DPER], vq[DPER], cpre[4];
-        tile_regs<false>(tile(B.L, t.i, t.j), ld, vp);
-        if (!diag) tile_regs<false>(tile(B.L, t.k, t.j), ld, vq);
+        tile_regs<false>(tileL(t.i, t.j), NB, vp);
+        if (!diag) tile_regs<false>(tileL(t.k, t.j), NB, vq);
         double* C = tile(B.A, t.i, t.k);
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg) cpre[rg] = cload(&C[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * ld]);
         regs_to_cols(vp, S0);
         if (!diag) regs_to_cols(vq, S1);
-        __syncthreads();
-        v4d u0 = {0.0, 0.0, 0.0, 0.0};
-        mfma1_k64(diag ? S0 : S1, p0, S0, q0, u0);  // update(m = q0 + lr, n = p0 + lk + 4r)
+#pragma unroll 1
+        for (int q = 0; q < t.n; ++q) {
+          double* X = pool + (q & 1) * 2 * TILE_LDS;
+          double* Xn = pool + (~q & 1) * 2 * TILE_LDS;
+          if (q + 1 < t.n) {
+            tile_regs<false>(tileL(t.i, t.j + q + 1), NB, vp);
+            if (!diag) tile_regs<false>(tileL(t.k, t.j + q + 1), NB, vq);
+          }
+          __syncthreads();
+          // rounded like a task of its own
+          v4d u0 = {0.0, 0.0, 0.0, 0.0};
+          mfma1_k64(diag ? X : X + TILE_LDS, p0, X, q0, u0);  // update(m = q0 + lr, n = p0 + lk + 4r)
+#pragma unroll
+          for (int rg = 0; rg < 4; ++rg) cpre[rg] -= u0[rg];
+          if (q + 1 < t.n) {
+            regs_to_cols(vp, Xn);
+            if (!diag) regs_to_cols(vq, Xn + TILE_LDS);
+          }
+        }
 #pragma unroll
         for (int rg = 0; rg < 4; ++rg)
-          cstore(&C[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * ld], cpre[rg] - u0[rg]);
+          cstore(&C[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * ld], cpre[rg]);
         break;
       }
       case dag::T_A:
@@ -748,7 +761,7 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
         // A(r, c, m): S(r, c) (+)= L(r, m) G(m, c);
         // R(j, c):    t = S(j, c) + L(j, j-1) G(j-1, c), G(j, c) = -G_jj t
         const bool row = t.type == dag::T_R;
-        const int r = t.i, c = t.k, m = row ? t.i - 1 : t.j;
+        const int r = t.i, c = t.k, m = row ? t.i - 1 : t.j, n = row ? 1 : t.n;
         double* Sd = B.stage + ((int64_t)r * (r - 1) / 2 + c) * (NB * NB);
         const bool acc = row ? (r - 1 > c) : (m > c);
         double prev[4] = {0.0, 0.0, 0.0, 0.0};
@@ -757,14 +770,27 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
           for (int rg = 0; rg < 4; ++rg) prev[rg] = cload(&Sd[(q0 + lr) + (p0 + lk + 4 * rg) * NB]);
         }
         double vy[DPER], vx[DPER], vg[DPER];
-        tile_regs<false>(tile(B.L, r, m), ld, vy);  // Y = L(r, m)
+        tile_regs<false>(tileL(r, m), NB, vy);  // Y = L(r, m)
         tile_regs<true>(tile(B.A, m, c), ld, vx);   // X = G(m, c)
         if (row) tile_regs<true>(tile(B.A, r, r), ld, vg);  // G_jj, for the second product
         regs_to_cols(vy, S0);
         regs_to_rows(vx, S1);
-        __syncthreads();
         v4d tv = {prev[0], prev[1], prev[2], prev[3]};
-        mfma1_k64(S1, p0, S0, q0, tv);  // (Y X)(q0 + lr, p0 + lk + 4r)
+#pragma unroll 1
+        for (int q = 0; q < n; ++q) {
+          double* X = pool + (q & 1) * 2 * TILE_LDS;
+          double* Xn = pool + (~q & 1) * 2 * TILE_LDS;
+          if (q + 1 < n) {
+            tile_regs<false>(tileL(r, m + q + 1), NB, vy);
+            tile_regs<true>(tile(B.A, m + q + 1, c), ld, vx);
+          }
+          __syncthreads();
+          mfma1_k64(X + TILE_LDS, p0, X, q0, tv);  // (Y X)(q0 + lr, p0 + lk + 4r)
+          if (q + 1 < n) {
+            regs_to_cols(vy, Xn);
+            regs_to_rows(vx, Xn + TILE_LDS);
+          }
+        }
         if (!row) {
 #pragma unroll
           for (int rg = 0; rg < 4; ++rg) cstore(&Sd[(q0 + lr) + (p0 + lk + 4 * rg) * NB], tv[rg]);
@@ -790,10 +816,10 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-      dag::Wait w[4], set;
-      (void)dag::waits_of(B.nbk, t, w, &set);
-      dag_store(B.ctr + set.ctr, set.value);
+      dag_store(B.ctr + rec->set[0], rec->set[1]);
+      s_task = atomicAdd(head, 1);
     }
+    __syncthreads();
   }
   // the last workgroup out (every task is then complete) zeroes the
   // counters and the head for the next launch
@@ -812,7 +838,7 @@ __global__ __launch_bounds__(POTRF_NT) void k_dag_chol(const uint64_t* __restric
   }
 }
 
-hipError_t launch_dag_chol(const uint64_t* tasks, int ntask, const DagBlock* blocks,
+hipError_t launch_dag_chol(const DagTask* tasks, int ntask, const DagBlock* blocks,
                            int nblocks, int32_t* head, int workers, hipStream_t s) {
   if (ntask <= 0 || nblocks <= 0 || workers <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_dag_chol, dim3(workers), dim3(POTRF_NT), 0, s, tasks, ntask, blocks,

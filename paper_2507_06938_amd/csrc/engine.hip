@@ -33,7 +33,7 @@ namespace dl {
 enum OpKind : int {
   OP_GEMM, OP_POTRF, OP_MISC, OP_GEMV_N, OP_GEMV_T, OP_SUM, OP_FINISH,
   OP_ASM_COLS, OP_ASM_TIPS, OP_THETA, OP_QUAD, OP_COMBINE, OP_GEMM32, OP_RES,
-  OP_PANEL, OP_DAG, OP_COUPLE, OP_NKIND
+  OP_DAG, OP_COUPLE, OP_NKIND
 };
 
 // One step of one sequence (before merging).
@@ -44,7 +44,6 @@ struct Step {
   double flops = 0.0, bytes = 0.0;
   std::vector<GemmTask> gemm;
   PotrfTileArgs potrf{};
-  PanelTask panel{};
   DagBlock dagb{};
   bool dag_inv = true;  // the block's inverse is formed too
   MiscJob misc{};
@@ -94,10 +93,11 @@ struct Plan {
 struct Descs {
   std::vector<GemmTask> gemm;
   std::vector<PotrfTileArgs> potrf;
-  std::vector<PanelTask> panel;
   std::vector<DagBlock> dagb;   // blocks of the persistent factorisation launches
-  std::vector<uint64_t> dagt;   // their task words (one list per launch)
+  std::vector<DagTask> dagt;    // their tasks
   int dag_launches = 0;
+  // first word and length of the list over blocks of given sizes (and inverses)
+  std::map<std::pair<std::vector<int>, std::vector<char>>, std::pair<int, int>> dag_lists;
   std::vector<MiscJob> misc;
   std::vector<GemvN> gn;
   std::vector<GemvT> gt;
@@ -114,9 +114,8 @@ struct Descs {
 struct DevDescs {
   GemmTask* gemm = nullptr;
   PotrfTileArgs* potrf = nullptr;
-  PanelTask* panel = nullptr;
   DagBlock* dagb = nullptr;
-  uint64_t* dagt = nullptr;
+  DagTask* dagt = nullptr;
   MiscJob* misc = nullptr;
   GemvN* gn = nullptr;
   GemvT* gt = nullptr;
@@ -176,13 +175,6 @@ static void merge(const std::vector<std::vector<Step>>& seqs, Descs& D,
   L.count = (int)D.vec.size() - L.off;                  \
   break;
       case OP_POTRF: PUSH(potrf, potrf)
-      case OP_PANEL: {
-        L.off = (int)D.panel.size();
-        for (const Step* st : g) D.panel.push_back(st->panel);
-        L.count = (int)D.panel.size() - L.off;
-        L.gx = finalize_panels(D.panel.data() + L.off, L.count);
-        break;
-      }
       case OP_DAG: {
         // one persistent launch over the blocks of the merged steps: their
         // tasks in one list (dag.hpp)
@@ -195,10 +187,34 @@ static void merge(const std::vector<std::vector<Step>>& seqs, Descs& D,
           inv.push_back(st->dag_inv ? 1 : 0);
         }
         L.count = (int)D.dagb.size() - L.off;
-        const std::vector<uint64_t> tl = dag::launch_list(nbks, inv);
-        L.gy = (int)D.dagt.size();
-        D.dagt.insert(D.dagt.end(), tl.begin(), tl.end());
-        L.gx = (int)tl.size();
+        // launches over blocks of the same sizes share their list
+        auto [at, fresh] = D.dag_lists.try_emplace({nbks, inv});
+        if (fresh) {
+          std::vector<uint64_t> tl = dag::launch_list(nbks, inv);
+          tl = dag::join(tl, dag::join_count(tl.size(), *std::max_element(nbks.begin(), nbks.end())));
+          at->second = {(int)D.dagt.size(), (int)tl.size()};
+          for (uint64_t w : tl) {
+            int b = 0;
+            const dag::Task t = dag::unpack(w, &b);
+            dag::Wait ws[4], set, mid;
+            DagTask r{};
+            r.word = w;
+            const int nw = dag::waits_of(nbks[b], t, ws, &set);
+            for (int e = 0; e < nw; ++e) {
+              r.wait[e][0] = (int32_t)ws[e].ctr;
+              r.wait[e][1] = ws[e].value;
+            }
+            r.set[0] = (int32_t)set.ctr;
+            r.set[1] = set.value;
+            if (dag::mid_set(t, &mid)) {
+              r.mid[0] = (int32_t)mid.ctr;
+              r.mid[1] = mid.value;
+            }
+            D.dagt.push_back(r);
+          }
+        }
+        L.gy = at->second.first;
+        L.gx = at->second.second;
         L.gz = D.dag_launches++;
         break;
       }
@@ -279,160 +295,54 @@ static Step misc_step(uint64_t key, int cat, int kind, double* dst,
   return s;
 }
 
-// Blocked right-looking Cholesky of the n x n block A (n multiple of 64),
-// panels of 64 columns.  With `fold`, the inverse G = L^{-1} is formed
-// alongside and on return the block holds G (lower triangle); otherwise the
-// block holds L with its diagonal tiles inverted (seq_trtri completes G).  Tile 0 is factored alone (its
-// inverse in place) and its panel solved in place, L(., 0) = P_0 G_00^T;
-// step j then updates the trailing tiles with L(., j), factors tile j+1,
-// solves panel j+1 and advances the inverse by one row of tiles (see
-// PanelTask); a closing launch forms the inverse's last row and one tile
-// copy puts its G(nbk-1, nbk-2) in place.  `tmp` holds the two-tile side
-// ring and the inverse's accumulators (2 + nbk (nbk - 1) / 2 tiles).
-// `breal`: unpadded size (operation count); `count_inv`: count the
-// inverse's b^3/3 (else it is extra work of the inverse-based solves).
-// Keys (major, group 1, j, sub): (0, 0) tile 0, (0, 1) the solve of panel 0,
-// (j, 2) step j and the closing launch (j = nbk - 1), (nbk - 1, 3) the copy.
+// Cholesky of the n x n block A (n multiple of 64) with its inverse G = L^{-1}:
+// on return the block holds G (lower triangle).  One tile is one workgroup's;
+// more of them go to the persistent launch, shared with the other blocks of the
+// same key (inverse = false: G is left unfinished and only log L_ii wanted).
+// At every size from 2 to 95 tiles, one to 62 blocks a launch, that is
+// faster than a launch per panel with the inverse beside it or by recursive
+// halving after it: one f_obj at 10 x 10 nodes 740 against 800 us, 17 x 17
+// bivariate 2.09 / 3.02 ms, 31 points at 12 x 12 trivariate 4.40 / 5.20, 9
+// points at 30 x 30 5.18 / 6.70 and at 45 x 45 19.8 / 23.1 (6 to 8 time steps),
+// 45 x 45 trivariate 47.5 / 51.1; a single tile is not (486 against 468 us).
+// `L`: nbk (nbk - 1) / 2 tiles; `stage`: as many, the inverse's
+// accumulators; ctr: nbk^2 counters.  `breal`: unpadded size (operation count);
+// `count_inv`: count the inverse's b^3/3 (else it is extra work of the
+// inverse-based solves).
 static void seq_potrf(std::vector<Step>& q, uint64_t major, double* A, int64_t ld,
                       int n, double* logdiag, int64_t* info, int64_t row0,
-                      int breal, double* tmp, bool count_inv, bool fold,
-                      double* lbuf = nullptr, int32_t* dctr = nullptr,
-                      bool dag_inv = true) {
+                      int breal, double* L, double* stage, int32_t* ctr, bool count_inv,
+                      bool inverse = true) {
   const int nbk = n / 64;
-  if (lbuf) {
-    // the whole factorisation and inverse in one persistent launch (shared
-    // with the other blocks of the same key)
-    Step s;
-    s.key = K(major, 1, 0, 2);
-    s.kind = OP_DAG;
-    s.cat = DL_CAT_PANEL_SYRK;
-    const double b3 = (double)breal * breal * breal / 3.0;
-    s.flops = b3 + (count_inv ? b3 : 0.0);
-    s.dag_inv = dag_inv;
-    DagBlock& d = s.dagb;
-    d.A = A;
-    d.ld = ld;
-    d.L = lbuf;
-    d.stage = tmp;
-    d.logdiag = logdiag;
-    d.info = info;
-    d.row0 = row0;
-    d.ctr = dctr;
-    d.nbk = nbk;
-    q.push_back(s);
-    return;
-  }
-  auto width = [&](int j) { return (double)std::max(0, std::min(64, breal - j * 64)); };
-  auto below = [&](int j) { return (double)std::max(0, breal - (j + 1) * 64); };
-  double* gside = tmp;
-  double* stage = tmp + 2 * 4096;
-  {
-    const double w = width(0);
-    Step s;
-    s.key = K(major, 1, 0, 0);
+  Step s;
+  s.key = K(major, 1);
+  const double b3 = (double)breal * breal * breal / 3.0;
+  s.flops = b3 + (count_inv ? b3 : 0.0);
+  if (nbk == 1) {
     s.kind = OP_POTRF;
     s.cat = DL_CAT_POTRF_TILE;
-    s.flops = w * w * w / 3.0;
     s.potrf.A = A;
     s.potrf.lda = ld;
     s.potrf.logdiag = logdiag;
     s.potrf.info = info;
     s.potrf.row0 = row0;
     s.potrf.mode = 1;
-    q.push_back(s);
-  }
-  if (nbk == 1) return;
-  {
-    double* panel = A + 64;
-    q.push_back(gemm_step(K(major, 1, 0, 1), DL_CAT_PANEL_TRSM, below(0) * width(0) * width(0),
-                          {mk(panel, ld, A, ld, panel, ld, n - 64, 64, 64, F_TB | F_BETA0,
-                              1.0, 0.0)}));
-  }
-  for (int j = 0; j < (fold ? nbk : nbk - 1); ++j) {
-    const bool last = (j + 1 == nbk);
-    Step s;
-    s.key = K(major, 1, j, 2);
-    s.kind = OP_PANEL;
+  } else {
+    s.kind = OP_DAG;
     s.cat = DL_CAT_PANEL_SYRK;
-    if (!last) {
-      // the trailing update of a right-looking Cholesky, the tile factor and
-      // the solve of the next panel
-      const double w = width(j), w1 = width(j + 1), bl = below(j);
-      s.flops = bl * bl * w + w1 * w1 * w1 / 3.0 + below(j + 1) * w1 * w1;
-    } else if (count_inv) {
-      s.flops = (double)breal * breal * breal / 3.0;  // the whole inverse
-    }
-    PanelTask& t = s.panel;
-    t.A = A;
-    t.ld = ld;
-    t.logdiag = logdiag + (int64_t)(j + 1) * 64;
-    t.info = info;
-    t.row0 = row0 + (int64_t)(j + 1) * 64;
-    t.gside = gside;
-    t.stage = stage;
-    t.j = j;
-    t.nbk = nbk;
-    t.last = last ? 1 : 0;
-    t.inv = fold ? 1 : 0;
-    q.push_back(s);
+    s.dag_inv = inverse;
+    DagBlock& d = s.dagb;
+    d.A = A;
+    d.ld = ld;
+    d.L = L;
+    d.stage = stage;
+    d.logdiag = logdiag;
+    d.info = info;
+    d.row0 = row0;
+    d.ctr = ctr;
+    d.nbk = nbk;
   }
-  if (!fold) return;
-  // G(nbk-1, nbk-2) from the accumulators into place
-  Step cp = misc_step(K(major, 1, nbk - 1, 3), DL_CAT_PANEL_SYRK, MJ_COPY2D,
-                      A + (int64_t)(nbk - 1) * 64 + (int64_t)(nbk - 2) * 64 * ld,
-                      stage + (int64_t)((nbk - 1) * (nbk - 2) / 2 + (nbk - 2)) * 4096, 0);
-  cp.misc.rows = 64;
-  cp.misc.cols = 64;
-  cp.misc.lds = 64;
-  cp.misc.ldd = ld;
-  q.push_back(cp);
-}
-
-// In-place inverse of the lower-triangular factor whose diagonal tiles
-// already hold their inverses: recursive halving, G21 = -G22 (L21 G11), all
-// nodes of one depth merged, deepest first.  temp: n x (n/2 + 64) (ld n).
-// `breal`: unpadded size for the operation count (0: not counted).
-static void collect_nodes(int lo, int hi, int depth,
-                          std::vector<std::vector<int>>& lv) {
-  if (hi - lo <= 1) return;
-  const int mid = lo + (hi - lo) / 2;
-  if ((int)lv.size() <= depth) lv.resize(depth + 1);
-  lv[depth].push_back(lo);
-  lv[depth].push_back(hi);
-  collect_nodes(lo, mid, depth + 1, lv);
-  collect_nodes(mid, hi, depth + 1, lv);
-}
-
-static void seq_trtri(std::vector<Step>& q, uint64_t major, double* A, int64_t ld,
-                      int n, double* temp, int breal, int xf) {
-  const int nbk = n / 64;
-  auto ext = [&](int lo, int hi) {
-    return (double)std::max(0, std::min(hi * 64, breal) - lo * 64);
-  };
-  std::vector<std::vector<int>> lv;
-  collect_nodes(0, nbk, 0, lv);
-  const int D = (int)lv.size();
-  for (int d = D - 1; d >= 0; --d) {
-    std::vector<GemmTask> tT, tG;
-    double fT = 0.0, fG = 0.0;
-    for (size_t k = 0; k < lv[d].size(); k += 2) {
-      const int lo = lv[d][k], hi = lv[d][k + 1];
-      const int mid = lo + (hi - lo) / 2;
-      const int n1 = (mid - lo) * 64, n2 = (hi - mid) * 64;
-      double* L21 = A + (int64_t)mid * 64 + (int64_t)lo * 64 * ld;
-      double* G11 = A + (int64_t)lo * 64 * (ld + 1);
-      double* G22 = A + (int64_t)mid * 64 * (ld + 1);
-      double* T = temp + (int64_t)lo * 64;
-      tT.push_back(mk(L21, ld, G11, ld, T, n, n2, n1, n1, F_KLO_COL | F_BETA0 | xf, 1.0, 0.0));
-      tG.push_back(mk(G22, ld, T, n, L21, ld, n2, n1, n2, F_KHI_ROW | F_BETA0 | xf, -1.0, 0.0));
-      const double r1 = ext(lo, mid), r2 = ext(mid, hi);
-      fT += r2 * r1 * r1;
-      fG += r1 * r2 * r2;
-    }
-    const int lvl = 15 - d;  // deeper levels first
-    q.push_back(gemm_step(K(major, 2, lvl, 0), DL_CAT_TRTRI, fT, tT));
-    q.push_back(gemm_step(K(major, 2, lvl, 1), DL_CAT_TRTRI, fG, tG));
-  }
+  q.push_back(s);
 }
 
 }  // namespace dl
@@ -467,9 +377,9 @@ struct Inst {
   bool two = false;
   int mid = 0;
   double *PcB = nullptr, *ttempB[2] = {nullptr, nullptr};
-  // persistent diagonal-block factorisation (DL_WS_DAG): the L tiles and the
-  // readiness counters of the block each chain factors, per matrix
-  double *lbuf[2] = {nullptr, nullptr}, *lbufB[2] = {nullptr, nullptr};
+  // persistent diagonal-block factorisation: the readiness counters of the block
+  // each chain factors, per matrix, and the L tiles of log|Q_p|'s one block
+  double* Lp = nullptr;
   int32_t *dctr[2] = {nullptr, nullptr}, *dctrB[2] = {nullptr, nullptr};
   double *uB = nullptr, *gpartB = nullptr, *xPB = nullptr;
   int32_t *gcnt = nullptr, *gcntB = nullptr;  // GEMV row-block counters (zero between launches)
@@ -526,8 +436,6 @@ struct dl_ws : PlanSet {
   int flags = 0;
   bool sel = false, keep_qp = false, mixed = false;
   bool splitk = false;
-  bool fold_inv = false;  // inverses inside the panel launches (DL_WS_FOLD_INV)
-  bool dag = false;       // one persistent launch per diagonal block (DL_WS_DAG)
   int dag_workers = 0;           // grid of the persistent launches
   double* partials = nullptr;  // split-k partial tiles (shared by all launches)
   int64_t partials_cap = 0;    // doubles allocated at `partials`
@@ -624,7 +532,6 @@ static hipError_t run_launch(dl_ws* W, const Launch& L, hipStream_t s) {
     int kk = DL_KERNEL_OTHER;
     if (L.kind == OP_GEMM || L.kind == OP_GEMM32) kk = DL_KERNEL_GEMM;
     else if (L.kind == OP_POTRF) kk = DL_KERNEL_POTRF_TILE;
-    else if (L.kind == OP_PANEL) kk = DL_KERNEL_PANEL;
     else if (L.kind == OP_DAG) kk = DL_KERNEL_DAG;
     else if (L.kind == OP_GEMV_N || L.kind == OP_GEMV_T) kk = DL_KERNEL_GEMV;
     else if (L.kind == OP_ASM_COLS) kk = DL_KERNEL_ASSEMBLE;
@@ -648,7 +555,6 @@ static hipError_t run_launch(dl_ws* W, const Launch& L, hipStream_t s) {
         break;
       case OP_RES: e = launch_residual(d.res + L.off, L.count, s); break;
       case OP_POTRF: e = launch_potrf_tiles(d.potrf + L.off, L.count, s); break;
-      case OP_PANEL: e = launch_panel_updates(d.panel + L.off, L.count, L.gx, s); break;
       case OP_DAG:
         e = launch_dag_chol(d.dagt + L.gy, L.gx, d.dagb + L.off, L.count,
                             W->dag_heads + 4 * (int64_t)L.gz,
@@ -806,8 +712,8 @@ static void seq_logdet_qp(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
   s.gx = bp;
   s.gy = 1;
   q.push_back(s);
-  seq_potrf(q, 1, I.Dp, bp, bp, logdiag, info, 0, m.b, I.ttemp[0], false, false,
-            W->dag ? I.lbuf[0] : nullptr, W->dag ? I.dctr[0] : nullptr, false);
+  seq_potrf(q, 1, I.Dp, bp, bp, logdiag, info, 0, m.b, I.Lp, I.ttemp[0], I.dctr[0], false,
+            false);
   const uint64_t tail = (uint64_t)nt_max + 1;
   double* ltip = logdiag + (int64_t)m.nt * bp;
   if (m.ap > 0) {
@@ -956,17 +862,15 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
     }
     // factor and inverse of the diagonal block
     double* tmp = chain == 1 ? I.ttempB[w] : I.ttemp[w];
-    double* lb = W->dag ? (chain == 1 ? I.lbufB[w] : I.lbuf[w]) : nullptr;
-    int32_t* dc = W->dag ? (chain == 1 ? I.dctrB[w] : I.dctr[w]) : nullptr;
-    seq_potrf(q, major, Dt(t), bp, bp, logdiag + (int64_t)t * bp, info,
-              (int64_t)t * m.b, m.b, tmp, count_inv, W->fold_inv, lb, dc);
-    if (!W->fold_inv && !W->dag) seq_trtri(q, major, Dt(t), bp, bp, tmp, count_inv ? m.b : 0, xf);
+    // (the tiles of L go where [C_t; R_t] does afterwards)
+    const int ci = chain == 1 ? 1 : 0;
+    const int nw = ring ? (ci ? 5 : 2) : spare[ci];
+    seq_potrf(q, major, Dt(t), bp, bp, logdiag + (int64_t)t * bp, info, (int64_t)t * m.b, m.b,
+              BRs(nw), tmp, ci ? I.dctrB[w] : I.dctr[w], count_inv);
     const int M = (root ? 0 : bp) + apr;
     if (M <= 0) return;
     const double b = m.b, ar = apr ? m.a : 0;
     const double mreal = (root ? 0.0 : b) + ar;
-    const int ci = chain == 1 ? 1 : 0;
-    const int nw = ring ? (ci ? 5 : 2) : spare[ci];
     // [C_t; R_t] <- [C_t; R_t] L_tt^{-T} = [C_t; R_t] G_t^T, C_t the coupling
     const int fl = F_TB | F_KHI_COL | F_BETA0 | x64 | xf;
     const double* Cin = nullptr;
@@ -1576,7 +1480,6 @@ static dl_status build_plans(dl_ws* W) {
   };
   up(H.gemm, W->Dd.gemm);
   up(H.potrf, W->Dd.potrf);
-  up(H.panel, W->Dd.panel);
   up(H.dagb, W->Dd.dagb);
   up(H.dagt, W->Dd.dagt);
   if (st == DL_OK && H.dag_launches > 0) {
@@ -1588,7 +1491,7 @@ static dl_status build_plans(dl_ws* W) {
                         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount,
                                               dev) != hipSuccess))
       st = DL_EHIP;
-    W->dag_workers = 2 * std::max(cus, 1);
+    W->dag_workers = std::max(cus, 1);  // their LDS fills a compute unit
   }
   up(H.misc, W->Dd.misc);
   up(H.gn, W->Dd.gn);
@@ -1685,12 +1588,9 @@ static void inst_buffers(const dl_ws* W, Inst& I, Alloc&& A) {
   A(tip, (void**)&I.Pc);
   A(tip, (void**)&I.GPc);
   A(tip, (void**)&I.GPp);
-  // per diagonal-block factorisation: the side ring and the folded
-  // inverse's accumulators (2 + nbk (nbk - 1) / 2 tiles of 64 x 64), or
-  // the recursive inverse's bp x (bp / 2 + 64) temporary (the larger)
+  // per diagonal-block factorisation: the inverse's accumulators
   const int64_t nbk = bp / 64;
-  const size_t ftemp = sizeof(double) * std::max<int64_t>(
-      4096 * (2 + nbk * (nbk - 1) / 2), (int64_t)bp * (nbk / 2 + 1) * 64);
+  const size_t ftemp = sizeof(double) * std::max<int64_t>(4096 * nbk * (nbk - 1) / 2, 1);
   for (int w = 0; w < 2; ++w) {
     A(ftemp, (void**)&I.ttemp[w]);
     A(sizeof(double) * m.Np, (void**)&I.logdiag[w]);
@@ -1717,16 +1617,13 @@ static void inst_buffers(const dl_ws* W, Inst& I, Alloc&& A) {
     A(sizeof(double) * m.Np, (void**)&I.xN);
     A(sizeof(double) * 2 * QF_BLOCKS, (void**)&I.tpart);
   }
-  if (W->dag) {
-    const size_t nc = sizeof(int32_t) * (size_t)dag::counters_per_block((int)nbk);
-    for (int w = 0; w < 2; ++w) {
-      A(sizeof(double) * bb, (void**)&I.lbuf[w]);
-      A(nc, (void**)&I.dctr[w]);
-      if (I.two && !(w == 0 && I.qp_kron)) {
-        A(sizeof(double) * bb, (void**)&I.lbufB[w]);
-        A(nc, (void**)&I.dctrB[w]);
-      }
-    }
+  // the one block of log|Q_p| is factored beside the first ones of Q_c, whose
+  // slots take their L tiles
+  if (I.qp_kron) A(ftemp, (void**)&I.Lp);
+  const size_t nc = sizeof(int32_t) * (size_t)dag::counters_per_block(bp / 64);
+  for (int w = 0; w < 2; ++w) {
+    A(nc, (void**)&I.dctr[w]);
+    if (I.two && !(w == 0 && I.qp_kron)) A(nc, (void**)&I.dctrB[w]);
   }
   if (I.two) {
     A(tip, (void**)&I.PcB);
@@ -1775,9 +1672,7 @@ static void ws_flags(dl_ws* W, int32_t flags) {
   W->mixed = (flags & DL_WS_MIXED) != 0;
   W->use_graph = (flags & DL_WS_GRAPH) != 0;
   W->splitk = (flags & DL_WS_SPLITK) != 0;
-  W->fold_inv = (flags & DL_WS_FOLD_INV) != 0;
   W->warm = (flags & DL_WS_WARM_START) != 0;
-  W->dag = (flags & DL_WS_DAG) != 0;
 }
 
 // Bytes of the buffers of each instance and of the workspace-wide ones,
@@ -1849,7 +1744,7 @@ extern "C" dl_status dl_ws_create_batch(const dl_model* const* models,
       if (c && st == DL_OK &&
           hipMemset(c, 0, sizeof(int32_t) * gemv_counters(I)) != hipSuccess)
         st = DL_EHIP;
-    if (W->dag && st == DL_OK) {
+    if (st == DL_OK) {
       const size_t nc = sizeof(int32_t) * (size_t)dag::counters_per_block(I.m.bp / 64);
       for (int w = 0; w < 2 && st == DL_OK; ++w)
         for (int32_t* c : {I.dctr[w], I.dctrB[w]})

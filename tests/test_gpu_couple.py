@@ -31,7 +31,7 @@ def D():
     return dalia
 
 
-def run(ws, wl, D, rhs, set_value):
+def run(ws, wl, D, rhs, two, set_value):
     ws.assemble(wl.theta)
     if set_value:
         ws.set_block(D.DL_QC, 1, 0, ws.get_block(D.DL_QC, 1, 0).clone())
@@ -41,6 +41,8 @@ def run(ws, wl, D, rhs, set_value):
         for kind in (0, 1, 2):
             if (kind == 1 and t == wl.nt - 1) or (kind == 2 and wl.nr == 0):
                 continue
+            if kind == 1 and two and wl.nt >= 4 and t == (wl.nt + 1) // 2:
+                continue  # the root of two chains couples to no later block
             B = ws.get_block(D.DL_QC, kind, t)
             out["%d,%d" % (kind, t)] = torch.tril(B) if kind == 0 else B
     out["var"] = ws.selinv()
@@ -66,8 +68,8 @@ def test_stencil_products_equal_dense_ones(D, nx, nt, nv, nr, two, mixed, family
     ws = D.Workspace(D.Model.from_workload(wl), mixed=mixed, two_sided=two, selinv=True)
     rng = np.random.default_rng(5)
     rhs = torch.tensor(rng.standard_normal((2, wl.N)), device="cuda")
-    a = run(ws, wl, D, rhs, False)
-    b = run(ws, wl, D, rhs, True)
+    a = run(ws, wl, D, rhs, two, False)
+    b = run(ws, wl, D, rhs, two, True)
     for k in a:
         # the arrow rows of a mixed univariate factor are rounded once, not per term
         tol = 2e-5 if mixed else 1e-10
@@ -76,7 +78,7 @@ def test_stencil_products_equal_dense_ones(D, nx, nt, nv, nr, two, mixed, family
         if mixed and nv > 1:
             assert torch.equal(a[k], b[k]) or k in ("var",), k
     # and the assembled plans are back after the next assembly
-    c = run(ws, wl, D, rhs, False)
+    c = run(ws, wl, D, rhs, two, False)
     for k in a:
         assert torch.equal(a[k], c[k]), k
 
