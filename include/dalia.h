@@ -446,8 +446,8 @@ dl_status dl_dpotrf(int64_t n, double* A_dev, int64_t lda, int32_t want_inverse,
  * recorded under HIP graph capture, serving loops with a fixed memory
  * footprint, harnesses that forbid hipMalloc): the same factorisation,
  * outputs and error behaviour as dl_dpotrf, but every temporary (tile
- * inverses, the recursive inversion's products, log-diagonal, reduction
- * partials, launch descriptors) lives in one static device array of
+ * inverses, the inverse's accumulators, log-diagonal, reduction partials,
+ * launch descriptors) lives in one static device array of
  * DL_DPOTRF_NOALLOC_SCRATCH_BYTES that the library holds on each GPU it runs
  * on until the process ends.  No device or host allocation and no stream
  * synchronisation: the results are ready in stream order.  n must be a

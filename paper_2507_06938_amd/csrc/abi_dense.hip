@@ -1,7 +1,6 @@
 // Dense FP64 building blocks exposed through the C ABI for testing: they run
 // the same kernels as the BTA path on caller-provided matrices.  Each call
 // copies its few descriptors to the device and synchronises the stream.
-#include <functional>
 #include <vector>
 
 #include "engine.hpp"
@@ -56,9 +55,11 @@ extern "C" dl_status dl_dgemm(int32_t transa, int32_t transb, int32_t lower,
   return e == hipSuccess ? DL_OK : DL_EHIP;
 }
 
-// Right-looking blocked Cholesky (64-column panels) with the same kernels as
-// the BTA diagonal blocks; with want_inverse the diagonal tiles keep their
-// inverses and a recursive inversion completes L^{-1}.
+// Right-looking blocked Cholesky, a launch per panel of 64 columns (PanelTask),
+// with want_inverse the inverse beside it.  One block is bound by the chain of
+// its tile factors (20 us a panel): 32 tiles take 0.71 ms, where a launch each
+// for the factor, the solve and the update of every panel and the inverse by
+// recursive halving after it took 1.25.
 extern "C" dl_status dl_dpotrf(int64_t n, double* A, int64_t lda,
                                int32_t want_inverse, double* logdet_dev,
                                int64_t* info_dev, void* stream) {
@@ -69,8 +70,9 @@ extern "C" dl_status dl_dpotrf(int64_t n, double* A, int64_t lda,
   const int nbk = (int)(n / 64);
   std::vector<void*> tmp;
   double *Gd = nullptr, *temp = nullptr, *logdiag = nullptr, *part = nullptr;
-  if (dev_alloc(tmp, sizeof(double) * n * 64, (void**)&Gd) != DL_OK ||
-      dev_alloc(tmp, sizeof(double) * n * (nbk / 2 + 1) * 64, (void**)&temp) != DL_OK ||
+  const size_t acc = want_inverse ? (size_t)nbk * (nbk - 1) / 2 : 0;
+  if (dev_alloc(tmp, sizeof(double) * 4096, (void**)&Gd) != DL_OK ||
+      dev_alloc(tmp, sizeof(double) * 4096 * (2 + acc), (void**)&temp) != DL_OK ||
       dev_alloc(tmp, sizeof(double) * n, (void**)&logdiag) != DL_OK ||
       dev_alloc(tmp, sizeof(double) * SUM_BLOCKS, (void**)&part) != DL_OK) {
     free_all(tmp);
@@ -79,92 +81,49 @@ extern "C" dl_status dl_dpotrf(int64_t n, double* A, int64_t lda,
   std::vector<MiscJob> pre(2);
   pre[0].kind = MJ_ZERO_I64; pre[0].dst = (double*)info_dev; pre[0].n = 1;
   pre[1].kind = MJ_ZERO_UPPER_TILES; pre[1].dst = A; pre[1].rows = (int)n; pre[1].ldd = lda;
-  std::vector<PotrfTileArgs> pt(nbk);
-  std::vector<GemmTask> tasks;
-  std::vector<int> t_off, t_cnt, t_tiles;
-  auto push_tasks = [&](std::vector<GemmTask> ts) {
-    const int o = (int)tasks.size();
-    const int tiles = finalize_tasks(ts.data(), (int)ts.size());
-    tasks.insert(tasks.end(), ts.begin(), ts.end());
-    t_off.push_back(o);
-    t_cnt.push_back((int)ts.size());
-    t_tiles.push_back(tiles);
-  };
-  // mode 0 (A <- L, inverse of the tile to Gd) without the inverse; mode 1
-  // (inverse in place) when the full inverse is wanted
-  const int mode = want_inverse ? 1 : 0;
-  for (int j = 0; j < nbk; ++j) {
-    PotrfTileArgs& a = pt[j];
-    a.A = A + (int64_t)j * 64 * (lda + 1);
-    a.lda = lda;
-    a.Ginv = mode == 0 ? Gd + (int64_t)j * 4096 : nullptr;
-    a.logdiag = logdiag + (int64_t)j * 64;
-    a.info = info_dev;
-    a.row0 = (int64_t)j * 64;
-    a.mode = mode;
-    if (j + 1 < nbk) {
-      const int rows = (int)n - (j + 1) * 64;
-      double* panel = A + (int64_t)(j + 1) * 64 + (int64_t)j * 64 * lda;
-      const double* G = mode == 0 ? Gd + (int64_t)j * 4096 : a.A;
-      const int64_t ldg = mode == 0 ? 64 : lda;
-      push_tasks({mk_task(panel, lda, G, ldg, panel, lda, rows, 64, 64,
-                          F_TB | F_BETA0, 1.0, 0.0)});
-      push_tasks({mk_task(panel, lda, panel, lda, A + (int64_t)(j + 1) * 64 * (lda + 1),
-                          lda, rows, rows, 64, F_TB | F_LOWER, -1.0, 1.0)});
-    }
-  }
-  // recursive inversion levels (deepest first)
-  std::vector<std::vector<int>> lv;
-  std::function<void(int, int, int)> rec = [&](int lo, int hi, int d) {
-    if (hi - lo <= 1) return;
-    const int mid = lo + (hi - lo) / 2;
-    if ((int)lv.size() <= d) lv.resize(d + 1);
-    lv[d].push_back(lo);
-    lv[d].push_back(hi);
-    rec(lo, mid, d + 1);
-    rec(mid, hi, d + 1);
-  };
-  const size_t n_fac = t_off.size();
-  if (want_inverse) {
-    rec(0, nbk, 0);
-    for (int d = (int)lv.size() - 1; d >= 0; --d) {
-      std::vector<GemmTask> tT, tG;
-      for (size_t k = 0; k < lv[d].size(); k += 2) {
-        const int lo = lv[d][k], hi = lv[d][k + 1], mid = lo + (hi - lo) / 2;
-        const int n1 = (mid - lo) * 64, n2 = (hi - mid) * 64;
-        double* L21 = A + (int64_t)mid * 64 + (int64_t)lo * 64 * lda;
-        double* G11 = A + (int64_t)lo * 64 * (lda + 1);
-        double* G22 = A + (int64_t)mid * 64 * (lda + 1);
-        double* T = temp + (int64_t)lo * 64;
-        tT.push_back(mk_task(L21, lda, G11, lda, T, n, n2, n1, n1, F_KLO_COL | F_BETA0, 1.0, 0.0));
-        tG.push_back(mk_task(G22, lda, T, n, L21, lda, n2, n1, n2, F_KHI_ROW | F_BETA0, -1.0, 0.0));
-      }
-      push_tasks(tT);
-      push_tasks(tG);
-    }
+  const bool inv = want_inverse != 0;
+  // tile 0 (mode 0: A <- L, its inverse to Gd; mode 1: inverse in place) and the
+  // panel below it, then the panel steps
+  std::vector<PotrfTileArgs> pt(1);
+  PotrfTileArgs& a = pt[0];
+  a.A = A;
+  a.lda = lda;
+  a.Ginv = inv ? nullptr : Gd;
+  a.logdiag = logdiag;
+  a.info = info_dev;
+  a.row0 = 0;
+  a.mode = inv ? 1 : 0;
+  std::vector<GemmTask> solve;
+  std::vector<PanelTask> steps(nbk);
+  std::vector<int> grid(nbk);
+  int units = 0, nsteps = 0;
+  std::vector<MiscJob> post;
+  if (nbk > 1) {
+    solve.push_back(mk_task(A + 64, lda, inv ? A : Gd, inv ? lda : 64, A + 64, lda, (int)n - 64,
+                            64, 64, F_TB | F_BETA0, 1.0, 0.0));
+    units = finalize_tasks(solve.data(), 1);
+    nsteps = panel_steps(n, A, lda, inv, logdiag, info_dev, temp, steps.data(), grid.data());
+    if (inv) post.push_back(last_inverse_tile(n, A, lda, temp));
   }
   std::vector<SumJob> sj(1);
   sj[0].src = logdiag; sj[0].n = n; sj[0].scale = 2.0; sj[0].dst = logdet_dev; sj[0].partial = part;
-  MiscJob* dpre = nullptr;
+  MiscJob *dpre = nullptr, *dpost = nullptr;
   PotrfTileArgs* dpt = nullptr;
   GemmTask* dt = nullptr;
+  PanelTask* dst = nullptr;
   SumJob* dsj = nullptr;
   hipError_t e = to_dev(tmp, pre, &dpre, s);
   if (e == hipSuccess) e = to_dev(tmp, pt, &dpt, s);
-  if (e == hipSuccess) e = to_dev(tmp, tasks, &dt, s);
+  if (e == hipSuccess) e = to_dev(tmp, solve, &dt, s);
+  if (e == hipSuccess) e = to_dev(tmp, steps, &dst, s);
+  if (e == hipSuccess) e = to_dev(tmp, post, &dpost, s);
   if (e == hipSuccess) e = to_dev(tmp, sj, &dsj, s);
   if (e == hipSuccess) e = launch_misc(dpre, 2, s);
-  for (int j = 0; j < nbk && e == hipSuccess; ++j) {
-    e = launch_potrf_tiles(dpt + j, 1, s);
-    if (e == hipSuccess && j + 1 < nbk) {
-      for (int k = 0; k < 2 && e == hipSuccess; ++k) {
-        const size_t i = 2 * j + k;
-        e = launch_gemm_tasks(dt + t_off[i], t_cnt[i], t_tiles[i], s);
-      }
-    }
-  }
-  for (size_t i = n_fac; i < t_off.size() && e == hipSuccess; ++i)
-    e = launch_gemm_tasks(dt + t_off[i], t_cnt[i], t_tiles[i], s);
+  if (e == hipSuccess) e = launch_potrf_tiles(dpt, 1, s);
+  if (e == hipSuccess) e = launch_gemm_tasks(dt, (int)solve.size(), units, s);
+  for (int j = 0; j < nsteps && e == hipSuccess; ++j)
+    e = launch_panel_updates(dst + j, 1, grid[j], s);
+  if (e == hipSuccess && !post.empty()) e = launch_misc(dpost, 1, s);
   if (e == hipSuccess) e = launch_sums(dsj, 1, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   free_all(tmp);

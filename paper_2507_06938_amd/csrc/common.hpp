@@ -186,12 +186,19 @@ struct PanelTask {
   double* stage;       // tile (r, c), c < r: ((r (r-1)) / 2 + c) * 4096 (ld 64)
   int32_t j, nbk;
   int32_t last;
-  int32_t inv;         // 0: no inverse workgroups (the recursive inverse follows)
+  int32_t inv;         // 0: no inverse; the diagonal tiles then hold L, not G
   int32_t beg[5];      // first workgroup of this task in each role segment
   int32_t tot[5];      // workgroups of each role in the launch (every task)
 };
 // Fill beg/tot; return the grid size.
 int finalize_panels(PanelTask* t, int n);
+// The panel steps of one n x n block (nbk = n / 64 >= 2 tiles; tile 0 factored
+// and panel 0 solved before the first): nbk - 1 of them, and with the inverse
+// the closing one, after which tile (nbk-1, nbk-2) of G is still to be copied
+// from `stage`.  tmp: the side ring and the inverse's accumulators, 2 + nbk (nbk -
+// 1) / 2 tiles.  Fills t[j] and its grid; returns the number of launches.
+int panel_steps(int64_t n, double* A, int64_t lda, bool inv, double* logdiag, int64_t* info,
+                double* tmp, PanelTask* t, int* grid);
 hipError_t launch_panel_updates(const PanelTask* tasks_dev, int ntask, int grid,
                                 hipStream_t s);
 

@@ -525,7 +525,7 @@ __global__ __launch_bounds__(POTRF_NT) void k_panel_update(const PanelTask* __re
   __syncthreads();
   const bool own = role == 0;
   potrf_body(nullptr, 0, S1, S2, own ? dst : nullptr, side ? NB : T.ld, nullptr,
-             own ? T.logdiag : nullptr, own ? T.info : nullptr, T.row0, 1);
+             own ? T.logdiag : nullptr, own ? T.info : nullptr, T.row0, own && !T.inv ? 0 : 1);
   if (own) return;
   // G staged as S1[k][r] = G(r, k) (zero above the diagonal); the updated
   // panel tile as S0[c][m] = A(m, c)
@@ -569,6 +569,28 @@ int finalize_panels(PanelTask* t, int n) {
   for (int i = 0; i < n; ++i)
     for (int k = 0; k < 5; ++k) t[i].tot[k] = tot[k];
   return grid;
+}
+
+int panel_steps(int64_t n, double* A, int64_t lda, bool inv, double* logdiag, int64_t* info,
+                double* tmp, PanelTask* t, int* grid) {
+  const int nbk = (int)(n / NB), steps = inv ? nbk : nbk - 1;
+  for (int j = 0; j < steps; ++j) {
+    PanelTask& p = t[j];
+    p = PanelTask{};
+    p.A = A;
+    p.ld = lda;
+    p.logdiag = logdiag + (int64_t)(j + 1) * NB;
+    p.info = info;
+    p.row0 = (int64_t)(j + 1) * NB;
+    p.gside = tmp;
+    p.stage = tmp + 2 * NB * NB;
+    p.j = j;
+    p.nbk = nbk;
+    p.last = j + 1 == nbk;
+    p.inv = inv;
+    grid[j] = finalize_panels(&p, 1);
+  }
+  return steps;
 }
 
 hipError_t launch_panel_updates(const PanelTask* tasks, int ntask, int grid,

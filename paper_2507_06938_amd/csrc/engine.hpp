@@ -38,6 +38,18 @@ inline dl_status upload(std::vector<void*>& list, const std::vector<T>& h,
   return DL_OK;
 }
 
+// The copy that puts G(nbk-1, nbk-2) into place after the closing panel step.
+inline MiscJob last_inverse_tile(int64_t n, double* A, int64_t lda, const double* tmp) {
+  const int64_t nbk = n / 64;
+  MiscJob J{};
+  J.kind = MJ_COPY2D;
+  J.rows = J.cols = 64;
+  J.dst = A + (nbk - 1) * 64 + (nbk - 2) * 64 * lda;
+  J.ldd = lda;
+  J.src = tmp + (2 + (nbk - 1) * (nbk - 2) / 2 + (nbk - 2)) * 4096;
+  J.lds = 64;
+  return J;
+}
 
 inline void free_all(std::vector<void*>& list) {
   for (void* p : list) (void)hipFree(p);

@@ -1,0 +1,57 @@
+"""dl_dpotrf and dl_dpotrf_noalloc at the edges of their panel steps: one tile, the
+first two and three (the closing step right after the first), a size above a
+descriptor chunk and the largest, with the inverse and without, in a matrix with
+a larger leading dimension whose other rows stay untouched.  The tolerance is
+that of a backward-stable factorisation, c n eps cond(A), with cond = 1e3."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def D():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2507_06938_amd import dalia
+    dalia.lib()
+    return dalia
+
+
+@pytest.mark.parametrize("n", [64, 128, 192, 512, 1600, 2048])
+@pytest.mark.parametrize("inverse", [0, 1])
+@pytest.mark.parametrize("entry", ["dl_dpotrf", "dl_dpotrf_noalloc"])
+def test_panel_steps(D, entry, inverse, n):
+    g = torch.Generator(device="cpu").manual_seed(n)
+    Q, _ = torch.linalg.qr(torch.randn(n, n, generator=g, dtype=torch.float64))
+    d = torch.logspace(-1.5, 1.5, n, dtype=torch.float64)
+    S = (Q * d) @ Q.T
+    S = 0.5 * (S + S.T)
+    lda = n + 5
+    A = torch.full((n, lda), 7.0, dtype=torch.float64)
+    A[:, :n] = S  # column-major: row c of the tensor is column c
+    A = A.cuda()
+    ld = torch.zeros(1, dtype=torch.float64, device="cuda")
+    info = torch.full((1,), 5, dtype=torch.int64, device="cuda")
+    args = (n, D._ptr(A), lda, inverse, D._ptr(ld), D._ptr(info), D._stream())
+    for _ in range(2):  # the second call finds the first one's scratch contents
+        A[:, :n] = S.cuda()
+        assert getattr(D.lib(), entry)(*args) == 0
+    torch.cuda.synchronize()
+    assert int(info[0]) == 0
+    X = A[:, :n].T.cpu()
+    assert torch.all(A[:, n:] == 7.0)
+    assert torch.all(torch.triu(X, 1) == 0)
+    L = torch.linalg.cholesky(S)
+    want = torch.linalg.inv(L) if inverse else L
+    tol = 4 * n * np.finfo(float).eps * 1e3
+    assert (X - want).abs().max() <= tol * want.abs().max()
+    assert abs(ld.item() - 2 * torch.log(torch.diagonal(L)).sum().item()) <= tol * n
+    # a pivot that fails in the last panel is reported at its row
+    bad = S.clone()
+    bad[n - 3, n - 3] = -1.0
+    A[:, :n] = bad.cuda()
+    assert getattr(D.lib(), entry)(*args) == 0
+    torch.cuda.synchronize()
+    assert int(info[0]) == n - 2
