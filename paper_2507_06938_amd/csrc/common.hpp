@@ -28,7 +28,10 @@ namespace dl {
 //   F_KLO_COL : k >= first column of the C tile; F_KHI_COL : k < last col+1;
 //   F_KLO_ROW : k >= first row of the C tile;    F_KHI_ROW : k < last row+1;
 //   F_BAND_ROW: op(A) is a banded coupling product (see Band): k >= its
-//               rows' first column;  F_BAND_COL: the same for op(B)'s columns.
+//               rows' first column;  F_BAND_COL: the same for op(B)'s columns;
+//   F_KTAIL   : B is such a [C; R] itself, K its rows, of one response: the rows
+//               of C that begin after the C tile's columns are passed over
+//               (the arrow rows, from band.end on, are not).
 enum : int {
   F_TA = 1,
   F_TB = 2,
@@ -51,6 +54,8 @@ enum : int {
   F_KVAR = 4096,
   F_BAND_ROW = 8192,
   F_BAND_COL = 16384,
+  F_KTAIL = 32768,
+  F_HALF_I = 65536,  // C = tril(I + alpha A B) with half its diagonal
 };
 
 // First nonzero column of the rows of [C_t; R_t], C_t = B_t G_t^T: row

@@ -73,7 +73,7 @@ struct Launch {
 
 // Default GEMM tile for a launch (before any measured choice): 128x128 when
 // every task is large and the launch still has >= 200 such tiles to spread
-// over the 256 compute units, else 64x64.
+// over the 256 compute units (1024 when their k ranges differ), else 64x64.
 static int default_tile(std::vector<GemmTask>& t, int off, int count) {
   bool big = true;
   for (int i = 0; i < count; ++i) {
@@ -82,7 +82,10 @@ static int default_tile(std::vector<GemmTask>& t, int off, int count) {
   }
   if (!big) return 64;
   const int n128 = finalize_tasks(t.data() + off, count, 128);
-  return n128 >= 200 ? 128 : 64;
+  // tiles of different k lengths: the longest 128-tile alone would take as long as
+  // the whole launch unless there are many (f_obj with variances, 45 x 45 nodes, 20
+  // steps: 22.8 ms against 27.2 with 200)
+  return n128 >= ((t[off].flags & F_KVAR) ? 1024 : 200) ? 128 : 64;
 }
 
 struct Plan {
@@ -393,6 +396,10 @@ struct Inst {
   double *f = nullptr, *parts = nullptr;
   int64_t* info_out = nullptr;
   // selected inversion
+  // sel_s: by the symmetric form (see seq_selinv), with S's lower half and its
+  // product per chain in place of every step's [W; V]
+  bool sel_s = false;
+  double *SU = nullptr, *SUB = nullptr, *ST = nullptr, *STB = nullptr;
   double *WV = nullptr, *Y = nullptr, *XC[2] = {nullptr, nullptr}, *selout = nullptr;
   double* GPp = nullptr;
   bool mixed = false;       // [B_t; R_t] in FP32, their products on FP32 MFMA
@@ -1135,6 +1142,91 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q, int n
   }
 }
 
+// The steps of seq_selinv in the form
+//   X_tt = G_t^T (I + [C_t; R_t]^T Z_t) G_t,  Z_t = X(s) [C_t; R_t],
+//   X_{P,t} = -Z_P,t G_t,
+// which keeps the triangles that [W_t; V_t] = [C_t; R_t] G_t fills in.  With one
+// response C_t begins `band` columns before the diagonal in every row, so that,
+// in units of b^3, Z takes 1 and the lower half of S = I + [C; R]^T Z 1/3; with U
+// the lower half of S and half its diagonal, X = M + M^T, M = G^T (U G), takes
+// 1/3 and 2/3: 7/3 where W, X W, G^T G and W^T X W took 4.  (With more responses
+// C fills up and the form saves nothing.)  The sums it forms are of the same
+// size, and its variances' error against 64 bits is the factor's either way.
+static void seq_selinv_s(dl_ws* W, Inst& I, std::vector<Step>& q) {
+  const ModelDev& m = I.m;
+  const int bp = m.bp, ap = m.ap;
+  const int64_t ld = I.ldbr;
+  const double b = m.b, a = m.a;
+  const int xf = W->splitk ? F_SPLIT : 0;
+  const int tail = W->dense ? 0 : F_KTAIL;
+  double* XCc[2][2] = {{I.XC[0], I.XC[1]}, {I.XCB[0], I.XCB[1]}};
+  double* Zc[2] = {I.Y, I.YB};
+  double* Uc[2] = {I.SU, I.SUB};
+  double* Tc[2] = {I.ST, I.STB};
+  auto step = [&](int t, uint64_t mj, const double* Xin, double* Xout, int c, bool root) {
+    const double* CR = I.BRc + (int64_t)I.slot_final[t] * ld * bp;
+    const double* G = I.Dc + (int64_t)t * bp * bp;
+    double *Z = Zc[c], *U = Uc[c], *T = Tc[c];
+    // the root has arrow rows only
+    const int r0 = root ? bp : 0, k = root ? ap : bp + ap;
+    const double b2 = b * b, b3 = b2 * b;
+    GemmTask z = mk(Xin + r0 + r0 * ld, ld, CR + r0, ld, Z + r0, ld, k, bp, k, F_BETA0 | xf, 1.0,
+                    0.0);
+    GemmTask u = mk(Z + r0, ld, CR + r0, ld, U, bp, bp, bp, k,
+                    F_TA | F_LOWER | F_HALF_I | F_BETA0 | xf, 1.0, 0.0);
+    if (!root && tail) {
+      z.flags = (z.flags & ~F_SPLIT) | tail;
+      u.flags = (u.flags & ~F_SPLIT) | tail;
+      z.band = u.band = coupling_band(I);
+    }
+    if (k > 0)
+      q.push_back(gemm_step(K(mj, 2, 0), DL_CAT_SELINV,
+                            root ? 2.0 * a * a * b : (b + a) * b2 + 2.0 * (b + a) * a * b, {z}));
+    q.push_back(gemm_step(K(mj, 2, 1), DL_CAT_SELINV,
+                          root ? a * b2 : b3 / 3.0 + a * b2, {u}));
+    std::vector<GemmTask> ug;
+    if (ap > 0)
+      ug.push_back(mk(Z + bp, ld, G, bp, T + bp, ld, ap, bp, bp, F_KLO_COL | F_BETA0 | xf, -1.0,
+                      0.0));
+    ug.push_back(mk(U, bp, G, bp, T, ld, bp, bp, bp,
+                    F_LOWER | F_KLO_COL | F_KHI_ROW | F_BETA0 | xf, 1.0, 0.0));
+    q.push_back(gemm_step(K(mj, 2, 2), DL_CAT_SELINV, b3 / 3.0 + a * b2, std::move(ug)));
+    q.push_back(gemm_step(K(mj, 2, 3), DL_CAT_SELINV, 2.0 * b3 / 3.0,
+                          {mk(G, bp, T, ld, Xout, ld, bp, bp, bp,
+                              F_TA | F_KLO_ROW | F_KLO_COL | F_BETA0 | xf, 1.0, 0.0)}));
+    Step fin;
+    fin.key = K(mj, 5);
+    fin.kind = OP_FINISH;
+    fin.cat = DL_CAT_SELINV;
+    fin.fin.XC = Xout;
+    fin.fin.ld = ld;
+    fin.fin.bp = bp;
+    fin.fin.ap = ap;
+    fin.fin.Y = T;
+    fin.fin.out = I.selout + (int64_t)t * bp;
+    fin.fin.sum = 1;
+    fin.gx = bp;
+    q.push_back(fin);
+  };
+  const int n = m.nt, mid = I.mid;
+  const int lenA = mid, lenB = n - 1 - mid;
+  step(mid, 1, XCc[0][0], XCc[0][1], 0, true);
+  int cur[2] = {1, -1};  // chain B reads the root's buffer first
+  for (int k = 0; k < std::max(lenA, lenB); ++k) {
+    const uint64_t mj = 2 + (uint64_t)k;
+    if (k < lenA) {
+      step(mid - 1 - k, mj, XCc[0][cur[0]], XCc[0][cur[0] ^ 1], 0, false);
+      cur[0] ^= 1;
+    }
+    if (k < lenB) {
+      const double* in = (k == 0) ? XCc[0][1] : XCc[1][cur[1]];
+      const int out = (k == 0) ? 0 : (cur[1] ^ 1);
+      step(mid + 1 + k, mj, in, XCc[1][out], 1, false);
+      cur[1] = out;
+    }
+  }
+}
+
 // Takahashi selected inversion of Q_c from the factor's off-diagonal blocks
 // and the diagonal-block inverses G_t, in the reverse of the elimination
 // order: the root block first, then each chain outward.  Block t needs the
@@ -1169,7 +1261,7 @@ static void seq_selinv(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
   double* Yc[2] = {I.Y, I.YB};
   // [W_t; V_t] of every step, eb bytes per element, ld x bp each
   auto WVt = [&](int t) { return eoff(I.WV, (int64_t)t * ld * bp, eb); };
-  for (int c = 0; c < nch; ++c)
+  for (int c = 0; c < nch && !I.sel_s; ++c)  // (whose steps write all they read)
     for (int k = 0; k < 2; ++k)
       q.push_back(misc_step(K(0, 0, 0, 2 * c + k), DL_CAT_SELINV, MJ_FILL, XCc[c][k],
                             nullptr, ld * ld, 0.0));
@@ -1186,6 +1278,10 @@ static void seq_selinv(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
                         ap);
     dg.misc.lds = ld;
     q.push_back(dg);
+  }
+  if (I.sel_s) {
+    seq_selinv_s(W, I, q);
+    return;
   }
   // [W_t; V_t] = [C_t; R_t]_factor G_t for all t: independent of the
   // recursion, so one launch (the root has only the arrow rows; its W block
@@ -1535,6 +1631,14 @@ static void ws_free(dl_ws* W) {
   delete W;
 }
 
+// Smallest padded block size of the selected inversion's symmetric form: it has
+// two launches more a step, and below this size those cost more than the
+// products it saves (f_obj with variances, 12 steps: 24 x 24 nodes 4.25 ms against
+// 3.60, 30 x 30 6.65 / 6.04, 34 x 34 with two chains 6.05 / 5.95; but 9 points of
+// 30 x 30 15.1 / 17.6, and 45 x 45, 20 steps, 22.8 / 27.4).  By the block size
+// alone, so that an evaluation does not depend on the batch it is part of.
+constexpr int SELINV_S_MIN = 1280;
+
 // Storage layout of instance I (host fields only) for the workspace flags.
 static void inst_layout(const dl_ws* W, Inst& I, const dl_model* model, bool two_sided) {
   I.model = model;
@@ -1555,6 +1659,7 @@ static void inst_layout(const dl_ws* W, Inst& I, const dl_model* model, bool two
   I.two = two_sided && m.nt >= 4;
   I.mid = I.two ? (m.nt + 1) / 2 : m.nt - 1;
   I.poisson = W->poisson;
+  I.sel_s = !I.mixed && m.nv == 1 && m.bp >= SELINV_S_MIN;
 }
 
 // One counter per 128 rows of the largest matrix-vector product.
@@ -1634,8 +1739,17 @@ static void inst_buffers(const dl_ws* W, Inst& I, Alloc&& A) {
     A(sizeof(double) * SOLVE_RHS * (ap > 0 ? ap : 1), (void**)&I.xPB);
   }
   if (W->sel) {
-    // [W_t; V_t] = [B_t; R_t] G_t of every time step (formed up front)
-    A((size_t)I.eb * m.nt * I.ldbr * bp, (void**)&I.WV);
+    if (I.sel_s) {
+      A(sizeof(double) * bb, (void**)&I.SU);
+      A(sizeof(double) * I.ldbr * bp, (void**)&I.ST);
+      if (I.two) {
+        A(sizeof(double) * bb, (void**)&I.SUB);
+        A(sizeof(double) * I.ldbr * bp, (void**)&I.STB);
+      }
+    } else {
+      // [W_t; V_t] = [B_t; R_t] G_t of every time step (formed up front)
+      A((size_t)I.eb * m.nt * I.ldbr * bp, (void**)&I.WV);
+    }
     A(sizeof(double) * I.ldbr * bp, (void**)&I.Y);
     A(sizeof(double) * I.ldbr * I.ldbr, (void**)&I.XC[0]);
     A(sizeof(double) * I.ldbr * I.ldbr, (void**)&I.XC[1]);
@@ -1740,6 +1854,12 @@ extern "C" dl_status dl_ws_create_batch(const dl_model* const* models,
       st = DL_EHIP;
     if (st == DL_OK && hipMemset(I.xm, 0, sizeof(double) * SOLVE_RHS * I.m.Np) != hipSuccess)
       st = DL_EHIP;
+    // above their diagonals these stay zero
+    for (double* p : {I.SU, I.SUB, I.ST, I.STB})
+      if (p && st == DL_OK &&
+          hipMemset(p, 0, sizeof(double) * I.m.bp *
+                              (size_t)(p == I.ST || p == I.STB ? I.ldbr : I.m.bp)) != hipSuccess)
+        st = DL_EHIP;
     for (int32_t* c : {I.gcnt, I.gcntB})
       if (c && st == DL_OK &&
           hipMemset(c, 0, sizeof(int32_t) * gemv_counters(I)) != hipSuccess)

@@ -117,13 +117,18 @@ struct VStage {
   const double* base;  // operand origin (the safe address of invalid slots)
   const double* p;     // slot 0 of the current chunk
   int64_t step, adv;
+  int64_t jump;        // from chunk `khop` to `kland` of the operand
+  int khop, kland;
   int rl, kq;          // tile-relative row, chunk-relative k of slot 0
   int kc, kend;        // current chunk's first k, k limit
   bool trans;
   unsigned rowok;      // bit j: slot j's row(s) inside the operand
 
   __device__ __forceinline__ void init(const double* X, int64_t ldx, bool tr, int r0, int R,
-                                       int k0, int ke, int tid) {
+                                       int k0, int ke, int tid, int hop, int land) {
+    khop = hop;
+    kland = land;
+    jump = (int64_t)(land - hop) * (tr ? 1 : ldx);
     base = X;
     trans = tr;
     kc = k0;
@@ -162,6 +167,10 @@ struct VStage {
   __device__ __forceinline__ void next() {
     p += adv;
     kc += BK;
+    if (kc == khop) {
+      p += jump;
+      kc = kland;
+    }
   }
 
   __device__ __forceinline__ void store(double* __restrict__ S, const v2d (&v)[PV]) const {
@@ -204,13 +213,13 @@ __device__ __forceinline__ void tile_k_range(const GemmTask& T, int m0, int n0, 
 __device__ __forceinline__ void tile_coords(const GemmTask& T, int lt, int& tm,
                                             int& tn) {
   constexpr int KCOL = F_KLO_COL | F_KHI_COL, KROW = F_KLO_ROW | F_KHI_ROW;
-  if (!(T.flags & F_LOWER) && (T.flags & (KCOL | KROW))) {
+  if (!(T.flags & F_LOWER) && (T.flags & (KCOL | KROW | F_KTAIL))) {
     // k range set by the tile column (or row): whole columns (rows) in
     // order of decreasing length
-    if (T.flags & KCOL) {
+    if (T.flags & (KCOL | F_KTAIL)) {
       const int c = lt / T.tiles_m;
       tm = lt - c * T.tiles_m;
-      tn = (T.flags & F_KHI_COL) ? T.tiles_n - 1 - c : c;
+      tn = (T.flags & (F_KHI_COL | F_KTAIL)) ? T.tiles_n - 1 - c : c;
     } else {
       const int r = lt / T.tiles_n;
       tn = lt - r * T.tiles_n;
@@ -218,8 +227,18 @@ __device__ __forceinline__ void tile_coords(const GemmTask& T, int lt, int& tm,
     }
     return;
   }
+  if ((T.flags & F_LOWER) && (T.flags & F_KLO_COL) && (T.flags & F_KHI_ROW)) {
+    // as long as the tile is far from the diagonal: the farthest first
+    int d = (int)((sqrt(8.0 * (double)lt + 1.0) - 1.0) * 0.5);
+    while (d * (d + 1) / 2 > lt) --d;
+    while ((d + 1) * (d + 2) / 2 <= lt) ++d;
+    tn = lt - d * (d + 1) / 2;
+    tm = tn + T.tiles_m - 1 - d;
+    return;
+  }
   if (T.flags & F_LOWER) {
     const int nt = T.tiles_m;  // square tile grid
+    if (T.flags & F_KTAIL) lt = T.ntiles - 1 - lt;  // the last columns first
     int g = (int)((sqrt(8.0 * (double)lt + 1.0) - 1.0) * 0.5) / GROUP;
     while (g > 0 && (g * GROUP) * (g * GROUP + 1) / 2 > lt) --g;
     while (((g + 1) * GROUP) * ((g + 1) * GROUP + 1) / 2 <= lt) ++g;
@@ -363,7 +382,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
   } else if (sl > 0) {
     return;
   }
-  const int nchunks = ke > kb ? (ke - kb + BK - 1) / BK : 0;
+  int nchunks = ke > kb ? (ke - kb + BK - 1) / BK : 0;
 
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -380,8 +399,16 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
   const bool vec_b = vec_operand(T.B, T.ldb, !tb, T.N, kb, ke);
   if (vec_a && vec_b) {
     VStage<BT, NT> sa, sb;
-    sa.init(T.A, T.lda, ta, m0, T.M, kb, ke, tid);
-    sb.init(T.B, T.ldb, !tb, n0, T.N, kb, ke, tid);
+    int hop = -1, land = 0;
+    if ((T.flags & F_KTAIL) && T.kslices == 1) {
+      const int last = n0 + min(BT, T.N - n0) + T.band.reach;  // rows of C up to here
+      hop = (last + BK - 1) / BK * BK;
+      land = T.band.end;
+      if (hop >= land) hop = -1;
+      else nchunks -= (land - hop) / BK;
+    }
+    sa.init(T.A, T.lda, ta, m0, T.M, kb, ke, tid, hop, land);
+    sb.init(T.B, T.ldb, !tb, n0, T.N, kb, ke, tid, hop, land);
     constexpr int PV = VStage<BT, NT>::PV;
     v2d a0[PV], b0[PV];
     sa.load(a0); sb.load(b0); sa.next(); sb.next();
@@ -453,6 +480,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
   }
   // epilogue: lane holds C[m][n0' + lk + 4r], m = row of lane
   const bool lower = T.flags & F_LOWER;
+  const bool half = T.flags & F_HALF_I;
   const bool beta0 = T.flags & F_BETA0;
 #pragma unroll
   for (int i = 0; i < FM; ++i) {
@@ -467,6 +495,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
         double* p = T.C + (int64_t)m + (int64_t)n * T.ldc;
         double v = T.alpha * acc[i][j][r];
         if (!beta0) v += T.beta * (*p);
+        if (half && n == m) v = 0.5 + 0.5 * v;
         *p = v;
       }
     }
@@ -501,6 +530,7 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(const GemmTask* __restrict_
     double* c = T.C + (int64_t)m + (int64_t)n * T.ldc;
     double v = T.alpha * sum;
     if (!beta0) v += T.beta * (*c);
+    if ((T.flags & F_HALF_I) && n == m) v = 0.5 + 0.5 * v;
     *c = v;
   }
 }
@@ -511,7 +541,7 @@ int finalize_tasks(GemmTask* t, int n, int tile, int* nred, int64_t* nslots) {
   bool kvar = false;
   for (int i = 0; i < n; ++i)
     kvar = kvar || (t[i].flags & (F_KLO_COL | F_KHI_COL | F_KLO_ROW | F_KHI_ROW |
-                                F_BAND_ROW | F_BAND_COL));
+                                F_BAND_ROW | F_BAND_COL | F_KTAIL));
   for (int i = 0; i < n; ++i) {
     t[i].flags = kvar ? (t[i].flags | F_KVAR) : (t[i].flags & ~F_KVAR);
     t[i].tiles_m = (t[i].M + tile - 1) / tile;

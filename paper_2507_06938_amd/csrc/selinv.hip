@@ -27,6 +27,25 @@ __global__ __launch_bounds__(256) void k_selinv_finish(const FinishJob* __restri
       tile[r][c] = XC[(int64_t)(r0 + r) + (int64_t)(c0 + c) * ld];
     }
     __syncthreads();
+    if (F.sum) {
+      // both tiles of the pair hold M: add the upper one's transpose
+      for (int idx = tid; idx < 64 * 64; idx += 256) {
+        const int c = idx & 63, r = idx >> 6;  // element (c0 + c, r0 + r)
+        if (I == J && c > r) continue;
+        double* up = &XC[(int64_t)(c0 + c) + (int64_t)(r0 + r) * ld];
+        const double x = tile[r][c] + (I == J ? tile[c][r] : *up);
+        tile[r][c] = x;
+        if (I == J && c == r) F.out[c0 + c] = x;
+        *up = x;
+      }
+      __syncthreads();
+      for (int idx = tid; idx < 64 * 64; idx += 256) {
+        const int r = idx & 63, c = idx >> 6;
+        if (I == J && c > r) continue;
+        XC[(int64_t)(r0 + r) + (int64_t)(c0 + c) * ld] = tile[r][c];
+      }
+      return;
+    }
     // upper tile (J, I): element (c0 + c, r0 + r) = lower (r0 + r, c0 + c)
     for (int idx = tid; idx < 64 * 64; idx += 256) {
       const int c = idx & 63, r = idx >> 6;  // row c0+c of the upper tile
@@ -45,7 +64,7 @@ __global__ __launch_bounds__(256) void k_selinv_finish(const FinishJob* __restri
     XC[(int64_t)(bp + i) + (int64_t)c * ld] = v;
     XC[(int64_t)c + (int64_t)(bp + i) * ld] = v;
   }
-  if (tid < 64) F.out[c0 + tid] = XC[(int64_t)(c0 + tid) * (ld + 1)];
+  if (tid < 64 && !F.sum) F.out[c0 + tid] = XC[(int64_t)(c0 + tid) * (ld + 1)];
 }
 
 hipError_t launch_selinv_finish(const FinishJob* jobs, int count, int max_bp,
