@@ -2,6 +2,8 @@
 // right-hand side A^T D y, quadratic forms and the f_obj combination.
 #include <math.h>
 
+#include <algorithm>
+
 #include "model.hpp"
 
 namespace dl {
@@ -22,139 +24,134 @@ namespace dl {
 // M2 = 1 | 2 | 1 on the diagonal (end | inside | end), -1 off it.  Either
 // way Q^i's diagonal and sub-diagonal blocks are weighted sums of the four
 // FEM pieces; wd/wb below hold those weights per process.
-__global__ void k_theta_coeffs(const ThetaJob* __restrict__ jobs) {
-  if (threadIdx.x != 0) return;
+//
+// One wave: a lane per process for its parameters and weights, a lane per
+// hyperparameter for the prior, then the tables by all lanes (by one lane, a
+// trivariate model took 88 us, now 16).
+__global__ __launch_bounds__(64) void k_theta_coeffs(const ThetaJob* __restrict__ jobs) {
   const ThetaJob J = jobs[blockIdx.x];
   const ModelDev& m = *J.m;
   const double* __restrict__ theta = J.theta;
   double* __restrict__ coef = J.coef;
-  const int nv = m.nv;
-  double kap[3], rho[3], tau[3], Li[3][3];
-  double Mw[3][3][3];
-  int bad = 0;
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) {
-      Li[i][j] = 0.0;
-      for (int k = 0; k < 3; ++k) Mw[i][j][k] = 0.0;
-    }
-  // Poisson responses have no noise precision in theta (tau = 1, unused)
-  const bool gauss = m.likelihood == DL_LIK_GAUSSIAN;
-  if (nv == 1) {
-    kap[0] = exp(theta[0]);
-    rho[0] = tanh(0.5 * theta[1]);
-    const double tau_u = exp(theta[2]);
-    tau[0] = gauss ? exp(theta[3]) : 1.0;
-    Mw[0][0][0] = tau_u;
-  } else {
-    const int nl = nv * (nv - 1) / 2;
-    double sg[3], lam[3] = {0.0, 0.0, 0.0};
-    for (int i = 0; i < nv; ++i) {
-      kap[i] = exp(theta[i]);
-      rho[i] = tanh(0.5 * theta[nv + i]);
-      sg[i] = exp(theta[2 * nv + i]);
-      tau[i] = gauss ? exp(theta[3 * nv + nl + i]) : 1.0;
-    }
-    for (int k = 0; k < nl; ++k) lam[k] = theta[3 * nv + k];
-    // Lambda of Eq. 5 (nv = 2 keeps its leading 2x2 block)
-    double L[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-    L[0][0] = sg[0];
-    L[1][0] = lam[0] * sg[0];
-    L[1][1] = sg[1];
-    if (nv == 3) {
-      L[2][0] = (lam[2] + lam[0] * lam[1]) * sg[0];
-      L[2][1] = lam[1] * sg[1];
-      L[2][2] = sg[2];
-    }
-    // inverse of the lower-triangular Lambda, column by column
-    for (int c = 0; c < nv; ++c) {
-      for (int r = 0; r < nv; ++r) {
-        if (r < c) { Li[r][c] = 0.0; continue; }
-        double acc = (r == c) ? 1.0 : 0.0;
-        for (int k = c; k < r; ++k) acc -= L[r][k] * Li[k][c];
-        Li[r][c] = acc / L[r][r];
-      }
-    }
-    for (int i = 0; i < nv; ++i)
-      for (int j = 0; j < nv; ++j)
-        for (int k = 0; k < nv; ++k) Mw[i][j][k] = Li[i][j] * Li[i][k];
-  }
+  const int nv = m.nv, lane = threadIdx.x;
+  __shared__ double tau[3], sg[3], Mw[3][3][3];
   // wd[i][tt][c]: weight of FEM piece c in a diagonal block of Q^i (tt = 0
   // end step, 1 inside, 2 single step); wb[i][c]: sub-diagonal block
-  double wd[3][3][NPIECE], wb[3][NPIECE];
-  for (int i = 0; i < 3; ++i)
+  __shared__ double wd[3][3][NPIECE], wb[3][NPIECE], logden[3], prior[64], llc[3];
+  __shared__ int bad;
+  if (lane == 0) bad = 0;
+  __syncthreads();
+  // Poisson responses have no noise precision in theta (tau = 1, unused)
+  const bool gauss = m.likelihood == DL_LIK_GAUSSIAN;
+  const bool diffusion = m.family == DL_MODEL_DIFFUSION;
+  const int nl = nv * (nv - 1) / 2;
+  const double two_pi = 6.283185307179586476925286766559;
+  if (lane < 3) {
+    const int i = lane;
+    logden[i] = 0.0;
+    llc[i] = 0.0;
     for (int c = 0; c < NPIECE; ++c) {
       wb[i][c] = 0.0;
       for (int tt = 0; tt < 3; ++tt) wd[i][tt][c] = 0.0;
     }
-  const bool diffusion = m.family == DL_MODEL_DIFFUSION;
-  double logt = 0.0;
-  for (int i = 0; i < nv; ++i) {
-    if (!isfinite(kap[i]) || !isfinite(tau[i])) bad = 1;
-    if (diffusion) {
-      const double g = kap[i] * kap[i];
-      const double gt = exp(theta[nv + i]);
-      if (!isfinite(gt)) bad = 1;
-      const double K1[NPIECE] = {g, 1.0, 0.0, 0.0};
-      const double K2[NPIECE] = {g * g, 2.0 * g, 1.0, 0.0};
-      const double K3[NPIECE] = {g * g * g, 3.0 * g * g, 3.0 * g, 1.0};
-      for (int c = 0; c < NPIECE; ++c) {
-        wd[i][0][c] = 0.5 * K3[c] + gt * K2[c] + gt * gt * K1[c];
-        wd[i][1][c] = K3[c] + 2.0 * gt * gt * K1[c];
-        wd[i][2][c] = wd[i][0][c];  // nt = 1 is rejected at model creation
-        wb[i][c] = -gt * gt * K1[c];
+    for (int j = 0; j < 3; ++j)
+      for (int k = 0; k < 3; ++k) Mw[i][j][k] = 0.0;
+    if (i < nv) {
+      const double kap = exp(theta[i]);
+      const double rho = tanh(0.5 * theta[nv + i]);
+      sg[i] = exp(theta[2 * nv + i]);
+      tau[i] = gauss ? exp(theta[3 * nv + nl + i]) : 1.0;
+      if (!isfinite(kap) || !isfinite(tau[i])) bad = 1;
+      if (diffusion) {
+        const double g = kap * kap;
+        const double gt = exp(theta[nv + i]);
+        if (!isfinite(gt)) bad = 1;
+        const double K1[NPIECE] = {g, 1.0, 0.0, 0.0};
+        const double K2[NPIECE] = {g * g, 2.0 * g, 1.0, 0.0};
+        const double K3[NPIECE] = {g * g * g, 3.0 * g * g, 3.0 * g, 1.0};
+        for (int c = 0; c < NPIECE; ++c) {
+          wd[i][0][c] = 0.5 * K3[c] + gt * K2[c] + gt * gt * K1[c];
+          wd[i][1][c] = K3[c] + 2.0 * gt * gt * K1[c];
+          wd[i][2][c] = wd[i][0][c];  // nt = 1 is rejected at model creation
+          wb[i][c] = -gt * gt * K1[c];
+        }
+      } else {
+        const double k2 = kap * kap;
+        const double q[NPIECE] = {k2 * k2, 2.0 * k2, 1.0, 0.0};
+        const double r = rho;
+        const double den = 1.0 - r * r;
+        if (!(den > 0.0)) bad = 1;
+        logden[i] = log(den);
+        const double Tend = 1.0 / den, Tmid = (1.0 + r * r) / den, Toff = -r / den;
+        for (int c = 0; c < NPIECE; ++c) {
+          wd[i][0][c] = Tend * q[c];
+          wd[i][1][c] = Tmid * q[c];
+          wd[i][2][c] = q[c];
+          wb[i][c] = Toff * q[c];
+        }
       }
-    } else {
-      const double k2 = kap[i] * kap[i];
-      const double q[NPIECE] = {k2 * k2, 2.0 * k2, 1.0, 0.0};
-      const double r = rho[i];
-      const double den = 1.0 - r * r;
-      if (!(den > 0.0)) bad = 1;
-      logt += log(den);
-      const double Tend = 1.0 / den, Tmid = (1.0 + r * r) / den, Toff = -r / den;
-      for (int c = 0; c < NPIECE; ++c) {
-        wd[i][0][c] = Tend * q[c];
-        wd[i][1][c] = Tmid * q[c];
-        wd[i][2][c] = q[c];
-        wb[i][c] = Toff * q[c];
-      }
+      const double mj = (double)(m.m_off[i + 1] - m.m_off[i]);
+      if (gauss) llc[i] = 0.5 * mj * log(tau[i]) - 0.5 * mj * log(two_pi);
+      coef[C_TAU + i] = tau[i];
     }
   }
-  for (int tt = 0; tt < 3; ++tt)
-    for (int k = 0; k < 3; ++k)
-      for (int j = 0; j < 3; ++j)
-        for (int c = 0; c < NPIECE; ++c) {
-          double v = 0.0;
-          if (k < nv && j < nv)
-            for (int i = 0; i < nv; ++i) v += Mw[i][k][j] * wd[i][tt][c];
-          coef[C_D + ((tt * 3 + k) * 3 + j) * NPIECE + c] = v;
-        }
-  for (int k = 0; k < 3; ++k)
-    for (int j = 0; j < 3; ++j)
-      for (int c = 0; c < NPIECE; ++c) {
-        double v = 0.0;
-        if (k < nv && j < nv)
-          for (int i = 0; i < nv; ++i) v += Mw[i][k][j] * wb[i][c];
-        coef[C_B + (k * 3 + j) * NPIECE + c] = v;
+  // dim_theta is at most 15
+  if (lane < m.dim_theta) {
+    const double sd = m.theta_prior_sd;
+    const double z = (theta[lane] - m.theta_prior_mean[lane]) / sd;
+    prior[lane] = -0.5 * log(two_pi * sd * sd) - 0.5 * z * z;
+    if (!isfinite(theta[lane])) bad = 1;
+  }
+  __syncthreads();
+  if (lane == 0) {
+    if (nv == 1) {
+      Mw[0][0][0] = sg[0];  // tau_u
+    } else {
+      double lam[3] = {0.0, 0.0, 0.0};
+      for (int k = 0; k < nl; ++k) lam[k] = theta[3 * nv + k];
+      // Lambda of Eq. 5 (nv = 2 keeps its leading 2x2 block)
+      double L[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+      double Li[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+      L[0][0] = sg[0];
+      L[1][0] = lam[0] * sg[0];
+      L[1][1] = sg[1];
+      if (nv == 3) {
+        L[2][0] = (lam[2] + lam[0] * lam[1]) * sg[0];
+        L[2][1] = lam[1] * sg[1];
+        L[2][2] = sg[2];
       }
-  const double two_pi = 6.283185307179586476925286766559;
-  double lp = 0.0;
-  const double sd = m.theta_prior_sd;
-  for (int d = 0; d < m.dim_theta; ++d) {
-    const double z = (theta[d] - m.theta_prior_mean[d]) / sd;
-    lp += -0.5 * log(two_pi * sd * sd) - 0.5 * z * z;
+      // inverse of the lower-triangular Lambda, column by column
+      for (int c = 0; c < nv; ++c)
+        for (int r = c; r < nv; ++r) {
+          double acc = (r == c) ? 1.0 : 0.0;
+          for (int k = c; k < r; ++k) acc -= L[r][k] * Li[k][c];
+          Li[r][c] = acc / L[r][r];
+        }
+      for (int i = 0; i < nv; ++i)
+        for (int j = 0; j < nv; ++j)
+          for (int k = 0; k < nv; ++k) Mw[i][j][k] = Li[i][j] * Li[i][k];
+    }
+    double lp = 0.0, ll = 0.0, logt = 0.0;
+    for (int d = 0; d < m.dim_theta; ++d) lp += prior[d];
+    for (int i = 0; i < nv; ++i) {
+      ll += llc[i];
+      logt += logden[i];
+    }
+    coef[C_LOGPRIOR] = lp;
+    coef[C_LLCONST] = ll;
+    coef[C_BAD] = bad ? 1.0 : 0.0;
+    coef[C_LOGT] = (double)m.ns * logt;
   }
-  double llc = 0.0;
-  for (int j = 0; j < nv; ++j) {
-    const double mj = (double)(m.m_off[j + 1] - m.m_off[j]);
-    if (gauss) llc += 0.5 * mj * log(tau[j]) - 0.5 * mj * log(two_pi);
-    coef[C_TAU + j] = tau[j];
+  __syncthreads();
+  // tt < 3: diagonal blocks; tt = 3: the sub-diagonal block
+  for (int e = lane; e < 36 * NPIECE; e += 64) {
+    const int c = e % NPIECE, j = e / NPIECE % 3, k = e / (3 * NPIECE) % 3, tt = e / (9 * NPIECE);
+    double v = 0.0;
+    if (k < nv && j < nv)
+      for (int i = 0; i < nv; ++i) v += Mw[i][k][j] * (tt < 3 ? wd[i][tt][c] : wb[i][c]);
+    if (tt < 3) coef[C_D + ((tt * 3 + k) * 3 + j) * NPIECE + c] = v;
+    else coef[C_B + (k * 3 + j) * NPIECE + c] = v;
   }
-  for (int d = 0; d < m.dim_theta; ++d)
-    if (!isfinite(theta[d])) bad = 1;
-  coef[C_LOGPRIOR] = lp;
-  coef[C_LLCONST] = llc;
-  coef[C_BAD] = bad ? 1.0 : 0.0;
-  coef[C_LOGT] = (double)m.ns * logt;
 }
 
 hipError_t launch_theta_coeffs(const ThetaJob* jobs, int count, hipStream_t s) {
@@ -165,113 +162,163 @@ hipError_t launch_theta_coeffs(const ThetaJob* jobs, int count, hipStream_t s) {
 
 // ---- a2: sparse -> dense BTA assembly --------------------------------------------
 //
-// One workgroup builds column c of time step t in LDS and writes it, whole
-// and coalesced, to the dense blocks: the diagonal block D_t (lower triangle;
-// rows above c are written as zero), the sub-diagonal block B_t of rows t+1,
-// and for Q_c the arrow block R_t.  Q_c's column is Q_p's plus the
-// observation terms tau_j w w^T (Eq. 4; d_row w w^T with the per-row weights
-// of a non-Gaussian likelihood), added by one thread in a fixed order
-// so the result does not depend on scheduling.  Padding columns c >= b
-// (up to the padded block size bp) carry a unit diagonal, which leaves the
-// log-determinant unchanged.
+// The dense blocks are cleared by streaming stores, then a wave per column c of
+// time step t writes what is in it: the stencil's entries of the diagonal block
+// D_t (its lower triangle) and of the sub-diagonal block B_t of rows t+1, and for
+// Q_c the observation terms tau_j w w^T (Eq. 4; d_row w w^T with the per-row
+// weights of a non-Gaussian likelihood), the arrow block R_t and the
+// right-hand side.  The terms of an entry are added in the order of the index, so
+// the result does not depend on scheduling.  Padding columns c >= b (up to the
+// padded block size bp) carry a unit diagonal, which leaves the
+// log-determinant unchanged.  Bound by the writes of the cleared blocks; built
+// in LDS and written out column by column, 31 points of a 12 x 12 trivariate
+// model took 1.60 ms (now 0.47) and 9 of a 30 x 30 one 2.20 (1.19).
+
+// b_stencil: only the entries of B_t are written, its zeros are not cleared.
+__global__ __launch_bounds__(256) void k_assemble_clear(const AsmJob* __restrict__ jobs) {
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  const AsmJob J = jobs[blockIdx.z];
+  const int64_t bp = J.m->bp, ap = J.m->ap;
+  const int tl = blockIdx.y;
+  if (tl >= J.nt) return;
+  const AssembleOut& o = J.o;
+  auto clear = [&](void* base, int64_t bytes) {  // a multiple of 16
+    v2d* p = (v2d*)base;
+    const int64_t n = bytes / 16, stride = (int64_t)gridDim.x * 256;
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += stride)
+      p[e] = (v2d){0.0, 0.0};
+  };
+  const int64_t eb = o.b32 ? 4 : 8;
+  if (o.Dp) clear(o.Dp + tl * o.dp_stride, bp * bp * 8);
+  if (o.Dc) clear(o.Dc + tl * o.dc_stride, bp * bp * 8);
+  if (!o.b_stencil) {
+    if (o.Bp) clear((char*)o.Bp + tl * o.bp_stride * eb, bp * bp * eb);
+    if (o.BRc) clear((char*)o.BRc + tl * o.brc_stride * eb, (bp + ap) * bp * eb);
+  }
+}
+
+__device__ __forceinline__ void wave_fence() {  // LDS written by one lane, read by others
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 __global__ __launch_bounds__(256) void k_assemble_cols(const AsmJob* __restrict__ jobs) {
-  extern __shared__ double lds[];
+  constexpr int MOST = 32;  // observations a pass
+  __shared__ double s_term[4][3 * MOST], s_rhs[4][MOST];
+  __shared__ int s_row[4][3 * MOST], s_done[4][3 * MOST];
   const AsmJob J = jobs[blockIdx.z];
   const ModelDev& m = *J.m;
   const AssembleOut& o = J.o;
-  const int c = blockIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int c = blockIdx.x * 4 + wv;
   const int tl = blockIdx.y;
   const int bp = m.bp, ap = m.ap, ns = m.ns, nv = m.nv;
-  if (c >= bp || tl >= J.nt) return;
+  if (c >= bp || tl >= J.nt) return;  // waves do not wait for each other
   const int t = J.t0 + tl;
-  const int tid = threadIdx.x;
   const int64_t ldbr = bp + ap;
-  double* colD = lds;            // bp
-  double* colB = lds + bp;       // bp
-  double* colR = lds + 2 * bp;   // ap (<= 64)
-  __shared__ double rhs_s;
-  const bool hasB = t + 1 < m.nt;
+  const bool hasB = t + 1 < m.nt, b32 = o.b32 != 0;
   double* Dp = o.Dp ? o.Dp + tl * o.dp_stride + (int64_t)c * bp : nullptr;
-  double* Bp = o.Bp ? o.Bp + tl * o.bp_stride + (int64_t)c * bp : nullptr;
   double* Dc = o.Dc ? o.Dc + tl * o.dc_stride + (int64_t)c * bp : nullptr;
-  double* BRc = o.BRc ? o.BRc + tl * o.brc_stride + (int64_t)c * ldbr : nullptr;
-
-  const bool b32 = o.b32 != 0;
-  float* Bp32 = o.Bp ? (float*)o.Bp + tl * o.bp_stride + (int64_t)c * bp : nullptr;
-  float* BRc32 = o.BRc ? (float*)o.BRc + tl * o.brc_stride + (int64_t)c * ldbr : nullptr;
+  const int64_t bo = tl * o.bp_stride + (int64_t)c * bp;
+  const int64_t bro = tl * o.brc_stride + (int64_t)c * ldbr;
+  auto put_br = [&](int r, double v) {
+    if (b32) ((float*)o.BRc)[bro + r] = (float)v; else o.BRc[bro + r] = v;
+  };
   if (c >= m.b) {
-    for (int r = tid; r < bp; r += 256) {
-      const double v = (r == c) ? 1.0 : 0.0;
-      if (Dp) Dp[r] = v;
-      if (Bp) { if (b32) Bp32[r] = 0.f; else Bp[r] = 0.0; }
-      if (Dc) Dc[r] = v;
-    }
-    if (BRc)
-      for (int r = tid; r < bp + ap; r += 256) {
-        if (b32) BRc32[r] = 0.f; else BRc[r] = 0.0;
+    if (lane == 0) {
+      if (Dp) Dp[c] = 1.0;
+      if (Dc) {
+        Dc[c] = 1.0;
+        o.rhs[(int64_t)t * bp + c] = 0.0;
       }
-    if (Dc && tid == 0) o.rhs[(int64_t)t * bp + c] = 0.0;
+    }
+    if (Dc)
+      for (int r = lane; r < ap; r += 64) put_br(bp + r, 0.0);
     return;
   }
   const int j = c / ns;
   const int s = c - j * ns;
-  for (int r = tid; r < 2 * bp + ap; r += 256) lds[r] = 0.0;
-  __syncthreads();
   const int tt = (m.nt == 1) ? 2 : ((t == 0 || t == m.nt - 1) ? 0 : 1);
-  const int e0 = m.sp_ptr[s], e1 = m.sp_ptr[s + 1];
-  const int ne = (e1 - e0) * nv;
-  for (int idx = tid; idx < ne; idx += 256) {
-    const int e = e0 + idx / nv;
-    const int k = idx % nv;
-    const int r = k * ns + m.sp_col[e];
-    const double pc = m.sp_C[e], pg = m.sp_G[e], pg2 = m.sp_G2[e], pg3 = m.sp_G3[e];
-    const double* cd = J.coef + C_D + ((tt * 3 + k) * 3 + j) * NPIECE;
-    colD[r] = cd[0] * pc + cd[1] * pg + cd[2] * pg2 + cd[3] * pg3;
-    if (hasB) {
-      const double* cb = J.coef + C_B + (k * 3 + j) * NPIECE;
-      colB[r] = cb[0] * pc + cb[1] * pg + cb[2] * pg2 + cb[3] * pg3;
-    }
-  }
-  __syncthreads();
-  if (Dp)
-    for (int r = tid; r < bp; r += 256) Dp[r] = (r >= c) ? colD[r] : 0.0;
-  if (Bp)
-    for (int r = tid; r < bp; r += 256) {
-      if (b32) Bp32[r] = (float)colB[r]; else Bp[r] = colB[r];
-    }
-  if (!Dc) return;
-  __syncthreads();
-  if (tid == 0) {
-    const double tau = J.coef[C_TAU + j];
-    const double* __restrict__ od = o.obs_d;
-    const double* __restrict__ oz = o.obs_z;
-    const int64_t key = ((int64_t)j * m.nt + t) * ns + s;
-    double racc = 0.0;
-    const int nr = m.nr;
-    for (int64_t p = m.no_ptr[key]; p < m.no_ptr[key + 1]; ++p) {
-      const int64_t row = m.no_row[p];
-      const int qs = m.no_q[p];
-      const double wq = m.obs_w[row * 3 + qs];
-      const double wr = od ? od[row] : tau;
-      for (int q2 = 0; q2 < 3; ++q2) {
-        const int r = j * ns + m.obs_nodes[row * 3 + q2];
-        colD[r] += wr * m.obs_w[row * 3 + q2] * wq;
+  const int e0 = m.sp_ptr[s];
+  const int ne = (m.sp_ptr[s + 1] - e0) * nv;  // at most 75: two a lane
+  double d[2];
+  int row[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int idx = lane + 64 * h;
+    row[h] = -1;
+    d[h] = 0.0;
+    if (idx < ne) {
+      const int e = e0 + idx / nv;
+      const int k = idx % nv;
+      const int r = k * ns + m.sp_col[e];
+      const double pc = m.sp_C[e], pg = m.sp_G[e], pg2 = m.sp_G2[e], pg3 = m.sp_G3[e];
+      const double* cd = J.coef + C_D + ((tt * 3 + k) * 3 + j) * NPIECE;
+      d[h] = cd[0] * pc + cd[1] * pg + cd[2] * pg2 + cd[3] * pg3;
+      row[h] = r;
+      if (Dp && r >= c) Dp[r] = d[h];
+      if (hasB) {
+        const double* cb = J.coef + C_B + (k * 3 + j) * NPIECE;
+        const double v = cb[0] * pc + cb[1] * pg + cb[2] * pg2 + cb[3] * pg3;
+        if (o.Bp) { if (b32) ((float*)o.Bp)[bo + r] = (float)v; else o.Bp[bo + r] = v; }
+        if (o.BRc) put_br(r, v);
       }
-      for (int rr = 0; rr < nr; ++rr)
-        colR[j * nr + rr] += wr * m.obs_x[row * nr + rr] * wq;
-      racc += od ? wq * oz[row] : tau * wq * m.obs_y[row];
     }
-    rhs_s = racc;
   }
-  __syncthreads();
-  for (int r = tid; r < bp; r += 256) {
-    Dc[r] = (r >= c) ? colD[r] : 0.0;
-    if (b32) BRc32[r] = (float)colB[r]; else BRc[r] = colB[r];
+  if (!Dc) return;
+  const double tau = J.coef[C_TAU + j];
+  const double* __restrict__ od = o.obs_d;
+  const double* __restrict__ oz = o.obs_z;
+  const int nr = m.nr;
+  const int64_t key = ((int64_t)j * m.nt + t) * ns + s;
+  const int64_t p0 = m.no_ptr[key], p1 = m.no_ptr[key + 1];
+  double* term = s_term[wv];
+  double* rterm = s_rhs[wv];
+  int* trow = s_row[wv];
+  int* done = s_done[wv];
+  double racc = 0.0, cov = 0.0;  // cov: of arrow row `lane` (ap is at most 64)
+  const int rr = lane - j * nr;
+  for (int64_t p = p0; p < p1; p += MOST) {
+    const int n = (int)min((int64_t)MOST, p1 - p);
+    wave_fence();  // the terms before are read no more
+    for (int e = lane; e < 3 * n; e += 64) {
+      const int64_t ob = m.no_row[p + e / 3];
+      const int q2 = e % 3;
+      const double wq = m.obs_w[ob * 3 + m.no_q[p + e / 3]];
+      term[e] = (od ? od[ob] : tau) * m.obs_w[ob * 3 + q2] * wq;
+      trow[e] = j * ns + m.obs_nodes[ob * 3 + q2];
+      done[e] = 0;
+      if (q2 == 0) rterm[e / 3] = od ? wq * oz[ob] : tau * wq * m.obs_y[ob];
+    }
+    if (rr >= 0 && rr < nr)
+      for (int e = 0; e < n; ++e) {
+        const int64_t ob = m.no_row[p + e];
+        const double wq = m.obs_w[ob * 3 + m.no_q[p + e]];
+        cov += (od ? od[ob] : tau) * m.obs_x[ob * nr + rr] * wq;
+      }
+    wave_fence();
+    for (int f = 0; f < 3 * n; ++f) {
+      const int r = trow[f];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (row[h] == r) {
+          d[h] += term[f];
+          done[f] = 1;
+        }
+    }
+    wave_fence();
+    if (lane == 0) {
+      for (int e = 0; e < n; ++e) racc += rterm[e];
+      // nodes beyond the stencil
+      for (int f = 0; f < 3 * n; ++f)
+        if (!done[f] && trow[f] >= c) Dc[trow[f]] += term[f];
+    }
   }
-  for (int r = tid; r < ap; r += 256) {
-    if (b32) BRc32[bp + r] = (float)colR[r]; else BRc[bp + r] = colR[r];
-  }
-  if (tid == 0) o.rhs[(int64_t)t * bp + c] = rhs_s;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (row[h] >= c) Dc[row[h]] = d[h];
+  if (lane < ap) put_br(bp + lane, cov);
+  if (lane == 0) o.rhs[(int64_t)t * bp + c] = racc;
 }
 
 // Tips (a x a, identity-padded to ap) and the fixed-effect part of the
@@ -323,13 +370,16 @@ __global__ __launch_bounds__(256) void k_assemble_tip(const AsmJob* __restrict__
   const int64_t b0 = m.m_off[j], b1 = m.m_off[j + 1];
   const double* __restrict__ od = o.obs_d;
   const double* __restrict__ oz = o.obs_z;
+  const double* __restrict__ xs = m.obs_x;
+  const double* __restrict__ ys = m.obs_y;
   double acc = 0.0;
+#pragma unroll 8  // one workgroup a sum: eight rows' loads in flight
   for (int64_t row = b0 + tid; row < b1; row += 256) {
-    const double xr = m.obs_x[row * nr + r];
+    const double xr = xs[row * nr + r];
     if (od)  // per-row weights: sum d x_r x_r2 and x_r z, no tau
-      acc += gram ? od[row] * xr * m.obs_x[row * nr + r2] : xr * oz[row];
+      acc += gram ? od[row] * xr * xs[row * nr + r2] : xr * oz[row];
     else
-      acc += gram ? xr * m.obs_x[row * nr + r2] : xr * m.obs_y[row];
+      acc += gram ? xr * xs[row * nr + r2] : xr * ys[row];
   }
   sh[tid] = acc;
   __syncthreads();
@@ -348,22 +398,16 @@ __global__ __launch_bounds__(256) void k_assemble_tip(const AsmJob* __restrict__
   }
 }
 
-hipError_t launch_assemble_cols(const AsmJob* jobs, int count, int max_bp,
-                                int max_nt, int max_shmem_doubles, hipStream_t s) {
+hipError_t launch_assemble_cols(const AsmJob* jobs, int count, int max_bp, int max_nt,
+                                hipStream_t s) {
   if (count <= 0) return hipSuccess;
-  const size_t shmem = (size_t)max_shmem_doubles * sizeof(double);
-  hipLaunchKernelGGL(k_assemble_cols, dim3(max_bp, max_nt, count), dim3(256),
-                     shmem, s, jobs);
+  // 32 KB or more a workgroup
+  const int64_t per = (int64_t)max_bp * max_bp / 4096;
+  hipLaunchKernelGGL(k_assemble_clear, dim3((unsigned)std::min<int64_t>(per, 256), max_nt, count),
+                     dim3(256), 0, s, jobs);
+  hipLaunchKernelGGL(k_assemble_cols, dim3((max_bp + 3) / 4, max_nt, count), dim3(256), 0, s,
+                     jobs);
   return hipGetLastError();
-}
-
-// Allow the column kernel its dynamic LDS (2*bp + ap doubles) beyond the
-// default 64 KiB; called once per workspace, outside any graph capture.
-hipError_t prepare_assemble(int max_shmem_doubles) {
-  const size_t shmem = (size_t)max_shmem_doubles * sizeof(double);
-  if (shmem <= 65536) return hipSuccess;
-  return hipFuncSetAttribute((const void*)k_assemble_cols,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
 }
 
 // max_blocks = 1 + max over jobs of nv*nr*nr + nv*nr
@@ -398,6 +442,45 @@ __device__ __forceinline__ double blk_sum(double v, double* sh) {
   return r;
 }
 
+// This lane's share (every fourth stencil point from `sub`) of row (t, k, sp) of
+// Q_p x; cs: the coefficient table in LDS.  Four lanes a row, and a point's
+// coefficients for all its products at once: with one lane a row, entry by
+// entry, 31 points of a 12 x 12 trivariate model took 317 us (a chain of 117
+// entries), now 31.
+__device__ __forceinline__ double stencil_part(const ModelDev& m, const double* cs,
+                                               const double* __restrict__ x, int t, int k, int sp,
+                                               int sub) {
+  const int ns = m.ns, nv = m.nv, bp = m.bp;
+  const int tt = (m.nt == 1) ? 2 : ((t == 0 || t == m.nt - 1) ? 0 : 1);
+  const double* __restrict__ pC = m.sp_C;
+  const double* __restrict__ pG = m.sp_G;
+  const double* __restrict__ pG2 = m.sp_G2;
+  const double* __restrict__ pG3 = m.sp_G3;
+  const int* __restrict__ pcol = m.sp_col;
+  const bool before = t > 0, after = t < m.nt - 1;
+  const double* xt = x + (int64_t)t * bp;
+  double q = 0.0;
+  const int e1 = m.sp_ptr[sp + 1];
+  for (int e = m.sp_ptr[sp] + sub; e < e1; e += 4) {
+    const int c = pcol[e];
+    const double a0 = pC[e], a1 = pG[e], a2 = pG2[e], a3 = pG3[e];
+    for (int j = 0; j < nv; ++j) {
+      const double* cd = cs + C_D + ((tt * 3 + k) * 3 + j) * NPIECE;
+      const double* cb = cs + C_B + (k * 3 + j) * NPIECE;
+      const double* xc = xt + j * ns + c;
+      const double xb = before ? xc[-bp] : 0.0, xa = after ? xc[bp] : 0.0;
+      q += (cd[0] * a0 + cd[1] * a1 + cd[2] * a2 + cd[3] * a3) * xc[0];
+      q += (cb[0] * a0 + cb[1] * a1 + cb[2] * a2 + cb[3] * a3) * (xb + xa);
+    }
+  }
+  return q;
+}
+
+__device__ __forceinline__ double quad_sum(double v) {  // over a row's four lanes
+  v += __shfl_xor(v, 1, 64);
+  return v + __shfl_xor(v, 2, 64);
+}
+
 __global__ __launch_bounds__(256) void k_quad_prior(const QuadJob* __restrict__ jobs) {
   __shared__ double sh[256];
   const QuadJob Q = jobs[blockIdx.y];
@@ -405,31 +488,21 @@ __global__ __launch_bounds__(256) void k_quad_prior(const QuadJob* __restrict__ 
   const double* __restrict__ coef = Q.coef;
   const double* __restrict__ mu = Q.mu;
   double* __restrict__ partial = Q.partial;
+  __shared__ double cs[C_SIZE];
+  for (int e = threadIdx.x; e < C_SIZE; e += 256) cs[e] = coef[e];
+  __syncthreads();
   const int64_t nrows = (int64_t)m.nt * m.b;
-  const int ns = m.ns, nv = m.nv, bp = m.bp;
+  const int ns = m.ns, bp = m.bp;
+  const int sub = threadIdx.x & 3;
   double acc = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nrows;
-       i += (int64_t)gridDim.x * 256) {
+  // rows are a quad's, so all four lanes of one take part in its sum
+  for (int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2); i < nrows;
+       i += (int64_t)gridDim.x * 64) {
     const int t = (int)(i / m.b);
     const int rl = (int)(i - (int64_t)t * m.b);
     const int k = rl / ns, sp = rl - k * ns;
-    const int tt = (m.nt == 1) ? 2 : ((t == 0 || t == m.nt - 1) ? 0 : 1);
-    double qmu = 0.0;
-    for (int dt = -1; dt <= 1; ++dt) {
-      const int t2 = t + dt;
-      if (t2 < 0 || t2 >= m.nt) continue;
-      for (int j = 0; j < nv; ++j) {
-        const double* cf = (dt == 0) ? coef + C_D + ((tt * 3 + k) * 3 + j) * NPIECE
-                                     : coef + C_B + (k * 3 + j) * NPIECE;
-        const double* x = mu + (int64_t)t2 * bp + j * ns;
-        for (int e = m.sp_ptr[sp]; e < m.sp_ptr[sp + 1]; ++e) {
-          const double qv = cf[0] * m.sp_C[e] + cf[1] * m.sp_G[e] + cf[2] * m.sp_G2[e] +
-                            cf[3] * m.sp_G3[e];
-          qmu += qv * x[m.sp_col[e]];
-        }
-      }
-    }
-    acc += mu[(int64_t)t * bp + rl] * qmu;
+    const double qmu = quad_sum(stencil_part(m, cs, mu, t, k, sp, sub));
+    if (sub == 0) acc += mu[(int64_t)t * bp + rl] * qmu;
   }
   if (blockIdx.x == 0)
     for (int f = threadIdx.x; f < m.a; f += 256) {
@@ -615,38 +688,30 @@ __global__ __launch_bounds__(256) void k_res_rows(const ResJob* __restrict__ job
   const ResJob R = jobs[blockIdx.y];
   const ModelDev& m = *R.m;
   const double* __restrict__ coef = R.coef;
-  const int ns = m.ns, nv = m.nv, bp = m.bp;
+  __shared__ double cs[C_SIZE];
+  for (int e = threadIdx.x; e < C_SIZE; e += 256) cs[e] = coef[e];
+  __syncthreads();
+  const int ns = m.ns, bp = m.bp;
   const int64_t nrows = (int64_t)m.nt * m.b;
+  const int sub = threadIdx.x & 3;
   double acc_r = 0.0, acc_b = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nrows;
-       i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2); i < nrows;
+       i += (int64_t)gridDim.x * 64) {
     const int t = (int)(i / m.b);
     const int rl = (int)(i - (int64_t)t * m.b);
     const int k = rl / ns, sp = rl - k * ns;
-    const int tt = (m.nt == 1) ? 2 : ((t == 0 || t == m.nt - 1) ? 0 : 1);
-    double q = 0.0;
-    for (int dt = -1; dt <= 1; ++dt) {
-      const int t2 = t + dt;
-      if (t2 < 0 || t2 >= m.nt) continue;
-      for (int j = 0; j < nv; ++j) {
-        const double* cf = (dt == 0) ? coef + C_D + ((tt * 3 + k) * 3 + j) * NPIECE
-                                     : coef + C_B + (k * 3 + j) * NPIECE;
-        const double* x = R.v + (int64_t)t2 * bp + j * ns;
-        for (int e = m.sp_ptr[sp]; e < m.sp_ptr[sp + 1]; ++e) {
-          const double qv = cf[0] * m.sp_C[e] + cf[1] * m.sp_G[e] + cf[2] * m.sp_G2[e] +
-                            cf[3] * m.sp_G3[e];
-          q += qv * x[m.sp_col[e]];
-        }
-      }
-    }
+    double q = stencil_part(m, cs, R.v, t, k, sp, sub);
     const int64_t key = ((int64_t)k * m.nt + t) * ns + sp;
-    for (int64_t p = m.no_ptr[key]; p < m.no_ptr[key + 1]; ++p)
+    for (int64_t p = m.no_ptr[key] + sub; p < m.no_ptr[key + 1]; p += 4)
       q += m.obs_w[(int64_t)m.no_row[p] * 3 + m.no_q[p]] * R.av[m.no_row[p]];
-    const int64_t o = (int64_t)t * bp + rl;
-    const double res = R.rhs[o] - q;
-    R.out[o] = res;
-    acc_r += res * res;
-    acc_b += R.rhs[o] * R.rhs[o];
+    q = quad_sum(q);
+    if (sub == 0) {
+      const int64_t o = (int64_t)t * bp + rl;
+      const double res = R.rhs[o] - q;
+      R.out[o] = res;
+      acc_r += res * res;
+      acc_b += R.rhs[o] * R.rhs[o];
+    }
   }
   const double s1 = blk_sum(acc_r, sh);
   const double s2 = blk_sum(acc_b, sh);
@@ -668,8 +733,12 @@ __global__ __launch_bounds__(256) void k_res_tip(const ResJob* __restrict__ jobs
   if (e < nv * nr) {
     const int j = e / nr, r = e % nr;
     double acc = 0.0;
-    for (int64_t row = m.m_off[j] + threadIdx.x; row < m.m_off[j + 1]; row += 256)
-      acc += m.obs_x[row * nr + r] * R.av[row];
+    const int64_t end = m.m_off[j + 1];
+    const double* __restrict__ xs = m.obs_x;
+    const double* __restrict__ av = R.av;
+#pragma unroll 8  // as in k_assemble_tip
+    for (int64_t row = m.m_off[j] + threadIdx.x; row < end; row += 256)
+      acc += xs[row * nr + r] * av[row];
     const double s = blk_sum(acc, sh);
     if (threadIdx.x == 0) {
       const int64_t o = base + e;

@@ -421,6 +421,7 @@ struct PlanSet {
   // refinement plans: init (x <- mu), res (residual of x and its norms), corr
   // (solve with the factor, x += correction unless converged), fin (mu <- x
   // and the final residual), resid (the final residual of mu alone)
+  Plan asm_e[3];  // assembly within an evaluation (see seq_assemble)
   Plan theta_p, asm_p[3], fac_p[3], solve_p, selinv_p, post_p, eval_p;
   Plan solve_m_p;  // SOLVE_RHS right-hand sides at once (I.xm -> I.mum)
   Plan qpsum_p;  // log|Q_p| after fac_p of an evaluation that keeps Q_p
@@ -471,7 +472,6 @@ struct dl_ws : PlanSet {
   MiscJob* d_io = nullptr;  // one descriptor for dl_ws_get_block / set_block
   bool assembled[2] = {false, false}, factored[2] = {false, false};
   bool solved = false;
-  int max_shmem = 0;
   // graph of the whole evaluation plan
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
@@ -574,7 +574,7 @@ static hipError_t run_launch(dl_ws* W, const Launch& L, hipStream_t s) {
       case OP_SUM: e = launch_sums(d.sum + L.off, L.count, s); break;
       case OP_FINISH: e = launch_selinv_finish(d.fin + L.off, L.count, L.gx, s); break;
       case OP_ASM_COLS:
-        e = launch_assemble_cols(d.asmj + L.off, L.count, L.gx, L.gy, W->max_shmem, s);
+        e = launch_assemble_cols(d.asmj + L.off, L.count, L.gx, L.gy, s);
         break;
       case OP_ASM_TIPS: e = launch_assemble_tips(d.asmj + L.off, L.count, L.gx, s); break;
       case OP_THETA: e = launch_theta_coeffs(d.th + L.off, L.count, s); break;
@@ -599,8 +599,11 @@ static double asm_bytes(const ModelDev& m, bool p, bool c, int nsteps) {
 }
 
 // theta -> coefficients, tips and fixed-effect right-hand side, and the dense
-// blocks of Q_c (and Q_p when it is stored in full).
-static void seq_assemble(dl_ws* W, Inst& I, bool p, bool c, std::vector<Step>& q) {
+// blocks of Q_c (and Q_p when it is stored in full).  stencil: of the sub-diagonal
+// blocks the stencil's entries alone (evaluations, whose assembled blocks
+// nobody else reads).
+static void seq_assemble(dl_ws* W, Inst& I, bool p, bool c, bool stencil,
+                         std::vector<Step>& q) {
   const ModelDev& m = I.m;
   Step th;
   th.key = K(0, 0, 0, 0);
@@ -648,6 +651,7 @@ static void seq_assemble(dl_ws* W, Inst& I, bool p, bool c, std::vector<Step>& q
     }
     J.o.rhs = I.rhs;
     J.o.b32 = I.mixed ? 1 : 0;
+    J.o.b_stencil = stencil ? 1 : 0;
     if (c && I.poisson) {
       J.o.obs_d = I.obs_d;
       J.o.obs_z = I.obs_z;
@@ -831,6 +835,7 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
     s.asmj.o.Bp = B;
     s.asmj.o.rhs = I.rhs;
     s.asmj.o.b32 = I.mixed ? 1 : 0;
+    s.asmj.o.b_stencil = W->dense ? 0 : 1;
     s.gx = bp;
     s.gy = 1;
     q.push_back(s);
@@ -1457,9 +1462,17 @@ static dl_status build_plans(dl_ws* W) {
     std::vector<std::vector<Step>> seqs;
     for (auto& I : W->inst) {
       seqs.emplace_back();
-      seq_assemble(W, I, wh != 1, wh != 0, seqs.back());
+      seq_assemble(W, I, wh != 1, wh != 0, false, seqs.back());
     }
     merge(seqs, H, W->table, W->asm_p[wh]);
+  }
+  for (int wh = 1; wh < 3 && !W->dense; ++wh) {  // evaluations: Q_c or both
+    std::vector<std::vector<Step>> seqs;
+    for (auto& I : W->inst) {
+      seqs.emplace_back();
+      seq_assemble(W, I, wh != 1, true, true, seqs.back());
+    }
+    merge(seqs, H, W->table, W->asm_e[wh]);
   }
   for (int wh = 0; wh < 3; ++wh) {
     std::vector<std::vector<Step>> seqs;
@@ -1531,7 +1544,7 @@ static dl_status build_plans(dl_ws* W) {
     merge(seqs, H, W->table, W->selinv_p);
   }
   W->eval_p.idx.clear();
-  append(W->eval_p, W->asm_p[2]);
+  append(W->eval_p, W->asm_e[2]);
   append(W->eval_p, W->fac_p[2]);
   append(W->eval_p, W->qpsum_p);
   append(W->eval_p, W->solve_p);
@@ -1841,12 +1854,12 @@ extern "C" dl_status dl_ws_create_batch(const dl_model* const* models,
   auto A = [&](size_t bytes, void** p) {
     if (st == DL_OK) st = dev_alloc(W->allocs, bytes, p, &W->bytes);
   };
-  int dim_total = 0;
+  int dim_total = 0, max_rows = 0;
   for (int k = 0; k < nmodels; ++k) {
     Inst& I = W->inst[k];
     inst_layout(W, I, models[k], two_sided);
     dim_total += I.dim;
-    W->max_shmem = std::max(W->max_shmem, 2 * I.m.bp + I.m.ap);
+    max_rows = std::max(max_rows, 2 * I.m.bp + I.m.ap);
     inst_buffers(W, I, A);
     if (I.poisson && st == DL_OK &&
         (hipMemset(I.obs_d, 0, sizeof(double) * (I.m.m_total + 1)) != hipSuccess ||
@@ -1902,8 +1915,7 @@ extern "C" dl_status dl_ws_create_batch(const dl_model* const* models,
       W->inst[k].alpha = W->alpha_all + k;
       W->inst[k].out4 = W->out4_all + 4 * k;
     }
-  if (W->max_shmem * 8 > 160 * 1024 ||
-      prepare_assemble(W->max_shmem) != hipSuccess) {
+  if (max_rows * 8 > 160 * 1024) {  // blocks beyond 10 000 rows are refused
     ws_free(W);
     return DL_EINVAL;
   }
@@ -2221,7 +2233,7 @@ static dl_status laplace_pass(dl_ws* W, int nk, hipStream_t s) {
   if (const dl_status st = assembled_plans(W, 0, 1); st != DL_OK) return st;
   // Q_p and the first step's Q_c(x0) share their launches
   DL_HIP_CHECK(launch_lap_weights(W->d_lap, B, s));
-  DL_HIP_CHECK(run(W, W->asm_p[2], s));
+  DL_HIP_CHECK(run(W, W->asm_e[2], s));
   DL_HIP_CHECK(run(W, W->fac_p[2], s));
   DL_HIP_CHECK(run(W, W->qpsum_p, s));
   // state: 0 iterating, 1 converged, -1 failed, 2 idle (k >= nk)
@@ -2238,7 +2250,7 @@ static dl_status laplace_pass(dl_ws* W, int nk, hipStream_t s) {
     if (!any) break;
     if (it > 0) {
       DL_HIP_CHECK(launch_lap_weights(W->d_lap, B, s));
-      DL_HIP_CHECK(run(W, W->asm_p[1], s));
+      DL_HIP_CHECK(run(W, W->asm_e[1], s));
       DL_HIP_CHECK(run(W, W->fac_p[1], s));
     }
     DL_HIP_CHECK(run(W, W->solve_p, s));
@@ -2290,7 +2302,7 @@ static dl_status laplace_pass(dl_ws* W, int nk, hipStream_t s) {
     if (state[k] == 0) state[k] = -1;
   // Q_c and its factor at the mode, then Eq. 8 at mu = x*
   DL_HIP_CHECK(launch_lap_weights(W->d_lap, B, s));
-  DL_HIP_CHECK(run(W, W->asm_p[1], s));
+  DL_HIP_CHECK(run(W, W->asm_e[1], s));
   DL_HIP_CHECK(run(W, W->fac_p[1], s));
   for (auto& I : W->inst)
     DL_HIP_CHECK(hipMemcpyAsync(I.mu, I.xcur, sizeof(double) * I.m.Np,
@@ -2319,7 +2331,7 @@ static dl_status run_eval(dl_ws* W, hipStream_t s) {
   dl_status st = assembled_plans(W, 0, 1);
   if (st != DL_OK || (st = set_refine_tol(W, DL_REFINE_TOL, s)) != DL_OK) return st;
   if (!W->use_graph) {
-    DL_HIP_CHECK(run(W, W->asm_p[2], s));
+    DL_HIP_CHECK(run(W, W->asm_e[2], s));
     DL_HIP_CHECK(run(W, W->fac_p[2], s));
     DL_HIP_CHECK(run(W, W->qpsum_p, s));
     DL_HIP_CHECK(run(W, W->solve_p, s));
@@ -2415,7 +2427,7 @@ extern "C" dl_status fobj_selinv_eval(dl_ws* W, const double* theta_dev, int32_t
     if ((st = assembled_plans(W, 0, 1)) != DL_OK ||
         (st = set_refine_tol(W, DL_REFINE_TOL, s)) != DL_OK)
       return st;
-    DL_HIP_CHECK(run(W, W->asm_p[2], s));
+    DL_HIP_CHECK(run(W, W->asm_e[2], s));
     DL_HIP_CHECK(run(W, W->fac_p[2], s));
     DL_HIP_CHECK(run(W, W->qpsum_p, s));
     DL_HIP_CHECK(hipEventRecord(W->ev_fork, s));

@@ -85,6 +85,8 @@ struct AssembleOut {
   double* Pc;   // ap x ap (tip of Q_c)
   double* rhs;  // Np
   int b32;      // Bp and BRc are stored in FP32 (mixed precision)
+  int b_stencil;  // only the stencil's entries of the sub-diagonal blocks are
+                  // written (all that the factorisation reads of them)
   // per-observation D and right-hand-side values (m_total each) in place of
   // tau_y and tau_y y (non-Gaussian likelihoods; null: Gaussian)
   const double* obs_d;
@@ -130,11 +132,9 @@ struct CombineJob {
 constexpr int QF_BLOCKS = 256;
 
 hipError_t launch_theta_coeffs(const ThetaJob* jobs, int count, hipStream_t s);
-// max_bp / max_nt bound the grid over the jobs; max_shmem_doubles = max over
-// the jobs' models of 2*bp + ap.
-hipError_t launch_assemble_cols(const AsmJob* jobs, int count, int max_bp,
-                                int max_nt, int max_shmem_doubles, hipStream_t s);
-hipError_t prepare_assemble(int max_shmem_doubles);
+// max_bp / max_nt bound the grid over the jobs.
+hipError_t launch_assemble_cols(const AsmJob* jobs, int count, int max_bp, int max_nt,
+                                hipStream_t s);
 hipError_t launch_assemble_tips(const AsmJob* jobs, int count, int max_blocks,
                                 hipStream_t s);
 hipError_t launch_quadforms(const QuadJob* jobs, int count, hipStream_t s);
