@@ -105,7 +105,10 @@ struct GemmTask {
   int32_t red_begin;         // first reduction workgroup of this task
   int32_t ksplit;            // split-k piece length (0: GEMM_KSPLIT; resolved
                              // by finalize_tasks)
-  int32_t pad_;
+  // the launch's tasks repeat with this period: equal ones (the chains' or the
+  // batch's) are dealt tile by tile, so that the long tiles of all come first
+  // (in turn, f_obj with variances at 45 x 45, 100 steps, took 106.7 ms, so 98.1)
+  int32_t period;
   Band band;                 // of the F_BAND_ROW / F_BAND_COL operands
 };
 

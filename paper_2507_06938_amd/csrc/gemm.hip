@@ -1,6 +1,7 @@
 // FP64 MFMA tile GEMM over a list of tasks (gfx950).
 //
-// One workgroup computes one 64x64 tile (4 wave64, 32x32 per wave) or one
+// One workgroup computes one 64x64 tile (4 wave64, 32x32 per wave, or 8 with
+// 16x32) or one
 // 128x128 tile (8 wave64, 64x32 per wave; two workgroups fit one compute
 // unit) of C for one task of a launch (the tile size is fixed per launch).
 // Tiles of all tasks of a launch are numbered consecutively; a workgroup
@@ -214,6 +215,16 @@ __device__ __forceinline__ void tile_coords(const GemmTask& T, int lt, int& tm,
                                             int& tn) {
   constexpr int KCOL = F_KLO_COL | F_KHI_COL, KROW = F_KLO_ROW | F_KHI_ROW;
   if (!(T.flags & F_LOWER) && (T.flags & (KCOL | KROW | F_KTAIL))) {
+    if ((T.flags & F_KLO_COL) && (T.flags & F_KLO_ROW) && T.tiles_m == T.tiles_n) {
+      // by both: shells of equal max(row, column)
+      int s = (int)sqrt((double)lt);
+      while (s * s > lt) --s;
+      while ((s + 1) * (s + 1) <= lt) ++s;
+      const int pos = lt - s * s;
+      tm = pos <= s ? s : pos - s - 1;
+      tn = pos <= s ? pos : s;
+      return;
+    }
     // k range set by the tile column (or row): whole columns (rows) in
     // order of decreasing length
     if (T.flags & (KCOL | F_KTAIL)) {
@@ -355,11 +366,13 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
 
   const int tid = threadIdx.x;
   const int wid = (tasks[0].flags & F_KVAR) ? (int)blockIdx.x : xcd_tile(blockIdx.x, gridDim.x);
-  const int ti = find_unit_task(tasks, ntask, wid, false);
-  const GemmTask T = tasks[ti];
+  const int period = tasks[0].period, reps = ntask / period;
+  const int kind = find_unit_task(tasks, period, wid, false);
+  const int unit = wid - tasks[kind].unit_begin;
+  const GemmTask T = tasks[kind + unit % reps * period];
   // slice-major: the workgroups of one XCD take one k piece of a compact
   // patch of tiles
-  const int local = wid - T.unit_begin;
+  const int local = unit / reps;
   const int lt = local % T.ntiles, sl = local / T.ntiles;
   int tm, tn;
   tile_coords(T, lt, tm, tn);
@@ -569,6 +582,31 @@ int finalize_tasks(GemmTask* t, int n, int tile, int* nred, int64_t* nslots) {
       red += t[i].ntiles;
     }
   }
+  // tiles of unequal lengths, unsplit: the shortest period of equal tasks
+  int period = n;
+  if (kvar && slots == 0) {
+    auto same = [&](const GemmTask& a, const GemmTask& b) {
+      return a.M == b.M && a.N == b.N && a.K == b.K && a.flags == b.flags &&
+             a.band.period == b.band.period && a.band.reach == b.band.reach &&
+             a.band.rows == b.band.rows && a.band.end == b.band.end;
+    };
+    for (int p = 1; p < n; ++p) {
+      bool ok = n % p == 0;
+      for (int i = p; i < n && ok; ++i) ok = same(t[i], t[i - p]);
+      if (ok) {
+        period = p;
+        break;
+      }
+    }
+  }
+  for (int i = 0; i < n; ++i) t[i].period = period;
+  if (period < n) {
+    int begin = 0;
+    for (int i = 0; i < period; ++i) {
+      t[i].unit_begin = t[i].tile_begin = begin;
+      begin += t[i].ntiles * (n / period);
+    }
+  }
   if (nred) *nred = red;
   if (nslots) *nslots = slots;
   return units;
@@ -577,8 +615,16 @@ int finalize_tasks(GemmTask* t, int n, int tile, int* nred, int64_t* nslots) {
 hipError_t launch_gemm_tasks(const GemmTask* tasks_dev, int ntask, int units,
                              hipStream_t s, int tile, double* partials) {
   if (units <= 0) return hipSuccess;
+  // Eight waves a 64 x 64 tile halve the time of one tile at the same rate of a
+  // compute unit, which counts where few tiles, or tiles of unequal length, end a
+  // launch (17 x 17 bivariate f_obj with variances 4.40 -> 4.20 ms, 45 x 45, 100
+  // steps, 110.5 -> 106.7); four waves read less LDS, which counts where many
+  // tiles follow each other (batch with blocks up to 6075 rows 114.7 / 115.9).
   if (tile == 128)
     hipLaunchKernelGGL((k_gemm_tasks<128, 2, 4, 4, 1>), dim3(units), dim3(512), 0, s,
+                       tasks_dev, ntask, partials);
+  else if (units < 4096)
+    hipLaunchKernelGGL((k_gemm_tasks<64, 4, 2, 6, 1>), dim3(units), dim3(512), 0, s,
                        tasks_dev, ntask, partials);
   else
     hipLaunchKernelGGL((k_gemm_tasks<64, 2, 2, 4, 1>), dim3(units), dim3(256), 0, s,
@@ -810,10 +856,12 @@ __global__ __launch_bounds__(256) void k_gemm32_tasks(
 
   const int tid = threadIdx.x;
   const int tile = (tasks[0].flags & F_KVAR) ? (int)blockIdx.x : xcd_tile(blockIdx.x, gridDim.x);
-  const int ti = find_task(tasks, ntask, tile);
-  const GemmTask T = tasks[ti];
+  const int period = tasks[0].period, reps = ntask / period;
+  const int kind = find_task(tasks, period, tile);
+  const int unit = tile - tasks[kind].tile_begin;
+  const GemmTask T = tasks[kind + unit % reps * period];
   int tm, tn;
-  tile_coords(T, tile - T.tile_begin, tm, tn);
+  tile_coords(T, unit / reps, tm, tn);
   const int m0 = tm * BT;
   const int n0 = tn * BT;
   const bool ta = T.flags & F_TA;
