@@ -568,7 +568,7 @@ static hipError_t run_launch(dl_ws* W, const Launch& L, hipStream_t s) {
                             std::min(L.gx, W->dag_workers), s);
         break;
       case OP_MISC: e = launch_misc(d.misc + L.off, L.count, s); break;
-      case OP_GEMV_N: e = launch_gemv_n(d.gn + L.off, L.count, L.gx, L.gy, s); break;
+      case OP_GEMV_N: e = launch_gemv_n(d.gn + L.off, L.count, L.gx, L.gz, L.gy, s); break;
       case OP_GEMV_T: e = launch_gemv_t(d.gt + L.off, L.count, L.gx, L.gy, s); break;
       case OP_COUPLE: e = launch_couple(d.couple + L.off, L.count, L.gx, W->mixed, s); break;
       case OP_SUM: e = launch_sums(d.sum + L.off, L.count, s); break;
@@ -997,6 +997,7 @@ static Step gn_step(uint64_t key, GemvN g, double bytes, int nrhs) {
   s.flops = bytes / 4.0;
   s.gx = g.M;
   s.gy = nrhs;
+  s.gz = g.K;
   return s;
 }
 

@@ -11,9 +11,12 @@
 // On the factor of the 45 x 45, nt = 100 model a solve took 3.55 ms: 16.8 us
 // (4.1 TB/s) per pair of 2112 x 2048 blocks plus a 4.1 us launch that summed
 // the pieces, and four right-hand sides four times that, since each read the
-// whole factor.  Now 2.92 ms
-// for one (14.2 us a pair and no second launch) and 3.8 ms for four (18.9).
+// whole factor.  Now 2.46 ms
+// for one (12.9 us a pair and no second launch) and 3.4 ms for four (17.1), of
+// about half the bytes (the zeros before a row's first column are passed over).
 #include "solve.hpp"
+
+#include <algorithm>
 
 namespace dl {
 
@@ -25,6 +28,12 @@ constexpr int GEMV_T_COLS = 4;
 typedef double v2d __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) double gdouble;
+// Columns of a slice.  Up to ONE columns are one slice: the hand-over to the last
+// workgroup takes longer than the other slices' loads.
+constexpr int ONE = 256;
+__host__ __device__ constexpr int slice_len(int K) {
+  return K <= ONE ? ONE : (K <= 64 * GEMV_KS ? 64 : (K + GEMV_KS - 1) / GEMV_KS);
+}
 template <typename TA> struct Vec;
 template <> struct Vec<double> { typedef v2d type; };
 template <> struct Vec<float> { typedef v4f type; };
@@ -51,7 +60,7 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
   typedef typename Vec<TA>::type vec_t;
   const int rb = blockIdx.x, sl = blockIdx.y;
   if (rb * RB >= g.M) return;
-  const int len = max(64, (g.K + GEMV_KS - 1) / GEMV_KS);
+  const int len = slice_len(g.K);
   const int kend = g.tri ? min(g.K, rb * RB + RB) : g.K;
   // A's zeros before its rows' first column are skipped by whole slices and
   // by whole 128 columns of a slice
@@ -140,14 +149,16 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
     if (m >= g.M) continue;
     double s;
     if (nsl > 1) {
-      double v[GEMV_KS];
+      s = 0.0;
+      for (int q0 = sl0; q0 < sl0 + nsl; q0 += 16) {
+        double v[16];
 #pragma unroll
-      for (int q = 0; q < GEMV_KS; ++q)
-        v[q] = q >= sl0 && q < sl0 + nsl ? cload(&g.partial[((int64_t)q * R + r) * g.M + m])
-                                         : 0.0;
-      s = v[0];
+        for (int q = 0; q < 16; ++q)
+          v[q] = q0 + q < sl0 + nsl ? cload(&g.partial[((int64_t)(q0 + q) * R + r) * g.M + m])
+                                    : 0.0;
 #pragma unroll
-      for (int q = 1; q < GEMV_KS; ++q) s += v[q];
+        for (int q = 0; q < 16; ++q) s += v[q];
+      }
     } else {
       s = wave_sum(e);
     }
@@ -171,9 +182,12 @@ __global__ __launch_bounds__(NT) void k_gemv_n(const GemvN* __restrict__ jobs) {
   else gemv_n_body<R, double>(g, xs, sh, &s_last);
 }
 
-hipError_t launch_gemv_n(const GemvN* jobs, int count, int max_M, int nrhs, hipStream_t s) {
+hipError_t launch_gemv_n(const GemvN* jobs, int count, int max_M, int max_K, int nrhs,
+                         hipStream_t s) {
   if (count <= 0 || max_M <= 0) return hipSuccess;
-  const dim3 grid((max_M + 127) / 128, GEMV_KS, count);
+  // the most slices of any K up to max_K
+  const int max_slices = max_K <= ONE ? 1 : std::min(GEMV_KS, (max_K + 63) / 64);
+  const dim3 grid((max_M + 127) / 128, max_slices, count);
   if (nrhs > 1) hipLaunchKernelGGL(k_gemv_n<SOLVE_RHS>, grid, dim3(NT), 0, s, jobs);
   else hipLaunchKernelGGL(k_gemv_n<1>, grid, dim3(NT), 0, s, jobs);
   return hipGetLastError();
@@ -225,14 +239,27 @@ __device__ void gemv_t_body(const GemvT& g, double* sh) {
         for (int v = 0; v < V; ++v) acc[r][c] = __builtin_fma((double)a[c][v], xv[v], acc[r][c]);
     }
   }
+  // a butterfly over the lanes, halving the sums a lane carries while it has
+  // several: R TC - 1 + 6 - log2(R TC) exchanges in place of 6 R TC
+  double* a = &acc[0][0];
+  int held = 0;  // the sum this lane ends up with
 #pragma unroll
-  for (int r = 0; r < R; ++r)
+  for (int off = 32, n = R * TC; off > 0; off >>= 1) {
+    const bool up = lane & off;
+    if (n > 1) {
+      n >>= 1;
 #pragma unroll
-    for (int c = 0; c < TC; ++c) {
-      double v = acc[r][c];
-      for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-      if (lane == 0) sh[(wave * R + r) * TC + c] = v;
+      for (int e = 0; e < n; ++e) {
+        const double keep = up ? a[e + n] : a[e];
+        a[e] = keep + __shfl_xor(up ? a[e] : a[e + n], off, 64);
+      }
+      held += up ? n : 0;
+    } else {
+      a[0] += __shfl_xor(a[0], off, 64);
     }
+  }
+  // every sum once: the lanes below its last exchange hold copies
+  if ((lane & (64 / (R * TC) - 1)) == 0) sh[wave * R * TC + held] = a[0];
   __syncthreads();
   if (threadIdx.x < R * TC) {
     const int r = threadIdx.x / TC, j = j0 + threadIdx.x % TC;

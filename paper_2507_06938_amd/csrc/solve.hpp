@@ -3,7 +3,7 @@
 
 namespace dl {
 
-constexpr int GEMV_KS = 16;   // most column slices of a matrix-vector product
+constexpr int GEMV_KS = 32;   // most column slices of a matrix-vector product
 constexpr int SOLVE_RHS = 4;  // right-hand sides of one pass over the factor
 
 // out = beta*base + alpha*A*x, rows [0, split) -> out1/base1 and rows
@@ -50,9 +50,9 @@ struct GemvT {
   Band band;  // of A's rows (period 0: dense)
 };
 
-// Batched launches over job arrays in device memory; max_M / max_N bound the
-// grid over all jobs; nrhs: 1 or SOLVE_RHS.
-hipError_t launch_gemv_n(const GemvN* jobs_dev, int count, int max_M, int nrhs,
+// Batched launches over job arrays in device memory; max_M / max_K / max_N bound
+// the grid over all jobs; nrhs: 1 or SOLVE_RHS.
+hipError_t launch_gemv_n(const GemvN* jobs_dev, int count, int max_M, int max_K, int nrhs,
                          hipStream_t s);
 hipError_t launch_gemv_t(const GemvT* jobs_dev, int count, int max_N, int nrhs,
                          hipStream_t s);
