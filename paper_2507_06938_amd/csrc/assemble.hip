@@ -217,6 +217,7 @@ __global__ __launch_bounds__(256) void k_assemble_cols(const AsmJob* __restrict_
   const int t = J.t0 + tl;
   const int64_t ldbr = bp + ap;
   const bool hasB = t + 1 < m.nt, b32 = o.b32 != 0;
+  if (o.bc && c == 0 && tl == 0 && lane < NPIECE) o.bc[lane] = J.coef[C_B + lane];
   double* Dp = o.Dp ? o.Dp + tl * o.dp_stride + (int64_t)c * bp : nullptr;
   double* Dc = o.Dc ? o.Dc + tl * o.dc_stride + (int64_t)c * bp : nullptr;
   const int64_t bo = tl * o.bp_stride + (int64_t)c * bp;

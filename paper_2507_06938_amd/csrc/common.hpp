@@ -56,6 +56,8 @@ enum : int {
   F_BAND_COL = 16384,
   F_KTAIL = 32768,
   F_HALF_I = 65536,  // C = tril(I + alpha A B) with half its diagonal
+  // FP32 kernel only: the products of every 16 terms are added in FP64
+  F_ACC64 = 131072,
 };
 
 // First nonzero column of the rows of [C_t; R_t], C_t = B_t G_t^T: row
@@ -131,8 +133,10 @@ hipError_t launch_gemm_tasks(const GemmTask* tasks_dev, int ntask, int units,
 hipError_t launch_gemm_reduce(const GemmTask* tasks_dev, int ntask, int nred,
                               const double* partials, hipStream_t s, int tile);
 // FP32 MFMA variant; A/B/C pointers are float* unless F_A64/F_B64/F_C64.
+// acc64: some task of the launch has F_ACC64.
 hipError_t launch_gemm32_tasks(const GemmTask* tasks_dev, int ntask,
-                               int total_tiles, hipStream_t s, int tile = 64);
+                               int total_tiles, hipStream_t s, int tile = 64,
+                               bool acc64 = false);
 
 // Convenience: copy host tasks to a device buffer, then launch.  Used by
 // the dense ABI entry points and by plan building (never inside timed
@@ -216,7 +220,7 @@ hipError_t launch_panel_updates(const PanelTask* tasks_dev, int ntask, int grid,
 // takes the next task word (in list order), waits until the counters it
 // depends on are set, runs the task on 64 x 64 tiles and sets its counter.
 // On return each block holds G in its lower triangle, logdiag[i] = log L_ii
-// and *info the first bad pivot (as the panel path), or DL_INFO_TIMEOUT when
+// and *info the first bad pivot, or DL_INFO_TIMEOUT when
 // a wait gave up (it never should: the list order cannot deadlock).
 struct DagBlock {
   double* A;          // the block (bp x bp, ld)

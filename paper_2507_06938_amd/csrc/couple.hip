@@ -47,12 +47,18 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) {
 // chain over the dense row; columns of B from the end of the tile on meet
 // zeros of G and are left out, so a tile before the stencil's reach only writes
 // zeros.
-template <typename T>
+//
+// S: type of the sums.  In FP32 storage with one response it is double, B's
+// entries are formed again from the model and C is rounded once: log|Q_p| is
+// exact there (one diagonal block's), so what FP32 sums and the rounding of a
+// stencil of few distinct values do to log|Q_c|, systematic over all rows, would
+// be in f.
+template <typename T, typename S>
 __device__ __forceinline__ void couple_tiles(const CoupleJob& J, int ti, int tj0, double* lds) {
   const int bp = J.bp, ns = J.ns, nv = J.nv, w = J.w;
   const int lane = threadIdx.x & 31, half = threadIdx.x >> 5;
   T* t = (T*)lds;                                // [64 columns][TR + 1]
-  T* val = (T*)(lds + TILE_LDS);                 // [nv][TR][WP]
+  S* val = (S*)(lds + TILE_LDS);                 // [nv][TR][WP]
   int* off = (int*)(lds + TILE_LDS + 3 * TR * WP);  // [nv][TR][WP]: column times bp / 64
   const T* B = (const T*)J.B;
   for (int e = threadIdx.x; e < nv * TR * WP; e += NT) {
@@ -63,7 +69,16 @@ __device__ __forceinline__ void couple_tiles(const CoupleJob& J, int ti, int tj0
       k = J.col[(i % ns) * w + q];
       if (k >= 0) k += kv * ns;
     }
-    val[(kv * TR + r) * WP + q] = k >= 0 ? B[i + (int64_t)k * J.ldb] : (T)0;
+    S v = (S)0;
+    if (k >= 0) {
+      if constexpr (sizeof(S) > sizeof(T)) {
+        const int e0 = J.m->sp_ptr[i] + q;  // the stencil is the whole pattern
+        v = J.bc[0] * J.m->sp_C[e0] + J.bc[1] * J.m->sp_G[e0] + J.bc[2] * J.m->sp_G2[e0];
+      } else {
+        v = B[i + (int64_t)k * J.ldb];
+      }
+    }
+    val[(kv * TR + r) * WP + q] = v;
     off[(kv * TR + r) * WP + q] = k >= 0 ? k * (bp / 64) : 0;
   }
   const int klo = J.band.lo(ti * TR, TR, bp);
@@ -73,27 +88,27 @@ __device__ __forceinline__ void couple_tiles(const CoupleJob& J, int ti, int tj0
     const int kend = (tj + 1) * 64, oend = kend * (bp / 64);
 #pragma unroll 1
     for (int row = half; row < TR; row += NT / 32) {
-      T a0 = (T)0, a1 = (T)0;
+      S a0 = (S)0, a1 = (S)0;
       if (klo < kend)
 #pragma unroll 1
         for (int kv = 0; kv < nv; ++kv) {
           const int at = (kv * TR + row) * WP;
           v2d g[W];
-          T v[W];
+          S v[W];
 #pragma unroll
           for (int q = 0; q < W; ++q) {
             const int o = off[at + q];
-            v[q] = o < oend ? val[at + q] : (T)0;
+            v[q] = o < oend ? val[at + q] : (S)0;
             g[q] = G[(int64_t)(o < oend ? o : oend - bp / 64) * 32];
           }
 #pragma unroll
           for (int q = 0; q < W; ++q) {
-            a0 = fma_t(v[q], (T)g[q].x, a0);
-            a1 = fma_t(v[q], (T)g[q].y, a1);
+            a0 = fma_t(v[q], (S)g[q].x, a0);
+            a1 = fma_t(v[q], (S)g[q].y, a1);
           }
         }
-      t[2 * lane * (TR + 1) + row] = a0;
-      t[(2 * lane + 1) * (TR + 1) + row] = a1;
+      t[2 * lane * (TR + 1) + row] = (T)a0;
+      t[(2 * lane + 1) * (TR + 1) + row] = (T)a1;
     }
     __syncthreads();
     // the stores run along the rows
@@ -193,7 +208,13 @@ __device__ __forceinline__ void couple_body(const CoupleJob& J, double* lds) {
   u -= arrow;
   const int nr = J.bp / TR;
   if (!J.B || u >= nr * J.groups) return;
-  couple_tiles<T>(J, u / J.groups, u % J.groups, lds);
+  if constexpr (sizeof(T) == 4) {
+    if (J.bc) {
+      couple_tiles<T, double>(J, u / J.groups, u % J.groups, lds);
+      return;
+    }
+  }
+  couple_tiles<T, T>(J, u / J.groups, u % J.groups, lds);
 }
 }  // namespace
 

@@ -6,6 +6,8 @@
 
 namespace dl {
 
+struct ModelDev;
+
 struct CoupleJob {
   const int* col;     // stencil of B (ModelDev::cp_col)
   int32_t b, a, bp, ap, ns, nv, w;
@@ -17,6 +19,10 @@ struct CoupleJob {
   int64_t ldb;
   int32_t groups;     // workgroups over the column tiles (finalize_couple)
   Band band;          // where the rows of C begin
+  // one response in FP32 storage: the model and the weights of the FEM pieces in
+  // B (C_BC), its entries then not read from their rounded storage
+  const ModelDev* m;
+  const double* bc;
 };
 
 // Fill the jobs' grouping for one launch and return its workgroups per job.

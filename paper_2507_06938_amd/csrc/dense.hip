@@ -606,8 +606,8 @@ hipError_t launch_panel_updates(const PanelTask* tasks, int ntask, int grid,
 // (one atomic add on head[0] each), wait until the counters the task depends
 // on are set (a lane polls each, 2 s limit), run the task on 64 x 64 tiles
 // staged in LDS and set the task's counter.  The tile operations
-// are those of the panel path: the same staging, the same MFMA products
-// (mfma1_k64), the same tile factor (potrf_body).
+// are those of the panel launches of dl_dpotrf: the same staging, the same
+// MFMA products (mfma1_k64), the same tile factor (potrf_body).
 //
 // Hand-over between workgroups, which may sit on different XCDs (each with
 // its own L2), without cache write-back or invalidation: every value a task

@@ -69,6 +69,7 @@ struct Launch {
   int gx, gy, gz;     // grid bounds (max over merged steps)
   int tile;           // GEMM output tile (64 or 128)
   int nred;           // GEMM: reduction workgroups of a split launch
+  bool acc64;         // GEMM32: some task sums in FP64
 };
 
 // Default GEMM tile for a launch (before any measured choice): 128x128 when
@@ -166,8 +167,12 @@ static void merge(const std::vector<std::vector<Step>>& seqs, Descs& D,
         for (const Step* st : g) D.gemm.insert(D.gemm.end(), st->gemm.begin(), st->gemm.end());
         L.count = (int)D.gemm.size() - L.off;
         if (L.kind == OP_GEMM32)  // the FP32 kernel does not split k
-          for (int i = L.off; i < L.off + L.count; ++i) D.gemm[i].flags &= ~F_SPLIT;
-        L.tile = default_tile(D.gemm, L.off, L.count);
+          for (int i = L.off; i < L.off + L.count; ++i) {
+            D.gemm[i].flags &= ~F_SPLIT;
+            L.acc64 |= (D.gemm[i].flags & F_ACC64) != 0;
+          }
+        // (with FP64 sums the 128 tile leaves a SIMD one wave)
+        L.tile = L.acc64 ? 64 : default_tile(D.gemm, L.off, L.count);
         L.gx = finalize_tasks(D.gemm.data() + L.off, L.count, L.tile, &L.nred);
         if (L.gx == 0) continue;
         break;
@@ -366,6 +371,14 @@ struct Inst {
   // seq_logdet_qp); Dp holds that block
   bool kron = false;     // the model and precision allow it
   bool qp_kron = false;
+  // FP32 off-diagonal blocks beside an exact log|Q_p|: the coupling products are
+  // summed in FP64 and rounded once, the updates' FP32 products added in FP64
+  // every 16 terms.  The systematic part of FP32 sums, which the sweeps of both
+  // matrices shared and f cancelled in part, no longer has a counterpart: at 45 x
+  // 45 nodes with 100 steps f was off by 4.8e-3 with both sweeps in FP32, by
+  // 2.2e-2 with the exact log|Q_p| and FP32 sums, now by 7.8e-4 (log|Q_c| 5.7e-8,
+  // now 2.0e-9 relative), for 51.6 ms an f_obj against 50.8.
+  bool acc64 = false;
   // Q_c: full storage, [B_t; R_t] in nt+1 slots of (bp+ap) x bp (nt+2 when
   // two-sided: one spare slot per elimination chain)
   double *Dc = nullptr, *BRc = nullptr, *Pc = nullptr, *GPc = nullptr;
@@ -558,7 +571,7 @@ static hipError_t run_launch(dl_ws* W, const Launch& L, hipStream_t s) {
         }
         break;
       case OP_GEMM32:
-        e = launch_gemm32_tasks(d.gemm + L.off, L.count, L.gx, s, L.tile);
+        e = launch_gemm32_tasks(d.gemm + L.off, L.count, L.gx, s, L.tile, L.acc64);
         break;
       case OP_RES: e = launch_residual(d.res + L.off, L.count, s); break;
       case OP_POTRF: e = launch_potrf_tiles(d.potrf + L.off, L.count, s); break;
@@ -648,6 +661,7 @@ static void seq_assemble(dl_ws* W, Inst& I, bool p, bool c, bool stencil,
     if (c) {
       J.o.Dc = I.Dc; J.o.dc_stride = bb;
       J.o.BRc = I.BRc; J.o.brc_stride = I.ldbr * m.bp;
+      if (I.acc64) J.o.bc = I.coef + C_BC;
     }
     J.o.rhs = I.rhs;
     J.o.b32 = I.mixed ? 1 : 0;
@@ -851,7 +865,7 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
   // split k of the FP64 products (FP32 launches drop the flag)
   const int xf = W->splitk ? F_SPLIT : 0;
   const int x64 = I.mixed ? F_B64 : 0;
-  const int c64 = I.mixed ? F_C64 : 0;
+  const int c64 = (I.mixed ? F_C64 : 0) | (w == 1 && I.acc64 ? F_ACC64 : 0);
   auto gs = [&](uint64_t key, int cat, double fl, std::vector<GemmTask> ts) {
     return I.mixed ? gemm32_step(key, cat, fl, std::move(ts))
                    : gemm_step(key, cat, fl, std::move(ts));
@@ -919,6 +933,10 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
       c.RC = BRo(nw, bp);
       c.ldb = ldbr;
       c.band = coupling_band(I);
+      if (w == 1 && I.acc64) {
+        c.m = I.model->dev;
+        c.bc = I.coef + C_BC;
+      }
       q.push_back(s);
     }
     if (!ring) {
@@ -1663,11 +1681,12 @@ static void inst_layout(const dl_ws* W, Inst& I, const dl_model* model, bool two
   // without observations Q_c is Q_p and the two half log-determinants of Eq. 8
   // cancel to the bit when both come from the same sweep; in mixed precision
   // the sweep's log|Q_p| of a coregional model carries up to 6e-5 of FP32
-  // rounding (nv = 1: 8e-8), which f keeps as it was
+  // rounding, much of which f cancels with log|Q_c|'s: both stay as they were
   I.kron = m.family == DL_MODEL_SEPARABLE && m.m_total > 0 && (!W->mixed || m.nv == 1);
   I.qp_kron = I.kron && I.qp_ring;
   I.ldbr = m.bp + m.ap;
   I.mixed = W->mixed;
+  I.acc64 = I.mixed && I.kron;
   I.eb = I.mixed ? 4 : 8;
   // two chains need at least one block each besides the root
   I.two = two_sided && m.nt >= 4;

@@ -652,6 +652,9 @@ hipError_t launch_gemm_reduce(const GemmTask* tasks_dev, int ntask, int nred,
 // the operand is stored in FP64 (it is then rounded to FP32 when staged);
 // C is FP32 unless F_C64, in which case alpha*acc + beta*C is formed in FP64
 // and stored in FP64 (Schur updates into FP64 diagonal blocks and tips).
+// F_ACC64 tasks add every chunk of 16 products to FP64 sums: a chain of b of them
+// in FP32 lost, systematically, 1e-7 of every pivot.  The 64 tile then has four waves
+// a SIMD in place of six: f_obj of 45 x 45 nodes, 100 steps 51.6 ms against 50.8.
 // Lane layout of the FP32 accumulator: register r of lane l holds
 // D[4(l/16) + r][l%16] (checked against host GEMMs by the GPU tests).
 typedef float v4f_ __attribute__((ext_vector_type(4)));
@@ -820,12 +823,26 @@ __device__ __forceinline__ void mma_chunk32(const float* __restrict__ as,
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[ks][j], fa[ks][i], acc[i][j], 0, 0, 0);
 }
 
-template <int BT, typename TA, typename TB>
+// acc64 += acc, acc = 0
+template <int F>
+__device__ __forceinline__ void flush32(v4f_ (&acc)[F][F], v4d (&acc64)[F][F]) {
+#pragma unroll
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc64[i][j][r] += (double)acc[i][j][r];
+      acc[i][j] = (v4f_){0.f, 0.f, 0.f, 0.f};
+    }
+}
+
+template <int BT, bool WIDE, typename TA, typename TB>
 __device__ __forceinline__ void gemm32_vec_loop(const GemmTask& T, bool ta, bool tb, int m0,
                                                 int n0, int kb, int ke, int nchunks, int tid,
                                                 float* As0, float* As1, float* Bs0, float* Bs1,
-                                                v4f_ (&acc)[BT / 32][BT / 32], int wm, int wn,
-                                                int lrow, int lk) {
+                                                v4f_ (&acc)[BT / 32][BT / 32],
+                                                v4d (&acc64)[BT / 32][BT / 32], bool wide,
+                                                int wm, int wn, int lrow, int lk) {
   VStage32<BT, TA> sa;
   VStage32<BT, TB> sb;
   sa.init(T.A, T.lda, ta, m0, T.M, kb, ke, tid);
@@ -838,6 +855,7 @@ __device__ __forceinline__ void gemm32_vec_loop(const GemmTask& T, bool ta, bool
   for (int c = 0; c < nchunks; ++c) {
     sa.load(va); sb.load(vb); sa.next(); sb.next();  // chunk c + 1
     mma_chunk32<BT>((c & 1) ? As1 : As0, (c & 1) ? Bs1 : Bs0, acc, wm, wn, lrow, lk);
+    if (WIDE && wide) flush32(acc, acc64);
     sa.store((c & 1) ? As0 : As1, va);
     sb.store((c & 1) ? Bs0 : Bs1, vb);
     __syncthreads();
@@ -845,7 +863,7 @@ __device__ __forceinline__ void gemm32_vec_loop(const GemmTask& T, bool ta, bool
 }
 }  // namespace
 
-template <int BT>
+template <int BT, bool WIDE>
 __global__ __launch_bounds__(256) void k_gemm32_tasks(
     const GemmTask* __restrict__ tasks, int ntask) {
   constexpr int LD = BT + 4;
@@ -883,22 +901,29 @@ __global__ __launch_bounds__(256) void k_gemm32_tasks(
   for (int i = 0; i < F; ++i)
 #pragma unroll
     for (int j = 0; j < F; ++j) acc[i][j] = (v4f_){0.f, 0.f, 0.f, 0.f};
+  const bool wide = WIDE && (T.flags & F_ACC64);
+  v4d acc64[F][F];
+  if (WIDE)
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+      for (int j = 0; j < F; ++j) acc64[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
 
   const bool vec_a = vec_operand32(T.A, a64 ? 8 : 4, T.lda, ta, T.M, kb, ke);
   const bool vec_b = vec_operand32(T.B, b64 ? 8 : 4, T.ldb, !tb, T.N, kb, ke);
   if (vec_a && vec_b) {
     if (a64 && b64)
-      gemm32_vec_loop<BT, double, double>(T, ta, tb, m0, n0, kb, ke, nchunks, tid, As[0], As[1],
-                                          Bs[0], Bs[1], acc, wm, wn, lrow, lk);
+      gemm32_vec_loop<BT, WIDE, double, double>(T, ta, tb, m0, n0, kb, ke, nchunks, tid, As[0], As[1],
+                                          Bs[0], Bs[1], acc, acc64, wide, wm, wn, lrow, lk);
     else if (a64)
-      gemm32_vec_loop<BT, double, float>(T, ta, tb, m0, n0, kb, ke, nchunks, tid, As[0], As[1],
-                                         Bs[0], Bs[1], acc, wm, wn, lrow, lk);
+      gemm32_vec_loop<BT, WIDE, double, float>(T, ta, tb, m0, n0, kb, ke, nchunks, tid, As[0], As[1],
+                                         Bs[0], Bs[1], acc, acc64, wide, wm, wn, lrow, lk);
     else if (b64)
-      gemm32_vec_loop<BT, float, double>(T, ta, tb, m0, n0, kb, ke, nchunks, tid, As[0], As[1],
-                                         Bs[0], Bs[1], acc, wm, wn, lrow, lk);
+      gemm32_vec_loop<BT, WIDE, float, double>(T, ta, tb, m0, n0, kb, ke, nchunks, tid, As[0], As[1],
+                                         Bs[0], Bs[1], acc, acc64, wide, wm, wn, lrow, lk);
     else
-      gemm32_vec_loop<BT, float, float>(T, ta, tb, m0, n0, kb, ke, nchunks, tid, As[0], As[1],
-                                        Bs[0], Bs[1], acc, wm, wn, lrow, lk);
+      gemm32_vec_loop<BT, WIDE, float, float>(T, ta, tb, m0, n0, kb, ke, nchunks, tid, As[0], As[1],
+                                        Bs[0], Bs[1], acc, acc64, wide, wm, wn, lrow, lk);
   } else {
     float va[PER], vb[PER];
     if (nchunks > 0) {
@@ -936,9 +961,11 @@ __global__ __launch_bounds__(256) void k_gemm32_tasks(
         store_chunk32<BT>(As[buf ^ 1], ta, tid, va);
         store_chunk32<BT>(Bs[buf ^ 1], !tb, tid, vb);
       }
+      if (WIDE && wide) flush32(acc, acc64);
       __syncthreads();
     }
   }
+  if (WIDE && !wide) flush32(acc, acc64);
   const bool lower = T.flags & F_LOWER;
   const bool beta0 = T.flags & F_BETA0;
   const bool c64 = T.flags & F_C64;
@@ -955,12 +982,12 @@ __global__ __launch_bounds__(256) void k_gemm32_tasks(
         const int64_t o = (int64_t)m + (int64_t)n * T.ldc;
         if (c64) {
           double* p = (double*)T.C + o;
-          double v = T.alpha * (double)acc[i][j][r];
+          double v = T.alpha * (WIDE ? acc64[i][j][r] : (double)acc[i][j][r]);
           if (!beta0) v += T.beta * (*p);
           *p = v;
         } else {
           float* p = (float*)T.C + o;
-          float v = (float)T.alpha * acc[i][j][r];
+          float v = (float)T.alpha * (WIDE ? (float)acc64[i][j][r] : acc[i][j][r]);
           if (!beta0) v += (float)T.beta * (*p);
           *p = v;
         }
@@ -970,14 +997,11 @@ __global__ __launch_bounds__(256) void k_gemm32_tasks(
 }
 
 hipError_t launch_gemm32_tasks(const GemmTask* tasks_dev, int ntask,
-                               int total_tiles, hipStream_t s, int tile) {
+                               int total_tiles, hipStream_t s, int tile, bool acc64) {
   if (total_tiles <= 0) return hipSuccess;
-  if (tile == 128)
-    hipLaunchKernelGGL(k_gemm32_tasks<128>, dim3(total_tiles), dim3(256), 0, s,
-                       tasks_dev, ntask);
-  else
-    hipLaunchKernelGGL(k_gemm32_tasks<64>, dim3(total_tiles), dim3(256), 0, s,
-                       tasks_dev, ntask);
+  const auto k = tile == 128 ? (acc64 ? k_gemm32_tasks<128, true> : k_gemm32_tasks<128, false>)
+                             : (acc64 ? k_gemm32_tasks<64, true> : k_gemm32_tasks<64, false>);
+  hipLaunchKernelGGL(k, dim3(total_tiles), dim3(256), 0, s, tasks_dev, ntask);
   return hipGetLastError();
 }
 

@@ -16,6 +16,7 @@ namespace dl {
 //                       block; tt = 0 first/last time step, 1 interior
 //                       step, 2 single step (nt = 1)
 //   [C_B + (k*3 + j)*NPIECE + c]  the same for a sub-diagonal block
+//   [C_BC + c]          those of the last Q_c assembled (one response)
 enum : int {
   NPIECE = 4,
   C_LOGPRIOR = 0,
@@ -25,7 +26,8 @@ enum : int {
   C_TAU = 4,
   C_D = 8,
   C_B = 8 + 27 * NPIECE,
-  C_SIZE = 8 + 36 * NPIECE + 4
+  C_BC = C_B + 9 * NPIECE,
+  C_SIZE = C_BC + NPIECE
 };
 
 // Most points of the coupling stencil.
@@ -91,6 +93,7 @@ struct AssembleOut {
   // tau_y and tau_y y (non-Gaussian likelihoods; null: Gaussian)
   const double* obs_d;
   const double* obs_z;
+  double* bc;   // the coefficients of B_t are copied there (null: not)
 };
 
 struct ThetaJob {
