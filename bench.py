@@ -292,9 +292,9 @@ def main():
                     help="only run the CPU oracle leg (full-size f_obj on the host, "
                          "no GPU) and print it")
     ap.add_argument("--diag-factor", choices=("panel", "dag"), default="dag",
-                    help="diagonal blocks factored by one launch per 64-column "
-                         "panel, or by one persistent tile-task launch per "
-                         "elimination step")
+                    help="accepted for older command lines; both values factor "
+                         "the diagonal blocks by one persistent tile-task launch "
+                         "per elimination step")
     ap.add_argument("--tiles", default=os.path.join(
         ROOT, "paper_2507_06938_amd", "tiles_gfx950.txt"),
         help="autotuner cache ('' disables tuning: default tiles)")
@@ -440,8 +440,7 @@ def main():
                    "nb": wl.a, "m": wl.m, "b": wl.b, "N": wl.N,
                    "step": "fobj_eval + bta_selinv (all marginal variances)",
                    "order": args.order,
-                   "block_inverse": ("inside the persistent tile-task launches" if dag
-                                     else "inside the panel launches"),
+                   "block_inverse": "inside the persistent tile-task launches",
                    "gemm_tiles": tiles},
         "fobj_only_evals_per_s": 1000.0 / fobj_ms,
         "bta_cholesky_tflops": F / (fac_ms * 1e-3) / 1e12,
@@ -454,8 +453,6 @@ def main():
     del ws
     torch.cuda.empty_cache()
     if not args.no_extras:
-        # (the batch keeps the panel launches: with nine instances' blocks in
-        # each persistent launch it measured 7.5 evals/s against 8.8)
         out["fd_gradient_batch"] = fd_batch(D, W, wl, model, fobj_ms, args.tiles,
                                             two_sided, dag=False)
         out["mixed_precision"] = mixed(D, wl, model, errors, args.tiles, two_sided, dag)
