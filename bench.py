@@ -11,9 +11,8 @@ marginal variances.  By default the time domain is split into two
 partitions eliminated concurrently toward a middle block (``--order
 two-sided``; ``one-sided`` sweeps the time steps forward only).  Inputs are
 seeded and synthetic and already resident on the device when the timed
-region starts.  Single evaluations form the diagonal blocks' inverses inside
-the launches of their factorisation (the batched gradient keeps the
-recursive GEMM inversion, which is faster for many blocks at once).
+region starts.  The diagonal blocks are factored and inverted by one
+persistent tile-task launch per elimination step.
 
 Prints one JSON line.  Besides the metric it reports the BTA Cholesky
 TFLOP/s of Q_c alone, the log-determinant error against the FP64 CPU oracle
