@@ -152,7 +152,10 @@ __device__ __forceinline__ void panel_columns(double (&rd)[16], double (&rp)[16]
 //    L_Jp^T, and row p of the inverse, G_pj = -G_pp T_pj (j < p);
 //  * beside panel p + 1: T_rj += L_rp G_pj for the rows r > p below, and (p =
 //    2) the first 48 rows of G are stored.
-// A panel takes about 2 300 cycles (145 a pivot).  One 4-column panel per wave
+// A panel takes about 2 300 cycles (145 a pivot), by the issue of its 240
+// multiply-adds with a broadcast operand: the reciprocal root's steps laid between
+// them changed nothing, a broadcast move before two plain multiply-adds took 744 us
+// for 711 (32 tiles of the dense entry).  One 4-column panel per wave
 // and 16 hand-overs through LDS took 420 cycles a pivot: the launch of one tile
 // went from 12.7 to 10.0 us, a panel step's launch from 21.6 to 18.0 us, a
 // persistent launch over two blocks of 32 tiles from 783 to 693 us.
