@@ -28,12 +28,6 @@ constexpr int GEMV_T_COLS = 4;
 typedef double v2d __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) double gdouble;
-// Columns of a slice.  Up to ONE columns are one slice: the hand-over to the last
-// workgroup takes longer than the other slices' loads.
-constexpr int ONE = 256;
-__host__ __device__ constexpr int slice_len(int K) {
-  return K <= ONE ? ONE : (K <= 64 * GEMV_KS ? 64 : (K + GEMV_KS - 1) / GEMV_KS);
-}
 template <typename TA> struct Vec;
 template <> struct Vec<double> { typedef v2d type; };
 template <> struct Vec<float> { typedef v4f type; };
@@ -60,7 +54,7 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
   typedef typename Vec<TA>::type vec_t;
   const int rb = blockIdx.x, sl = blockIdx.y;
   if (rb * RB >= g.M) return;
-  const int len = slice_len(g.K);
+  const int len = gemv_slice_len(g.K);
   const int kend = g.tri ? min(g.K, rb * RB + RB) : g.K;
   // A's zeros before its rows' first column are skipped by whole slices and
   // by whole 128 columns of a slice
@@ -71,7 +65,7 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row = rb * RB + lane * V;
   const bool ok = row < g.M;
-  const TA* p = (const TA*)g.A + (ok ? row : 0) + (int64_t)(k0 + wave) * g.lda;
+  const TA* p = (const TA*)g.A + (ok ? row : 0) + (int64_t)k0 * g.lda;
   const int n = k1 - k0;
   // tri: columns from the end of the row's 64 x 64 diagonal tile on count as zero
   const int lim = g.tri ? (row | 63) + 1 - k0 : n;
@@ -80,19 +74,18 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
   for (int r = 0; r < R; ++r)
 #pragma unroll
     for (int v = 0; v < V; ++v) acc[r][v] = 0.0;
-  // the slice's x, R values a column (at most 128 columns a slice, or
-  // ks_len for very wide blocks, staged 128 at a time)
-  const int kb0 = max(klo - k0, 0) & ~127;
-  for (int kb = kb0; kb < n; kb += 128) {
-    const int nb = min(128, n - kb);
+  // the slice's x, R values a column, staged GEMV_STAGE columns at a time (slices
+  // are 64 columns, one of up to 256, or K / GEMV_KS beyond 2048)
+  const int kb0 = max(klo - k0, 0) / GEMV_STAGE * GEMV_STAGE;
+  for (int kb = kb0; kb < n; kb += GEMV_STAGE) {
+    const int nb = min(GEMV_STAGE, n - kb);
     // two batches of columns: the second is in flight while the first is used
     vec_t a[2][UN];
     auto load = [&](vec_t (&d)[UN], int k) {
 #pragma unroll
       for (int u = 0; u < UN; ++u) {
-        const int c = k + 4 * u;
-        d[u] = *(const __attribute__((address_space(1))) vec_t*)(
-            p + (int64_t)(kb + (c + wave < nb ? c : 0)) * g.lda);
+        const int c = gemv_column(k + 4 * u + wave, nb);
+        d[u] = *(const __attribute__((address_space(1))) vec_t*)(p + (int64_t)(kb + c) * g.lda);
       }
     };
     auto use = [&](const vec_t (&d)[UN], int k) {
@@ -174,7 +167,7 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
 
 template <int R>
 __global__ __launch_bounds__(NT) void k_gemv_n(const GemvN* __restrict__ jobs) {
-  __shared__ double xs[128 * R];
+  __shared__ double xs[GEMV_STAGE * R];
   __shared__ double sh[4 * R * 256];
   __shared__ int s_last;
   const GemvN g = jobs[blockIdx.z];
@@ -186,7 +179,7 @@ hipError_t launch_gemv_n(const GemvN* jobs, int count, int max_M, int max_K, int
                          hipStream_t s) {
   if (count <= 0 || max_M <= 0) return hipSuccess;
   // the most slices of any K up to max_K
-  const int max_slices = max_K <= ONE ? 1 : std::min(GEMV_KS, (max_K + 63) / 64);
+  const int max_slices = max_K <= GEMV_ONE ? 1 : std::min(GEMV_KS, (max_K + 63) / 64);
   const dim3 grid((max_M + 127) / 128, max_slices, count);
   if (nrhs > 1) hipLaunchKernelGGL(k_gemv_n<SOLVE_RHS>, grid, dim3(NT), 0, s, jobs);
   else hipLaunchKernelGGL(k_gemv_n<1>, grid, dim3(NT), 0, s, jobs);

@@ -1,9 +1,11 @@
 #pragma once
 #include "common.hpp"
 
+#define DL_GEMV_FN __host__ __device__ inline
+#include "gemv_index.hpp"
+
 namespace dl {
 
-constexpr int GEMV_KS = 32;   // most column slices of a matrix-vector product
 constexpr int SOLVE_RHS = 4;  // right-hand sides of one pass over the factor
 
 // out = beta*base + alpha*A*x, rows [0, split) -> out1/base1 and rows
