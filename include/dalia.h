@@ -29,8 +29,9 @@
  *     DL_ENOMEM, DL_EHIP).  Numerical failure (a non-positive pivot) is
  *     reported through info_dev: 0 = ok, k > 0 = first bad pivot at BTA row
  *     k-1 (LAPACK style); f_obj is then -inf.
- *   - Nothing is allocated after dl_ws_create; no C++ exception crosses the
- *     ABI.
+ *   - No evaluation allocates after dl_ws_create (dl_autotune, dl_ws_force_split
+ *     and the first dl_ws_set_block of a sub-diagonal block may); no C++
+ *     exception crosses the ABI.
  */
 #ifndef DALIA_H
 #define DALIA_H
@@ -389,7 +390,11 @@ dl_status dl_ws_get_block(dl_ws* W, dl_which which, int32_t kind, int32_t t,
  * sub-diagonal block also as its own transpose, so they need symmetric
  * B_t.  DL_ESTATE unless the matrix was assembled since its last
  * factorisation (or for Q_p blocks without DL_WS_KEEP_QP).  Synchronises the
- * stream. */
+ * stream.  A sub-diagonal block (kind 1) may be dense: until the next assembly
+ * the workspace runs launches that make no use of the assembled blocks' zeros.
+ * The first such call builds them and allocates their descriptors (with
+ * DL_WS_SPLITK also partial tiles of their own): DL_ENOMEM, with the workspace
+ * as it was, when there is no room for them. */
 dl_status dl_ws_set_block(dl_ws* W, dl_which which, int32_t kind, int32_t t,
                           const double* in_dev, void* stream);
 

@@ -440,6 +440,11 @@ struct PlanSet {
   Plan qpsum_p;  // log|Q_p| after fac_p of an evaluation that keeps Q_p
   Plan ref_init_p, ref_res_p, ref_corr_p, ref_fin_p, resid_p;
   int32_t* dag_heads = nullptr;  // [4 x launches] task head, finished workgroups, abort
+  // split-k partial tiles, shared by the set's launches.  A set's own: the buffer
+  // grows when a set is built or retuned, and a captured graph of the other set
+  // keeps its address
+  double* partials = nullptr;
+  int64_t partials_cap = 0;    // doubles allocated at `partials`
 };
 
 struct dl_ws : PlanSet {
@@ -458,8 +463,6 @@ struct dl_ws : PlanSet {
   bool sel = false, keep_qp = false, mixed = false;
   bool splitk = false;
   int dag_workers = 0;           // grid of the persistent launches
-  double* partials = nullptr;  // split-k partial tiles (shared by all launches)
-  int64_t partials_cap = 0;    // doubles allocated at `partials`
   int dim_total = 0;
   double* theta_all = nullptr;   // packed theta of all instances
   double* f_all = nullptr;       // [B]
@@ -1455,8 +1458,19 @@ static dl_status use_plans(dl_ws* W, bool dense) {
   std::swap(static_cast<PlanSet&>(*W), W->other);
   W->dense = dense;
   if (W->have_other) return DL_OK;
-  const dl_status st = build_plans(W);
+  const size_t held = W->allocs.size(), bytes = W->bytes;
+  dl_status st = DL_OK;
+  try {
+    st = build_plans(W);
+  } catch (const std::bad_alloc&) {  // the host's lists
+    st = DL_ENOMEM;
+  }
   if (st != DL_OK) {
+    // nothing of the unfinished set is kept
+    if (W->partials) (void)hipFree(W->partials);
+    for (size_t k = held; k < W->allocs.size(); ++k) (void)hipFree(W->allocs[k]);
+    W->allocs.resize(held);
+    W->bytes = bytes;
     std::swap(static_cast<PlanSet&>(*W), W->other);
     W->dense = !dense;
     W->other = PlanSet{};
@@ -1632,7 +1646,7 @@ static dl_status build_plans(dl_ws* W) {
   up(H.comb, W->Dd.comb);
   up(H.res, W->Dd.res);
   up(H.couple, W->Dd.couple);
-  if (W->poisson) {
+  if (W->poisson && !W->d_lap) {  // of the workspace, not of a set
     std::vector<LapJob> lap;
     std::vector<TrialJob> trial;
     std::vector<QuadJob> nquad;
@@ -1658,7 +1672,8 @@ static void ws_free(dl_ws* W) {
   if (W->aux_stream) (void)hipStreamDestroy(W->aux_stream);
   if (W->ev_fork) (void)hipEventDestroy(W->ev_fork);
   if (W->ev_join) (void)hipEventDestroy(W->ev_join);
-  if (W->partials) (void)hipFree(W->partials);
+  for (double* p : {W->partials, W->other.partials})
+    if (p) (void)hipFree(p);
   free_all(W->allocs);
   delete W;
 }
