@@ -134,6 +134,22 @@ DL_DAG_FN bool mid_set(const Task& t, Wait* s) {
   return true;
 }
 
+// The patience of a worker that polls for a counter, in clock ticks.  Only time spent
+// polling counts, at most `step` for each poll: a process that is held off the
+// card between two polls (time slices of other processes, a suspended queue) has
+// not waited, for the workers it waits on were held off with it.
+struct Patience {
+  long long last;       // the clock at the poll before
+  long long spent = 0;
+  // After a poll that found nothing: true once `limit` is spent.
+  DL_DAG_FN bool out(long long now, long long limit, long long step) {
+    const long long d = now - last;
+    spent += d < step ? d : step;
+    last = now;
+    return spent > limit;
+  }
+};
+
 // All tasks of one block in phase order (step j: F(j), S(., j), R(j, .),
 // U(., ., j), A(., ., j)), which is a valid order.  Chained: F(0), and in
 // step j, C(j) in place of S(j+1, j) (it also stands for U(j+1, j+1, j) and

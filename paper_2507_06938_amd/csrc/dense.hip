@@ -624,7 +624,10 @@ hipError_t launch_panel_updates(const PanelTask* tasks, int ntask, int grid,
 // counter is set; the counters themselves are relaxed device-scope atomics.
 
 namespace {
-constexpr long long kDagWaitTicks = 200000000;  // 2 s of the 100 MHz constant clock
+// of the 100 MHz constant clock: 2 s of polling, of which one poll counts 0.1 ms at
+// most (it takes about a microsecond)
+constexpr long long kDagWaitTicks = 200000000;
+constexpr long long kDagPollTicks = 10000;
 
 typedef __attribute__((address_space(1))) int32_t gint;
 __device__ __forceinline__ int dag_load(const int32_t* p) {
@@ -634,16 +637,16 @@ __device__ __forceinline__ void dag_store(int32_t* p, int v) {
   __hip_atomic_store((gint*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// true once *p >= value; false after the time limit, or at once when the
+// true once *p >= value; false after kDagWaitTicks of polling, or at once when the
 // launch has given up (*abort set by a wait that timed out)
 __device__ bool dag_wait(const int32_t* p, int value, int32_t* abort) {
   if (dag_load(p) >= value) return true;
-  const long long t0 = wall_clock64();
+  dag::Patience patience{wall_clock64()};
   for (;;) {
     __builtin_amdgcn_s_sleep(1);
     if (dag_load(p) >= value) return true;
     if (dag_load(abort) != 0) return false;
-    if (wall_clock64() - t0 > kDagWaitTicks) {
+    if (patience.out(wall_clock64(), kDagWaitTicks, kDagPollTicks)) {
       dag_store(abort, 1);
       return false;
     }
