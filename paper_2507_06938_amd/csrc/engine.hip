@@ -102,6 +102,7 @@ struct Descs {
   int dag_launches = 0;
   // first word and length of the list over blocks of given sizes (and inverses)
   std::map<std::pair<std::vector<int>, std::vector<char>>, std::pair<int, int>> dag_lists;
+  dag::Schedules schedules;     // while the plans are built
   std::vector<MiscJob> misc;
   std::vector<GemvN> gn;
   std::vector<GemvT> gt;
@@ -198,7 +199,7 @@ static void merge(const std::vector<std::vector<Step>>& seqs, Descs& D,
         // launches over blocks of the same sizes share their list
         auto [at, fresh] = D.dag_lists.try_emplace({nbks, inv});
         if (fresh) {
-          std::vector<uint64_t> tl = dag::launch_list(nbks, inv);
+          std::vector<uint64_t> tl = dag::launch_list(nbks, inv, true, &D.schedules);
           tl = dag::join(tl, dag::join_count(tl.size(), *std::max_element(nbks.begin(), nbks.end())));
           at->second = {(int)D.dagt.size(), (int)tl.size()};
           for (uint64_t w : tl) {
@@ -1594,6 +1595,7 @@ static dl_status build_plans(dl_ws* W) {
     append(W->eval_p, W->resid_p);
   }
   append(W->eval_p, W->post_p);
+  H.schedules = dag::Schedules{};
   // split-k partial tiles: the largest need of any launch, for either tile
   int64_t pmax = 0;
   for (const Launch& L : W->table) {
