@@ -598,14 +598,23 @@ extern "C" dl_status dl_mlp_params(dl_mlp* N, float** params_dev, float** grads_
   return DL_OK;
 }
 
+// Do the n floats at a and the m floats at b share memory?
+static bool overlap(const float* a, int64_t n, const float* b, int64_t m) {
+  return a && b && a < b + m && b < a + n;
+}
+
 extern "C" dl_status mlp_fwd(dl_mlp* N, const float* X, int32_t n, float* yhat,
                              void* stream) {
   if (!N || !X || n <= 0 || n > N->max_batch) return DL_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   if (N->whole) {
+    // outputs over the inputs: a workgroup's would reach rows not yet read
+    const bool over = overlap(X, (int64_t)n * N->sizes[0], yhat, n);
     hipLaunchKernelGGL(k_mlp_fwd, dim3((n + MLP_ROWS - 1) / MLP_ROWS), dim3(MLP_NT), N->lds,
-                       s, N->args, X, n, yhat);
+                       s, N->args, X, n, over ? nullptr : yhat);
     DL_HIP_CHECK(hipGetLastError());
+    if (over)
+      DL_HIP_CHECK(hipMemcpyAsync(yhat, N->yhat, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
     N->last_n = n;
     return DL_OK;
   }
@@ -647,6 +656,12 @@ extern "C" dl_status mlp_bwd(dl_mlp* N, const float* dy, int32_t n, float* dX,
   hipStream_t s = (hipStream_t)stream;
   const int L = (int)N->sizes.size() - 1;
   if (N->whole) {
+    if (overlap(dy, n, dX, (int64_t)n * N->sizes[0])) {
+      // dX over dy, which the last layer's gradients are formed from as well
+      DL_HIP_CHECK(hipMemcpyAsync(N->G[L - 1], dy, sizeof(float) * n, hipMemcpyDeviceToDevice,
+                                  s));
+      dy = N->G[L - 1];
+    }
     if (L > 1 || dX) {
       hipLaunchKernelGGL(k_mlp_bwd_rows, dim3((n + MLP_ROWS - 1) / MLP_ROWS), dim3(MLP_NT),
                          N->lds, s, N->args, dy, n, dX);
