@@ -568,10 +568,12 @@ extern "C" dl_status dl_mlp_create(const int32_t* sizes, int32_t nsizes,
     }
     N->tiles.first[L] = tiles;
     N->lds = sizeof(__bf16) * 2 * MLP_ROWS * (size_t)a.ld;
+    // the limit is the function's, not the network's: always the widest one's
+    constexpr int most = sizeof(__bf16) * 2 * MLP_ROWS * (MLP_WMAX + MLP_PAD);
     if (N->lds > 65536)
       for (const void* f : {(const void*)k_mlp_fwd, (const void*)k_mlp_bwd_rows})
         if (st == DL_OK && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)N->lds) != hipSuccess)
+                                               most) != hipSuccess)
           st = DL_EHIP;
   }
   if (st != DL_OK) {

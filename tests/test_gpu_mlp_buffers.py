@@ -37,3 +37,22 @@ def test_buffers_that_share_memory(sizes):
         torch.cuda.synchronize()
         assert torch.equal(buf.view(n, d), dX0), shift
         assert np.array_equal(net.grads.cpu().numpy(), g0.cpu().numpy()), shift
+
+
+def test_a_narrower_network_leaves_a_wide_one_its_lds():
+    """The kernels' limit of dynamic LDS belongs to the function: networks of
+    several widths beyond 64 KB of it, created in any order."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2507_06938_amd import dalia as D
+    X = torch.randn(20, 3, device="cuda")
+    dy = torch.randn(20, device="cuda")
+    nets = [D.MLP((3, h, 1), max_batch=64) for h in (2048, 1100, 1030)]
+    for net in nets:
+        net.params.normal_(0, 0.1)
+    want = [(net.forward(X).clone(), net.backward(dy, want_dx=True).clone()) for net in nets[::-1]]
+    nets.append(D.MLP((3, 1040, 1), max_batch=64))
+    got = [(net.forward(X).clone(), net.backward(dy, want_dx=True).clone()) for net in nets[2::-1]]
+    for a, b in zip(want, got):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+        assert torch.isfinite(a[0]).all() and a[0].abs().max() > 0
