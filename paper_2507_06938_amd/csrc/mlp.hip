@@ -15,9 +15,10 @@
 // (21 us for one row, 25 for 930) is one compute unit's fetch of the weights
 // (540 KB) beyond its XCD's L2; staging whole rows of W through LDS, prefetching
 // the next layer's block in registers (spills) and the arguments in device
-// memory did not shorten it.  Networks wider than MLP_WMAX or
-// deeper than MLP_LMAX (their rows do not fit LDS, their layers not the
-// kernels' arguments) take one launch per product.
+// memory did not shorten it.  Wide layers and large batches take one launch per
+// product where that is ahead (whole_fwd, whole_bwd), as do networks wider than
+// MLP_WMAX or deeper than MLP_LMAX (their rows do not fit LDS, their layers not the
+// kernels' arguments).
 #include <math.h>
 #include <stdint.h>
 
@@ -493,7 +494,8 @@ struct dl_mlp {
   float *w = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   std::vector<float*> Z, Hs;  // pre-activations and layer inputs (H[0] = X copy)
   std::vector<float*> G;      // d loss / d Z_k (max_batch x out_k; the last: none)
-  bool whole = false;         // whole passes (MLP_WMAX, MLP_LMAX)
+  bool whole = false;         // whole passes possible (MLP_WMAX, MLP_LMAX)
+  int widest = 0;             // most outputs of a layer
   MlpArgs args{};
   MlpTiles tiles{};
   size_t lds = 0;             // bytes of k_mlp_fwd and k_mlp_bwd_rows
@@ -522,6 +524,7 @@ extern "C" dl_status dl_mlp_create(const int32_t* sizes, int32_t nsizes,
     off += sizes[k + 1];
   }
   for (int k = 0; k < nsizes; ++k) wmax = std::max(wmax, sizes[k]);
+  for (int k = 1; k < nsizes; ++k) N->widest = std::max(N->widest, sizes[k]);
   N->nparam = off;
   dl_status st = DL_OK;
   auto A = [&](size_t bytes, void** p) {
@@ -600,6 +603,50 @@ extern "C" dl_status dl_mlp_params(dl_mlp* N, float** params_dev, float** grads_
   return DL_OK;
 }
 
+// Which passes one launch takes, by the widest layer and the rows (us, one launch /
+// one per product; networks of three equal hidden layers; every other size between
+// lies between).
+//
+// Forward, a workgroup of 16 waves goes through 16 rows, 256 columns at a time, and
+// its time is its own fetch of the weights until 4096 rows fill the card:
+//   * up to 512 columns it is always ahead there (1 row 65 / 110, 4096 rows 73 / 172);
+//   * wider, the fetch is longer than the launches it saves unless the rows keep the
+//     product launches long: 640 columns 1 row 149 / 133, 32 rows 152 / 155; 1024
+//     columns 32 rows 240 / 230, 64 rows 240 / 275; 1280 columns 512 rows 368 / 359,
+//     1024 rows 368 / 383; 2048 columns 901 / 426 and still behind at 16384 rows;
+//   * a round of 256 columns that is not full costs a full one: 896 columns 1024 rows
+//     261 / 260, 4096 rows 262 / 319;
+//   * from 4096 rows on the 64 x 64 tiles of the product launches read W less often:
+//     8192 rows 384 columns 155 / 162, 640 columns 315 / 266; 16384 rows 64 columns
+//     46 / 48, 384 columns 298 / 213, 768 columns 565 / 593; 65536 rows 64 columns
+//     162 / 91, 256 columns 365 / 374, 512 columns 1075 / 1012.
+static bool whole_fwd(const dl_mlp* N, int n) {
+  if (!N->whole) return false;
+  const int w = N->widest, round = (w + 255) / 256 * 256;
+  const bool fills = 10 * w > 9 * round;
+  if (n > 16384) return fills && round == 256;
+  if (n > 4096) return w <= 64 || (n <= 8192 && w <= 512) || (fills && round <= 768);
+  switch (round / 256) {
+    case 1: case 2: return true;
+    case 3: return fills || n > 16;
+    case 4: return n > (fills ? 32 : 1024);
+    case 5: return n > (fills ? 512 : 2048);
+    case 6: return fills && n > 2048;
+    default: return false;
+  }
+}
+
+// Backward, where the weights' launch sums over rows and the product launches of the
+// column sums are serial: behind only where a few rows meet wide layers (1280 columns,
+// 1 row 254 / 223, 64 rows 306 / 359; 2048 columns, 1 row 581 / 426, 64 rows 667 / 535,
+// 256 rows 650 / 799; with d loss / d X 1280 columns 1 row 257 / 291, 2048 columns 16
+// rows 663 / 557, 64 rows 676 / 707).
+static bool whole_bwd(const dl_mlp* N, int n, bool dx) {
+  const int w = N->widest;
+  if (dx) return N->whole && (w <= 1792 || n > 32);
+  return N->whole && (w <= 1152 || n > (w > 1664 ? 128 : 32));
+}
+
 // Do the n floats at a and the m floats at b share memory?
 static bool overlap(const float* a, int64_t n, const float* b, int64_t m) {
   return a && b && a < b + m && b < a + n;
@@ -609,7 +656,7 @@ extern "C" dl_status mlp_fwd(dl_mlp* N, const float* X, int32_t n, float* yhat,
                              void* stream) {
   if (!N || !X || n <= 0 || n > N->max_batch) return DL_EINVAL;
   hipStream_t s = (hipStream_t)stream;
-  if (N->whole) {
+  if (whole_fwd(N, n)) {
     // outputs over the inputs: a workgroup's would reach rows not yet read
     const bool over = overlap(X, (int64_t)n * N->sizes[0], yhat, n);
     hipLaunchKernelGGL(k_mlp_fwd, dim3((n + MLP_ROWS - 1) / MLP_ROWS), dim3(MLP_NT), N->lds,
@@ -657,7 +704,7 @@ extern "C" dl_status mlp_bwd(dl_mlp* N, const float* dy, int32_t n, float* dX,
   if (!N || !dy || n != N->last_n) return DL_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   const int L = (int)N->sizes.size() - 1;
-  if (N->whole) {
+  if (whole_bwd(N, n, dX != nullptr)) {
     if (overlap(dy, n, dX, (int64_t)n * N->sizes[0])) {
       // dX over dy, which the last layer's gradients are formed from as well
       DL_HIP_CHECK(hipMemcpyAsync(N->G[L - 1], dy, sizeof(float) * n, hipMemcpyDeviceToDevice,
