@@ -75,7 +75,7 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
 #pragma unroll
     for (int v = 0; v < V; ++v) acc[r][v] = 0.0;
   // the slice's x, R values a column, staged GEMV_STAGE columns at a time (slices
-  // are 64 columns, one of up to 256, or K / GEMV_KS beyond 2048)
+  // are 64 columns, or K / GEMV_KS beyond 2048)
   const int kb0 = max(klo - k0, 0) / GEMV_STAGE * GEMV_STAGE;
   for (int kb = kb0; kb < n; kb += GEMV_STAGE) {
     const int nb = min(GEMV_STAGE, n - kb);
@@ -179,7 +179,7 @@ hipError_t launch_gemv_n(const GemvN* jobs, int count, int max_M, int max_K, int
                          hipStream_t s) {
   if (count <= 0 || max_M <= 0) return hipSuccess;
   // the most slices of any K up to max_K
-  const int max_slices = max_K <= GEMV_ONE ? 1 : std::min(GEMV_KS, (max_K + 63) / 64);
+  const int max_slices = std::min(GEMV_KS, (max_K + 63) / 64);
   const dim3 grid((max_M + 127) / 128, max_slices, count);
   if (nrhs > 1) hipLaunchKernelGGL(k_gemv_n<SOLVE_RHS>, grid, dim3(NT), 0, s, jobs);
   else hipLaunchKernelGGL(k_gemv_n<1>, grid, dim3(NT), 0, s, jobs);
