@@ -1178,8 +1178,10 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q, int n
 // in units of b^3, Z takes 1 and the lower half of S = I + [C; R]^T Z 1/3; with U
 // the lower half of S and half its diagonal, X = M + M^T, M = G^T (U G), takes
 // 1/3 and 2/3: 7/3 where W, X W, G^T G and W^T X W took 4.  (With more responses
-// C fills up and the form saves nothing.)  The sums it forms are of the same
-// size, and its variances' error against 64 bits is the factor's either way.
+// C fills up and the form saves nothing.)  Its variances are no further off: at 20 x
+// 20 to 45 x 45 nodes, one chain and two, their error against 80-bit arithmetic on the
+// same matrix was 0.85 to 0.94 times the general form's (36 x 36, 4 steps: 4.0e-15
+// against 4.5e-15).
 static void seq_selinv_s(dl_ws* W, Inst& I, std::vector<Step>& q) {
   const ModelDev& m = I.m;
   const int bp = m.bp, ap = m.ap;
@@ -1680,13 +1682,15 @@ static void ws_free(dl_ws* W) {
   delete W;
 }
 
-// Smallest padded block size of the selected inversion's symmetric form: it has
-// two launches more a step, and below this size those cost more than the
-// products it saves (f_obj with variances, 12 steps: 24 x 24 nodes 4.25 ms against
-// 3.60, 30 x 30 6.65 / 6.04, 34 x 34 with two chains 6.05 / 5.95; but 9 points of
-// 30 x 30 15.1 / 17.6, and 45 x 45, 20 steps, 22.8 / 27.4).  By the block size
-// alone, so that an evaluation does not depend on the batch it is part of.
-constexpr int SELINV_S_MIN = 1280;
+// Smallest padded block size of the selected inversion's symmetric form, with one
+// chain and two: it has two launches more a step, and below these sizes those cost
+// more than the products it saves (12 steps, general / symmetric form in us: one
+// chain 34 x 34 nodes 2669 / 3285, 37 x 37 3507 / 3910, 38 x 38 4403 / 4303, 40 x 40
+// 5075 / 4811, 45 x 45 9458 / 7351; two chains 30 x 30 1401 / 1576, 32 x 32 1743 /
+// 1733, 34 x 34 2334 / 2182, 38 x 38 3763 / 3066).  A batch would take it earlier (four
+// instances of 30 x 30 with f_obj 9654 / 9144, of 36 x 36 19858 / 14821), but an
+// evaluation does not depend on the batch it is part of.
+constexpr int SELINV_S_ONE = 1472, SELINV_S_TWO = 1152;
 
 // Storage layout of instance I (host fields only) for the workspace flags.
 static void inst_layout(const dl_ws* W, Inst& I, const dl_model* model, bool two_sided) {
@@ -1709,7 +1713,7 @@ static void inst_layout(const dl_ws* W, Inst& I, const dl_model* model, bool two
   I.two = two_sided && m.nt >= 4;
   I.mid = I.two ? (m.nt + 1) / 2 : m.nt - 1;
   I.poisson = W->poisson;
-  I.sel_s = !I.mixed && m.nv == 1 && m.bp >= SELINV_S_MIN;
+  I.sel_s = !I.mixed && m.nv == 1 && m.bp >= (I.two ? SELINV_S_TWO : SELINV_S_ONE);
 }
 
 // One counter per 128 rows of the largest matrix-vector product.

@@ -1,8 +1,8 @@
 """Selected inversion of large univariate blocks, whose steps multiply triangles
-(X = G^T (I + [C; R]^T X [C; R]) G): the smallest padded block size that takes
-this form and one with padding rows, one chain and two, with and without arrow
-rows, one time step, and a caller's dense sub-diagonal block, all against a dense
-inverse.  The tolerance allows for cond(Q) eps (about 1e5 here)."""
+(X = G^T (I + [C; R]^T X [C; R]) G): the smallest padded block sizes that take
+this form with one chain (38 x 38 nodes) and with two (33 x 33) and the general form
+below them, with and without arrow rows, one time step, and a caller's dense
+sub-diagonal block, all against a dense inverse.  The tolerance allows for cond(Q) eps (about 1e5 here)."""
 import numpy as np
 import pytest
 
@@ -25,7 +25,10 @@ def D():
 
 @pytest.mark.parametrize("nx,nt,nr,two,dense", [(36, 3, 2, False, False), (36, 4, 0, True, False),
                                                 (37, 4, 1, True, False), (36, 1, 1, False, False),
-                                                (36, 1, 0, False, False), (36, 2, 1, False, True)])
+                                                (36, 1, 0, False, False), (36, 2, 1, False, True),
+                                                (38, 3, 2, False, False), (38, 1, 0, False, False),
+                                                (38, 2, 1, False, True), (33, 4, 0, True, False),
+                                                (32, 4, 2, True, False), (33, 4, 1, True, True)])
 def test_variances_of_large_blocks(D, nx, nt, nr, two, dense):
     wl = W.scaled("selform", nx, nt, 1, nr, 700, seed=13)
     ref = OF.fobj_parts(wl, wl.theta, return_factors=True)
