@@ -188,6 +188,8 @@ hipError_t launch_potrf_tiles(const PotrfTileArgs* args_dev, int count,
 // row j of the inverse reads L(j, j-1), G(j, j-1) stays in stage and step j+1
 // moves it into place.  The closing launch (last = 1, j = nbk-1) computes
 // the inverse's last row only; its G(nbk-1, nbk-2) is left in stage.
+// PANEL_L: L itself, without the inverse; PANEL_DIAG: L, its diagonal tiles inverted.
+enum : int { PANEL_L = 0, PANEL_INVERSE = 1, PANEL_DIAG = 2 };
 struct PanelTask {
   double* A;
   int64_t ld;
@@ -198,18 +200,18 @@ struct PanelTask {
   double* stage;       // tile (r, c), c < r: ((r (r-1)) / 2 + c) * 4096 (ld 64)
   int32_t j, nbk;
   int32_t last;
-  int32_t inv;         // 0: no inverse; the diagonal tiles then hold L, not G
+  int32_t inv;         // PANEL_L, ..
   int32_t beg[5];      // first workgroup of this task in each role segment
   int32_t tot[5];      // workgroups of each role in the launch (every task)
 };
 // Fill beg/tot; return the grid size.
 int finalize_panels(PanelTask* t, int n);
 // The panel steps of one n x n block (nbk = n / 64 >= 2 tiles; tile 0 factored
-// and panel 0 solved before the first): nbk - 1 of them, and with the inverse
+// and panel 0 solved before the first): nbk - 1 of them, and with PANEL_INVERSE
 // the closing one, after which tile (nbk-1, nbk-2) of G is still to be copied
-// from `stage`.  tmp: the side ring and the inverse's accumulators, 2 + nbk (nbk -
+// from `stage`.  tmp: the side ring, and the inverse's accumulators: 2 + nbk (nbk -
 // 1) / 2 tiles.  Fills t[j] and its grid; returns the number of launches.
-int panel_steps(int64_t n, double* A, int64_t lda, bool inv, double* logdiag, int64_t* info,
+int panel_steps(int64_t n, double* A, int64_t lda, int inv, double* logdiag, int64_t* info,
                 double* tmp, PanelTask* t, int* grid);
 hipError_t launch_panel_updates(const PanelTask* tasks_dev, int ntask, int grid,
                                 hipStream_t s);

@@ -528,7 +528,7 @@ __global__ __launch_bounds__(POTRF_NT) void k_panel_update(const PanelTask* __re
   __syncthreads();
   const bool own = role == 0;
   potrf_body(nullptr, 0, S1, S2, own ? dst : nullptr, side ? NB : T.ld, nullptr,
-             own ? T.logdiag : nullptr, own ? T.info : nullptr, T.row0, own && !T.inv ? 0 : 1);
+             own ? T.logdiag : nullptr, own ? T.info : nullptr, T.row0, own && T.inv == PANEL_L ? 0 : 1);
   if (own) return;
   // G staged as S1[k][r] = G(r, k) (zero above the diagonal); the updated
   // panel tile as S0[c][m] = A(m, c)
@@ -558,8 +558,8 @@ int finalize_panels(PanelTask* t, int n) {
       const int m = nbk - j - 1;  // trailing tile rows (>= 1)
       cnt[0] = 1;
       cnt[1] = m - 1;
-      cnt[2] = t[i].inv ? j : 0;
-      cnt[3] = t[i].inv ? (nbk - 1 - j) * j : 0;
+      cnt[2] = t[i].inv == PANEL_INVERSE ? j : 0;
+      cnt[3] = t[i].inv == PANEL_INVERSE ? (nbk - 1 - j) * j : 0;
       cnt[4] = m * (m - 1) / 2;
     }
     for (int k = 0; k < 5; ++k) {
@@ -574,9 +574,9 @@ int finalize_panels(PanelTask* t, int n) {
   return grid;
 }
 
-int panel_steps(int64_t n, double* A, int64_t lda, bool inv, double* logdiag, int64_t* info,
+int panel_steps(int64_t n, double* A, int64_t lda, int inv, double* logdiag, int64_t* info,
                 double* tmp, PanelTask* t, int* grid) {
-  const int nbk = (int)(n / NB), steps = inv ? nbk : nbk - 1;
+  const int nbk = (int)(n / NB), steps = inv == PANEL_INVERSE ? nbk : nbk - 1;
   for (int j = 0; j < steps; ++j) {
     PanelTask& p = t[j];
     p = PanelTask{};

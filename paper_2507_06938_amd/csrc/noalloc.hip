@@ -155,7 +155,7 @@ extern "C" dl_status dl_dpotrf_noalloc(int64_t n, double* A, int64_t lda,
     solve = task(A + 64, lda, inv ? A : Gd, inv ? lda : 64, A + 64, lda, (int)n - 64, 64, 64,
                  F_TB | F_BETA0, 1.0, 0.0);
     units = finalize_tasks(&solve, 1);
-    nsteps = panel_steps(n, A, lda, inv, logdiag, info_dev, temp, steps, grid);
+    nsteps = panel_steps(n, A, lda, inv ? PANEL_INVERSE : PANEL_L, logdiag, info_dev, temp, steps, grid);
     if (inv) post = last_inverse_tile(n, A, lda, temp);
   }
   SumJob sj{};

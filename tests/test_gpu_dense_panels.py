@@ -55,3 +55,29 @@ def test_panel_steps(D, entry, inverse, n):
     assert getattr(D.lib(), entry)(*args) == 0
     torch.cuda.synchronize()
     assert int(info[0]) == n - 2
+
+
+@pytest.mark.parametrize("n", [4096, 4160, 4416])
+def test_inverse_beside_and_after_the_factor(D, n):
+    """The largest block whose inverse is formed beside the factor, and the first
+    beyond it (an odd number of tiles: halves of unequal size), against LAPACK."""
+    g = torch.Generator(device="cpu").manual_seed(n)
+    M = torch.randn(n, n, generator=g, dtype=torch.float64)
+    S = (M @ M.T / n + 0.1 * torch.eye(n, dtype=torch.float64))  # cond about 40
+    lda = n + 3
+    A = torch.full((n, lda), 7.0, dtype=torch.float64)
+    A[:, :n] = S
+    A = A.cuda()
+    ld = torch.zeros(1, dtype=torch.float64, device="cuda")
+    info = torch.full((1,), 5, dtype=torch.int64, device="cuda")
+    assert D.lib().dl_dpotrf(n, D._ptr(A), lda, 1, D._ptr(ld), D._ptr(info), D._stream()) == 0
+    torch.cuda.synchronize()
+    assert int(info[0]) == 0
+    X = A[:, :n].T.cpu()
+    assert torch.all(A[:, n:] == 7.0)
+    assert torch.all(torch.triu(X, 1) == 0)
+    L = torch.linalg.cholesky(S)
+    want = torch.linalg.solve_triangular(L, torch.eye(n, dtype=torch.float64), upper=False)
+    tol = 4 * n * np.finfo(float).eps * 40
+    assert (X - want).abs().max() <= tol * want.abs().max()
+    assert abs(ld.item() - 2 * torch.log(torch.diagonal(L)).sum().item()) <= tol * n
