@@ -162,7 +162,7 @@ hipError_t launch_theta_coeffs(const ThetaJob* jobs, int count, hipStream_t s) {
 
 // ---- a2: sparse -> dense BTA assembly --------------------------------------------
 //
-// The dense blocks are cleared by streaming stores, then a wave per column c of
+// The dense blocks are cleared first, then a wave per column c of
 // time step t writes what is in it: the stencil's entries of the diagonal block
 // D_t (its lower triangle) and of the sub-diagonal block B_t of rows t+1, and for
 // Q_c the observation terms tau_j w w^T (Eq. 4; d_row w w^T with the per-row
@@ -175,18 +175,21 @@ hipError_t launch_theta_coeffs(const ThetaJob* jobs, int count, hipStream_t s) {
 // model took 1.60 ms (now 0.47) and 9 of a 30 x 30 one 2.20 (1.19).
 
 // b_stencil: only the entries of B_t are written, its zeros are not cleared.
-__global__ __launch_bounds__(256) void k_assemble_clear(const AsmJob* __restrict__ jobs) {
+// Launches that clear more than the 256 MB of the last cache level store past it: 45 x
+// 45 nodes, 20 steps, Q_c 375 -> 326 us, with a kept Q_p 605 -> 549 (built and written
+// column by column in LDS 485 and 625); what fits is faster to fill in next when the
+// zeros stay there (36 x 36, 8 steps 70 / 74).
+template <bool PAST>
+__device__ __forceinline__ void clear_step(const AsmJob& J, int64_t bp, int64_t ap) {
   typedef double v2d __attribute__((ext_vector_type(2)));
-  const AsmJob J = jobs[blockIdx.z];
-  const int64_t bp = J.m->bp, ap = J.m->ap;
-  const int tl = blockIdx.y;
-  if (tl >= J.nt) return;
   const AssembleOut& o = J.o;
+  const int tl = blockIdx.y;
   auto clear = [&](void* base, int64_t bytes) {  // a multiple of 16
     v2d* p = (v2d*)base;
     const int64_t n = bytes / 16, stride = (int64_t)gridDim.x * 256;
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += stride)
-      p[e] = (v2d){0.0, 0.0};
+      if constexpr (PAST) __builtin_nontemporal_store((v2d){0.0, 0.0}, &p[e]);
+      else p[e] = (v2d){0.0, 0.0};
   };
   const int64_t eb = o.b32 ? 4 : 8;
   if (o.Dp) clear(o.Dp + tl * o.dp_stride, bp * bp * 8);
@@ -195,6 +198,18 @@ __global__ __launch_bounds__(256) void k_assemble_clear(const AsmJob* __restrict
     if (o.Bp) clear((char*)o.Bp + tl * o.bp_stride * eb, bp * bp * eb);
     if (o.BRc) clear((char*)o.BRc + tl * o.brc_stride * eb, (bp + ap) * bp * eb);
   }
+}
+
+__global__ __launch_bounds__(256) void k_assemble_clear(const AsmJob* __restrict__ jobs) {
+  const AsmJob J = jobs[blockIdx.z];
+  const int64_t bp = J.m->bp, ap = J.m->ap;
+  if ((int)blockIdx.y >= J.nt) return;
+  const AssembleOut& o = J.o;
+  const int64_t eb = o.b32 ? 4 : 8;
+  int64_t step = ((o.Dp ? 1 : 0) + (o.Dc ? 1 : 0)) * bp * bp * 8;  // bytes per time step
+  if (!o.b_stencil) step += ((o.Bp ? bp : 0) + (o.BRc ? bp + ap : 0)) * bp * eb;
+  if (step * J.nt * gridDim.z > (256 << 20)) clear_step<true>(J, bp, ap);
+  else clear_step<false>(J, bp, ap);
 }
 
 __device__ __forceinline__ void wave_fence() {  // LDS written by one lane, read by others
