@@ -477,13 +477,16 @@ dl_status dl_dpotrf_noalloc(int64_t n, double* A_dev, int64_t lda,
  * choices needing more than 4 GiB of them are not tried).
  * Synchronises the stream; the
  * workspace's matrices must be re-assembled afterwards (fobj_eval always
- * does).  Call before the first evaluation of a DL_WS_GRAPH workspace. */
+ * does).  Call before the first evaluation of a DL_WS_GRAPH workspace.  The
+ * launches for a caller's sub-diagonal blocks (dl_ws_set_block) are timed too
+ * when they are built; built later, they take the choices of their shapes that
+ * were timed.  dl_ws_tile_counts counts the launches of the evaluations. */
 dl_status dl_autotune(dl_ws* ws, const char* cache_path, void* stream);
 dl_status dl_ws_tile_counts(const dl_ws* ws, int64_t* n64, int64_t* n128);
 /* Set the tile (64 or 128) of every matrix-product launch, overriding the
  * default and any tuned choice; each launch keeps its split-k setting
- * (measurement and tests).  DL_EINVAL for
- * other sizes, DL_ESTATE once a graph has been captured. */
+ * (measurement and tests).  Like dl_ws_force_split it holds for the launches of
+ * dl_ws_set_block as well, built before or after.  DL_EINVAL for other sizes, DL_ESTATE once a graph has been captured. */
 dl_status dl_ws_force_tile(dl_ws* ws, int32_t tile);
 /* Split the k range of every FP64 matrix-product launch into pieces of
  * ksplit (a multiple of 16, at least 64; cut at absolute multiples, so

@@ -19,7 +19,11 @@
 #include <algorithm>
 #include <cmath>
 #include <map>
+#include <fstream>
 #include <new>
+#include <sstream>
+#include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "couple.hpp"
@@ -427,6 +431,13 @@ struct Inst {
   double *tpart = nullptr, *alpha = nullptr, *out4 = nullptr;
 };
 
+// Tile size and split k of one matrix-product launch.
+struct TileChoice {
+  int tile = 64;
+  bool split = false;
+  int ksplit = GEMM_KSPLIT;
+};
+
 // The launches of a workspace's plans and their descriptors.
 struct PlanSet {
   Descs H;
@@ -457,6 +468,10 @@ struct dl_ws : PlanSet {
   bool caller_b[2] = {false, false};  // Q_p / Q_c holds a caller's sub-diagonal block
   PlanSet other;
   bool have_other = false;
+  // what dl_ws_force_tile / dl_ws_force_split (0 / -1: never called) and dl_autotune
+  // chose, for the set that is built later
+  int forced_tile = 0, forced_split = -1;
+  std::unordered_map<std::string, TileChoice> tuned;  // by launch signature
   std::vector<Inst> inst;
   std::vector<void*> allocs;
   size_t bytes = 0;
@@ -1456,6 +1471,7 @@ static void append(Plan& dst, const Plan& src) {
 // Make the plans for dense (caller's) or assembled sub-diagonal blocks of Q_c
 // or Q_p the active ones.
 static dl_status build_plans(dl_ws* W);
+static dl_status apply_choices(dl_ws* W);
 static dl_status use_plans(dl_ws* W, bool dense) {
   if (W->dense == dense) return DL_OK;
   std::swap(static_cast<PlanSet&>(*W), W->other);
@@ -1465,6 +1481,7 @@ static dl_status use_plans(dl_ws* W, bool dense) {
   dl_status st = DL_OK;
   try {
     st = build_plans(W);
+    if (st == DL_OK) st = apply_choices(W);
   } catch (const std::bad_alloc&) {  // the host's lists
     st = DL_ENOMEM;
   }
@@ -2678,11 +2695,6 @@ extern "C" dl_status dl_ws_profile_end(dl_ws* W, double* ms, int64_t* launches,
 // rebuilt by the next assembly) and the faster one is kept for every launch
 // of that signature.  Choices are cached in a text file, one line per
 // signature, so later workspaces of the same shapes skip the measurement.
-#include <fstream>
-#include <sstream>
-#include <string>
-#include <unordered_map>
-
 static std::string gemm_signature(const dl_ws* W, const Launch& L) {
   std::ostringstream o;
   o << "gfx950 " << (L.kind == OP_GEMM32 ? "gemm32" : "gemm") << " cat" << L.cat
@@ -2730,12 +2742,43 @@ static int launch_ksplit(const dl_ws* W, const Launch& L) {
 // choices needing more are not tried.
 constexpr int64_t kSplitBudgetDoubles = (int64_t)4 << 27;  // 4 GiB
 
-// One tuned choice of a matrix-product launch.
-struct TileChoice {
-  int tile = 64;
-  bool split = false;
-  int ksplit = GEMM_KSPLIT;
-};
+// Do f for the active plan set and for the other one, if it is built.
+template <typename F>
+static dl_status each_set(dl_ws* W, F f) {
+  dl_status st = f();
+  if (!W->have_other || st != DL_OK) return st;
+  std::swap(static_cast<PlanSet&>(*W), W->other);
+  st = f();
+  std::swap(static_cast<PlanSet&>(*W), W->other);
+  return st;
+}
+
+// The forced and the tuned choices for every matrix-product launch of the active set
+// (the others keep theirs).
+static dl_status apply_choices(dl_ws* W) {
+  for (Launch& L : W->table) {
+    if (L.kind != OP_GEMM && L.kind != OP_GEMM32) continue;
+    TileChoice c{L.tile, launch_split(W, L), launch_ksplit(W, L)};
+    if (W->forced_tile > 0) c.tile = W->forced_tile;
+    if (W->forced_split >= 0 && L.kind == OP_GEMM) {
+      c.split = W->forced_split > 0;
+      c.ksplit = W->forced_split > 0 ? W->forced_split : GEMM_KSPLIT;
+    }
+    if (auto it = W->tuned.find(gemm_signature(W, L)); it != W->tuned.end()) {
+      c.tile = it->second.tile;
+      if (L.kind == OP_GEMM) {
+        c.split = it->second.split;
+        c.ksplit = it->second.ksplit;
+      }
+    }
+    if (L.tile == c.tile && launch_split(W, L) == c.split &&
+        (!c.split || launch_ksplit(W, L) == c.ksplit))
+      continue;
+    if (const dl_status st = retile(W, L, c.tile, c.split, nullptr, c.ksplit); st != DL_OK)
+      return st;
+  }
+  return DL_OK;
+}
 
 extern "C" dl_status dl_autotune(dl_ws* W, const char* cache_path, void* stream) {
   if (!W) return DL_EINVAL;
@@ -2766,62 +2809,67 @@ extern "C" dl_status dl_autotune(dl_ws* W, const char* cache_path, void* stream)
   hipEvent_t e0, e1;
   DL_HIP_CHECK(hipEventCreate(&e0));
   DL_HIP_CHECK(hipEventCreate(&e1));
-  dl_status st = DL_OK;
-  for (Launch& L : W->table) {
-    if ((L.kind != OP_GEMM && L.kind != OP_GEMM32) || st != DL_OK) continue;
-    const std::string sig = gemm_signature(W, L);
-    auto it = best.find(sig);
-    if (it == best.end()) {
-      // candidates: both tiles, unsplit and (FP64 products with a k extent
-      // above a piece length) split into pieces of 512 or 256
-      int kmax = 0;
-      if (L.kind == OP_GEMM)
-        for (int i = 0; i < L.count; ++i) kmax = std::max(kmax, W->H.gemm[L.off + i].K);
-      std::vector<TileChoice> cand;
-      for (int tile : {64, 128}) {
-        cand.push_back({tile, false, GEMM_KSPLIT});
-        for (int ks : {512, 256}) {
-          if (kmax <= ks) continue;
-          // partial tiles of this choice: skipped above the budget
-          std::vector<GemmTask> tmp(W->H.gemm.begin() + L.off,
-                                    W->H.gemm.begin() + L.off + L.count);
-          for (auto& t : tmp) {
-            t.flags |= F_SPLIT;
-            t.ksplit = ks;
+  auto tune = [&] {
+    dl_status st = DL_OK;
+    for (Launch& L : W->table) {
+      if ((L.kind != OP_GEMM && L.kind != OP_GEMM32) || st != DL_OK) continue;
+      const std::string sig = gemm_signature(W, L);
+      auto it = best.find(sig);
+      if (it == best.end()) {
+        // candidates: both tiles, unsplit and (FP64 products with a k extent
+        // above a piece length) split into pieces of 512 or 256
+        int kmax = 0;
+        if (L.kind == OP_GEMM)
+          for (int i = 0; i < L.count; ++i) kmax = std::max(kmax, W->H.gemm[L.off + i].K);
+        std::vector<TileChoice> cand;
+        for (int tile : {64, 128}) {
+          cand.push_back({tile, false, GEMM_KSPLIT});
+          for (int ks : {512, 256}) {
+            if (kmax <= ks) continue;
+            // partial tiles of this choice: skipped above the budget
+            std::vector<GemmTask> tmp(W->H.gemm.begin() + L.off,
+                                      W->H.gemm.begin() + L.off + L.count);
+            for (auto& t : tmp) {
+              t.flags |= F_SPLIT;
+              t.ksplit = ks;
+            }
+            int64_t slots = 0;
+            (void)finalize_tasks(tmp.data(), L.count, tile, nullptr, &slots);
+            if (slots * tile * tile <= kSplitBudgetDoubles || slots * tile * tile <= W->partials_cap)
+              cand.push_back({tile, true, ks});
           }
-          int64_t slots = 0;
-          (void)finalize_tasks(tmp.data(), L.count, tile, nullptr, &slots);
-          if (slots * tile * tile <= kSplitBudgetDoubles || slots * tile * tile <= W->partials_cap)
-            cand.push_back({tile, true, ks});
         }
+        float tbest = 1e30f;
+        TileChoice choice;
+        for (const TileChoice& c : cand) {
+          if ((st = retile(W, L, c.tile, c.split, s, c.ksplit)) != DL_OK) break;
+          float tmin = 1e30f;
+          for (int rep = 0; rep < 3; ++rep) {
+            (void)hipEventRecord(e0, s);
+            (void)run_launch(W, L, s);
+            (void)hipEventRecord(e1, s);
+            (void)hipEventSynchronize(e1);
+            float ms = 0.f;
+            (void)hipEventElapsedTime(&ms, e0, e1);
+            tmin = std::min(tmin, ms);
+          }
+          if (tmin < tbest) {
+            tbest = tmin;
+            choice = c;
+          }
+        }
+        it = best.emplace(sig, choice).first;
+        fresh.push_back(sig);
       }
-      float tbest = 1e30f;
-      TileChoice choice;
-      for (const TileChoice& c : cand) {
-        if ((st = retile(W, L, c.tile, c.split, s, c.ksplit)) != DL_OK) break;
-        float tmin = 1e30f;
-        for (int rep = 0; rep < 3; ++rep) {
-          (void)hipEventRecord(e0, s);
-          (void)run_launch(W, L, s);
-          (void)hipEventRecord(e1, s);
-          (void)hipEventSynchronize(e1);
-          float ms = 0.f;
-          (void)hipEventElapsedTime(&ms, e0, e1);
-          tmin = std::min(tmin, ms);
-        }
-        if (tmin < tbest) {
-          tbest = tmin;
-          choice = c;
-        }
-      }
-      it = best.emplace(sig, choice).first;
-      fresh.push_back(sig);
+      const TileChoice& c = it->second;
+      if (st == DL_OK && (L.tile != c.tile || launch_split(W, L) != c.split ||
+                          (c.split && launch_ksplit(W, L) != c.ksplit)))
+        st = retile(W, L, c.tile, c.split, s, c.ksplit);
+      if (st == DL_OK) W->tuned[sig] = c;
     }
-    const TileChoice& c = it->second;
-    if (st == DL_OK && (L.tile != c.tile || launch_split(W, L) != c.split ||
-                        (c.split && launch_ksplit(W, L) != c.ksplit)))
-      st = retile(W, L, c.tile, c.split, s, c.ksplit);
-  }
+    return st;
+  };
+  const dl_status st = each_set(W, tune);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (st == DL_OK && cache_path && !fresh.empty()) {
@@ -2839,31 +2887,27 @@ extern "C" dl_status dl_autotune(dl_ws* W, const char* cache_path, void* stream)
 extern "C" dl_status dl_ws_force_tile(dl_ws* W, int32_t tile) {
   if (!W || (tile != 64 && tile != 128)) return DL_EINVAL;
   if (W->graph_exec) return DL_ESTATE;
-  for (Launch& L : W->table) {
-    if (L.kind != OP_GEMM && L.kind != OP_GEMM32) continue;
-    const dl_status st = retile(W, L, tile, launch_split(W, L), nullptr, launch_ksplit(W, L));
-    if (st != DL_OK) return st;
-  }
-  return DL_OK;
+  W->forced_tile = tile;
+  for (auto& c : W->tuned) c.second.tile = tile;
+  return each_set(W, [&] { return apply_choices(W); });
 }
 
 extern "C" dl_status dl_ws_force_split(dl_ws* W, int32_t ksplit) {
   if (!W || ksplit < 0 || (ksplit > 0 && (ksplit < 64 || ksplit % 16))) return DL_EINVAL;
   if (W->graph_exec) return DL_ESTATE;
-  for (Launch& L : W->table) {
-    if (L.kind != OP_GEMM) continue;
-    const dl_status st =
-        retile(W, L, L.tile, ksplit > 0, nullptr, ksplit > 0 ? ksplit : GEMM_KSPLIT);
-    if (st != DL_OK) return st;
+  W->forced_split = ksplit;
+  for (auto& c : W->tuned) {
+    c.second.split = ksplit > 0;
+    c.second.ksplit = ksplit > 0 ? ksplit : GEMM_KSPLIT;
   }
-  return DL_OK;
+  return each_set(W, [&] { return apply_choices(W); });
 }
 
-// Number of GEMM launches of the workspace using each tile size.
+// Number of GEMM launches of the evaluations' plans using each tile size.
 extern "C" dl_status dl_ws_tile_counts(const dl_ws* W, int64_t* n64, int64_t* n128) {
   if (!W) return DL_EINVAL;
   int64_t a = 0, b = 0;
-  for (const Launch& L : W->table)
+  for (const Launch& L : W->dense ? W->other.table : W->table)
     if (L.kind == OP_GEMM || L.kind == OP_GEMM32) (L.tile == 128 ? b : a)++;
   if (n64) *n64 = a;
   if (n128) *n128 = b;

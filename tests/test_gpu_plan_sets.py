@@ -48,3 +48,41 @@ def test_split_graph_replays_after_a_callers_block(D, nx, nt, two):
         again = own_block(ws, wl, D)
         assert all(torch.equal(a, b) for a, b in zip(own, again)), rep
     assert (keep == 7.0).all()
+
+
+@pytest.mark.parametrize("ksplit", [64, 256])
+def test_forced_choices_reach_both_sets(D, ksplit):
+    """Split products sum in another order, so a forced split shows in the bits: it
+    must hold for the caller's blocks whether their set is built before or after,
+    and for evaluations after a call made while that set is the active one."""
+    wl = W.scaled("forced", 20, 4, 1, 2, 200, seed=4)  # bp = 448
+    model = D.Model.from_workload(wl)
+
+    def space():
+        return D.Workspace(model, two_sided=True)
+
+    plain = space()
+    f_plain = plain.fobj(wl.theta)[1][:, :7].clone()
+    own_plain = own_block(plain, wl, D)
+    before, after = space(), space()
+    before.force_split(ksplit)
+    before.force_tile(128)
+    own_block(after, wl, D)        # builds the second set, which is now active
+    after.force_split(ksplit)
+    after.force_tile(128)
+    for ws in (before, after):
+        assert ws.tile_counts()["tile64"] == 0 and ws.tile_counts()["tile128"] > 0
+    f0, f1 = (ws.fobj(wl.theta)[1][:, :7].clone() for ws in (before, after))
+    assert torch.equal(f0, f1) and not torch.equal(f0, f_plain)
+    a, b = own_block(before, wl, D), own_block(after, wl, D)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    assert not torch.equal(a[1], own_plain[1])
+    assert (a[1] - own_plain[1]).abs().max() <= 1e-10 * own_plain[1].abs().max()
+    for ws in (before, after):
+        assert ws.tile_counts()["tile64"] == 0  # also while the second set is active
+    # and back
+    for ws in (before, after):
+        ws.force_split(0)
+    for x, y in zip(own_block(before, wl, D), own_plain):
+        assert torch.equal(x, y)
+    assert torch.equal(after.fobj(wl.theta)[1][:, :7], f_plain)
