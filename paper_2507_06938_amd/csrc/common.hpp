@@ -257,10 +257,11 @@ hipError_t launch_dag_chol(const DagTask* tasks, int ntask, const DagBlock* bloc
 // MJ_AXPY_UNCONV: dst += src unless norms[0] <= tol2[0] * norms[1] (a
 // residual already within the squared relative tolerance: the iterate
 // stays as it is, bit for bit);
-// MJ_COPY2D_TO_F32: FP64 src into an FP32 dst.
+// MJ_COPY2D_TO_F32: FP64 src into an FP32 dst;
+// MJ_COPY2D_LOWER: the lower triangle only.
 enum : int { MJ_FILL = 0, MJ_COPY = 1, MJ_ZERO_I64 = 2, MJ_DIAG = 3,
              MJ_COPY2D = 4, MJ_ZERO_UPPER_TILES = 5, MJ_COPY2D_F32 = 6,
-             MJ_AXPY = 7, MJ_AXPY_UNCONV = 8, MJ_COPY2D_TO_F32 = 9 };
+             MJ_AXPY = 7, MJ_AXPY_UNCONV = 8, MJ_COPY2D_TO_F32 = 9, MJ_COPY2D_LOWER = 10 };
 struct MiscJob {
   int32_t kind, rows, cols, pad_;
   double* dst;

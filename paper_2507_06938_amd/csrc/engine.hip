@@ -2562,7 +2562,8 @@ static dl_status block_job(dl_ws* W, dl_which which, int32_t kind, int32_t t, bo
   J->rows = rows;
   J->cols = cols;
   if (to_ws) {
-    J->kind = f32 ? MJ_COPY2D_TO_F32 : MJ_COPY2D;
+    // of a diagonal block or the tip the lower triangle: tiles of 128 read zeros above
+    J->kind = f32 ? MJ_COPY2D_TO_F32 : (kind == 0 || kind == 3 ? MJ_COPY2D_LOWER : MJ_COPY2D);
     J->dst = ws; J->ldd = ldw; J->src = user; J->lds = rows;
   } else {
     J->kind = f32 ? MJ_COPY2D_F32 : MJ_COPY2D;

@@ -86,3 +86,25 @@ def test_forced_choices_reach_both_sets(D, ksplit):
     for x, y in zip(own_block(before, wl, D), own_plain):
         assert torch.equal(x, y)
     assert torch.equal(after.fobj(wl.theta)[1][:, :7], f_plain)
+
+
+@pytest.mark.parametrize("tile", [64, 128])
+def test_only_the_lower_triangle_of_a_callers_diagonal_block_counts(D, tile):
+    """A caller's symmetric diagonal blocks and tip, given in full, give the bits of
+    their lower triangles, also where the products' tiles reach above a 64-wide
+    diagonal tile."""
+    wl = W.scaled("lower", 20, 3, 1, 2, 200, seed=6)
+    model = D.Model.from_workload(wl)
+    out = []
+    for full in (False, True):
+        ws = D.Workspace(model, selinv=True)
+        ws.force_tile(tile)
+        ws.assemble(wl.theta)
+        for kind, t in ((0, 0), (0, 1), (0, 2), (3, 0)):
+            A = torch.tril(ws.get_block(D.DL_QC, kind, t))
+            ws.set_block(D.DL_QC, kind, t, A + torch.tril(A, -1).T if full else A)
+        ld, info = ws.factor(D.DL_QC)
+        assert int(info[0]) == 0
+        out.append((ld.clone(), ws.solve().clone(), ws.selinv().clone()))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
