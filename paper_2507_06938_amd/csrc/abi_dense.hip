@@ -51,7 +51,7 @@ extern "C" dl_status dl_dgemm(int32_t transa, int32_t transb, int32_t lower,
   std::vector<void*> tmp;
   GemmTask* d = nullptr;
   hipError_t e = to_dev(tmp, t, &d, s);
-  if (e == hipSuccess) e = launch_gemm_tasks(d, 1, total, s);
+  if (e == hipSuccess) e = launch_gemm_tasks(d, 1, total, s, 64, nullptr, true);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   free_all(tmp);
   return e == hipSuccess ? DL_OK : DL_EHIP;

@@ -126,9 +126,10 @@ int finalize_tasks(GemmTask* t, int n, int tile = 64, int* nred = nullptr,
 // Launch a batch of tasks already resident in device memory (tasks_dev) with
 // `units` workgroups of tile x tile outputs (tile 64 or 128, the value the
 // tasks were finalised with).  partials: nslots * tile * tile doubles (may be
-// null when nothing is split).
+// null when nothing is split).  even: one task, all its tiles of the same length.
 hipError_t launch_gemm_tasks(const GemmTask* tasks_dev, int ntask, int units,
-                             hipStream_t s, int tile = 64, double* partials = nullptr);
+                             hipStream_t s, int tile = 64, double* partials = nullptr,
+                             bool even = false);
 // The reduction of a split launch (nred workgroups).
 hipError_t launch_gemm_reduce(const GemmTask* tasks_dev, int ntask, int nred,
                               const double* partials, hipStream_t s, int tile);

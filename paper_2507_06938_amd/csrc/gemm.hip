@@ -613,17 +613,22 @@ int finalize_tasks(GemmTask* t, int n, int tile, int* nred, int64_t* nslots) {
 }
 
 hipError_t launch_gemm_tasks(const GemmTask* tasks_dev, int ntask, int units,
-                             hipStream_t s, int tile, double* partials) {
+                             hipStream_t s, int tile, double* partials, bool even) {
   if (units <= 0) return hipSuccess;
   // Eight waves a 64 x 64 tile halve the time of one tile at the same rate of a
   // compute unit, which counts where few tiles, or tiles of unequal length, end a
   // launch (17 x 17 bivariate f_obj with variances 4.40 -> 4.20 ms, 45 x 45, 100
-  // steps, 110.5 -> 106.7); four waves read less LDS, which counts where many
-  // tiles follow each other (batch with blocks up to 6075 rows 114.7 / 115.9).
+  // steps, 110.5 -> 106.7; with four / eight waves an f_obj at 10 x 10, 10 steps 817 /
+  // 793 us, at 30 x 30, 12 steps 4036 / 3981); four waves read less LDS, which counts
+  // where many tiles follow each other (batch with blocks up to 6075 rows 114.7 / 115.9
+  // ms; one product of 4096 tiles 2361 / 2370 us) and where the last round of four tiles
+  // a compute unit is nearly full (products of equal tiles, K = 2048: 729 tiles 262 /
+  // 255, 784 to 1024 tiles 326 / 335, 1089 tiles 413 / 404).
+  const bool four = units >= 4096 || (even && units > 768 && units <= 1024);
   if (tile == 128)
     hipLaunchKernelGGL((k_gemm_tasks<128, 2, 4, 4, 1>), dim3(units), dim3(512), 0, s,
                        tasks_dev, ntask, partials);
-  else if (units < 4096)
+  else if (!four)
     hipLaunchKernelGGL((k_gemm_tasks<64, 4, 2, 6, 1>), dim3(units), dim3(512), 0, s,
                        tasks_dev, ntask, partials);
   else
