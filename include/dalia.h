@@ -462,7 +462,7 @@ dl_status dl_dpotrf(int64_t n, double* A_dev, int64_t lda, int32_t want_inverse,
  * GPU (other streams, other threads) race and must be serialised by the
  * caller. */
 #define DL_DPOTRF_NOALLOC_MAX_N 2048
-#define DL_DPOTRF_NOALLOC_SCRATCH_BYTES 18958336
+#define DL_DPOTRF_NOALLOC_SCRATCH_BYTES 16435200
 dl_status dl_dpotrf_noalloc(int64_t n, double* A_dev, int64_t lda,
                             int32_t want_inverse, double* logdet_dev,
                             int64_t* info_dev, void* stream);
@@ -560,7 +560,7 @@ enum {
   DL_KERNEL_GEMV = 2,        /* solve matrix-vector products             */
   DL_KERNEL_ASSEMBLE = 3,    /* assembly                                 */
   DL_KERNEL_OTHER = 4,
-  DL_KERNEL_PANEL = 5,       /* fused trailing update + next tile factor */
+  DL_KERNEL_PANEL = 5,       /* retired: no launch of a workspace is one */
   DL_KERNEL_GEMM_REDUCE = 6, /* sum of the pieces of split-k products    */
   DL_KERNEL_DAG = 7          /* persistent diagonal-block factorisation  */
 };

@@ -178,7 +178,7 @@ extern "C" dl_status dl_dpotrf(int64_t n, double* A, int64_t lda,
   if (e == hipSuccess) e = launch_potrf_tiles(dpt, 1, s);
   if (e == hipSuccess) e = launch_gemm_tasks(dt, (int)solve.size(), units, s);
   for (int j = 0; j < nsteps && e == hipSuccess; ++j)
-    e = launch_panel_updates(dst + j, 1, grid[j], s);
+    e = launch_panel_step(dst + j, grid[j], s);
   if (e == hipSuccess && !post.empty()) e = launch_misc(dpost, 1, s);
   for (size_t l = 0; after && l < halves->begin.size() && e == hipSuccess; ++l)
     e = launch_gemm_tasks(dh + halves->begin[l], halves->count(l), halves->units[l], s);

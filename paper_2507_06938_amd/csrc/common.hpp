@@ -139,15 +139,6 @@ hipError_t launch_gemm32_tasks(const GemmTask* tasks_dev, int ntask,
                                int total_tiles, hipStream_t s, int tile = 64,
                                bool acc64 = false);
 
-// Convenience: copy host tasks to a device buffer, then launch.  Used by
-// the dense ABI entry points and by plan building (never inside timed
-// evaluation loops, where task arrays are prebuilt).
-struct DeviceTasks {
-  GemmTask* dev = nullptr;
-  int ntask = 0;
-  int total = 0;
-};
-
 // ---- 64x64 diagonal-tile Cholesky ------------------------------------------
 // Factor the 64 x 64 SPD tile at A (lda) in place.  mode 0: lower triangle
 // of A <- L (upper zeroed), Ginv (64 x 64, ld 64, may be null) <- L^{-1};
@@ -202,11 +193,8 @@ struct PanelTask {
   int32_t j, nbk;
   int32_t last;
   int32_t inv;         // PANEL_L, ..
-  int32_t beg[5];      // first workgroup of this task in each role segment
-  int32_t tot[5];      // workgroups of each role in the launch (every task)
+  int32_t tot[5];      // workgroups of each role
 };
-// Fill beg/tot; return the grid size.
-int finalize_panels(PanelTask* t, int n);
 // The panel steps of one n x n block (nbk = n / 64 >= 2 tiles; tile 0 factored
 // and panel 0 solved before the first): nbk - 1 of them, and with PANEL_INVERSE
 // the closing one, after which tile (nbk-1, nbk-2) of G is still to be copied
@@ -214,8 +202,7 @@ int finalize_panels(PanelTask* t, int n);
 // 1) / 2 tiles.  Fills t[j] and its grid; returns the number of launches.
 int panel_steps(int64_t n, double* A, int64_t lda, int inv, double* logdiag, int64_t* info,
                 double* tmp, PanelTask* t, int* grid);
-hipError_t launch_panel_updates(const PanelTask* tasks_dev, int ntask, int grid,
-                                hipStream_t s);
+hipError_t launch_panel_step(const PanelTask* step_dev, int grid, hipStream_t s);
 
 // ---- persistent tile-task factorisation of diagonal blocks --------------------
 // One launch factors several diagonal blocks (A = L L^T, G = L^{-1} formed

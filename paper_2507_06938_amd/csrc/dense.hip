@@ -15,12 +15,6 @@ constexpr int POTRF_NT = 1024;      // threads of a tile-factor workgroup (16 wa
 typedef double v4d __attribute__((ext_vector_type(4)));
 }
 
-__device__ __forceinline__ double readlane_f64(double x, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
-  return __hiloint2double(hi, lo);
-}
-
 // Device-coherent accesses (agent-scope relaxed atomics: sc1 loads and
 // stores that bypass the per-XCD caches): the persistent factorisation
 // exchanges tiles between workgroups on different XCDs with these.
@@ -429,26 +423,18 @@ __device__ void panel_inverse(const PanelTask& T, int role, int loc, double* S0,
     global_store(&dst[(q0 + lr) + (int64_t)(p0 + lk + 4 * rg) * ldd], -g[rg]);
 }
 
-__global__ __launch_bounds__(POTRF_NT) void k_panel_update(const PanelTask* __restrict__ tasks,
-                                                           int ntask) {
+__global__ __launch_bounds__(POTRF_NT) void k_panel_update(const PanelTask* __restrict__ step) {
   __shared__ __align__(16) double pool[3 * TILE_LDS];
   double* S0 = pool;
   double* S1 = pool + TILE_LDS;
   double* S2 = pool + 2 * TILE_LDS;
-  // role segments: 0 factor, 1 column, 2 inverse row, 3 inverse accumulate,
-  // 4 rest; then the task whose share of the segment holds this workgroup
-  int g = blockIdx.x, role = 0;
-  while (role < 4 && g >= tasks[0].tot[role]) {
-    g -= tasks[0].tot[role];
+  // role segments: 0 factor, 1 column, 2 inverse row, 3 inverse accumulate, 4 rest
+  int loc = blockIdx.x, role = 0;
+  while (role < 4 && loc >= step->tot[role]) {
+    loc -= step->tot[role];
     ++role;
   }
-  int lo = 0, hi = ntask - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (tasks[mid].beg[role] <= g) lo = mid; else hi = mid - 1;
-  }
-  const int loc = g - tasks[lo].beg[role];
-  const PanelTask T = tasks[lo];
+  const PanelTask T = *step;
   if (role == 2 || role == 3) {
     panel_inverse(T, role, loc, S0, S1);
     return;
@@ -546,31 +532,17 @@ __global__ __launch_bounds__(POTRF_NT) void k_panel_update(const PanelTask* __re
   for (int rg = 0; rg < 4; ++rg) global_store(&C[co + (int64_t)(4 * rg) * T.ld], a0[rg]);
 }
 
-int finalize_panels(PanelTask* t, int n) {
-  int tot[5] = {0, 0, 0, 0, 0};
-  for (int i = 0; i < n; ++i) {
-    const int j = t[i].j, nbk = t[i].nbk;
-    int cnt[5];
-    if (t[i].last) {
-      cnt[0] = cnt[1] = cnt[3] = cnt[4] = 0;
-      cnt[2] = j;
-    } else {
-      const int m = nbk - j - 1;  // trailing tile rows (>= 1)
-      cnt[0] = 1;
-      cnt[1] = m - 1;
-      cnt[2] = t[i].inv == PANEL_INVERSE ? j : 0;
-      cnt[3] = t[i].inv == PANEL_INVERSE ? (nbk - 1 - j) * j : 0;
-      cnt[4] = m * (m - 1) / 2;
-    }
-    for (int k = 0; k < 5; ++k) {
-      t[i].beg[k] = tot[k];
-      tot[k] += cnt[k];
-    }
-  }
+// Fill the workgroups of each role; return the grid size.
+static int panel_grid(PanelTask& t) {
+  const int j = t.j, nbk = t.nbk, m = nbk - j - 1;  // m: trailing tile rows
+  const bool inv = t.inv == PANEL_INVERSE;
+  const int steps[5] = {1, m - 1, inv ? j : 0, inv ? m * j : 0, m * (m - 1) / 2};
+  const int last[5] = {0, 0, j, 0, 0};
   int grid = 0;
-  for (int k = 0; k < 5; ++k) grid += tot[k];
-  for (int i = 0; i < n; ++i)
-    for (int k = 0; k < 5; ++k) t[i].tot[k] = tot[k];
+  for (int k = 0; k < 5; ++k) {
+    t.tot[k] = t.last ? last[k] : steps[k];
+    grid += t.tot[k];
+  }
   return grid;
 }
 
@@ -591,15 +563,14 @@ int panel_steps(int64_t n, double* A, int64_t lda, int inv, double* logdiag, int
     p.nbk = nbk;
     p.last = j + 1 == nbk;
     p.inv = inv;
-    grid[j] = finalize_panels(&p, 1);
+    grid[j] = panel_grid(p);
   }
   return steps;
 }
 
-hipError_t launch_panel_updates(const PanelTask* tasks, int ntask, int grid,
-                                hipStream_t s) {
-  if (ntask <= 0 || grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_panel_update, dim3(grid), dim3(POTRF_NT), 0, s, tasks, ntask);
+hipError_t launch_panel_step(const PanelTask* step, int grid, hipStream_t s) {
+  if (grid <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_panel_update, dim3(grid), dim3(POTRF_NT), 0, s, step);
   return hipGetLastError();
 }
 

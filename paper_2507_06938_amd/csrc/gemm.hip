@@ -338,9 +338,6 @@ __device__ __forceinline__ void mma_chunk(const double* __restrict__ as,
   }
 }
 
-// One workgroup of WM x WN waves computes one BT x BT tile; wave (wm, wn)
-// owns rows wm*BT/WM .. and columns wn*BT/WN .. of it, FM x FN MFMA blocks
-// of 16 x 16.  MINW: waves per SIMD the register budget must allow.
 // Task of workgroup (or reduction workgroup) `u`: the last task whose
 // first index is <= u (tasks with no work share their successor's first).
 __device__ __forceinline__ int find_unit_task(const GemmTask* __restrict__ tasks,
@@ -353,7 +350,10 @@ __device__ __forceinline__ int find_unit_task(const GemmTask* __restrict__ tasks
   return lo;
 }
 
-template <int BT, int WM, int WN, int MINW, int PF>
+// One workgroup of WM x WN waves computes one BT x BT tile; wave (wm, wn)
+// owns rows wm*BT/WM .. and columns wn*BT/WN .. of it, FM x FN MFMA blocks
+// of 16 x 16.  MINW: waves per SIMD the register budget must allow.
+template <int BT, int WM, int WN, int MINW>
 __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
     const GemmTask* __restrict__ tasks, int ntask, double* __restrict__ partials) {
   constexpr int NT = WM * WN * 64;
@@ -425,32 +425,13 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
     constexpr int PV = VStage<BT, NT>::PV;
     v2d a0[PV], b0[PV];
     sa.load(a0); sb.load(b0); sa.next(); sb.next();
-    if constexpr (PF == 1) {
-      sa.store(As[0], a0); sb.store(Bs[0], b0);
+    sa.store(As[0], a0); sb.store(Bs[0], b0);
+    __syncthreads();
+    for (int c = 0; c < nchunks; ++c) {
+      sa.load(a0); sb.load(b0); sa.next(); sb.next();  // chunk c + 1
+      mma_chunk<BT, WM, WN>(As[c & 1], Bs[c & 1], acc, wm, wn, lrow, lk);
+      sa.store(As[(c + 1) & 1], a0); sb.store(Bs[(c + 1) & 1], b0);
       __syncthreads();
-      for (int c = 0; c < nchunks; ++c) {
-        sa.load(a0); sb.load(b0); sa.next(); sb.next();  // chunk c + 1
-        mma_chunk<BT, WM, WN>(As[c & 1], Bs[c & 1], acc, wm, wn, lrow, lk);
-        sa.store(As[(c + 1) & 1], a0); sb.store(Bs[(c + 1) & 1], b0);
-        __syncthreads();
-      }
-    } else {
-      // two chunks in flight: a0/b0 and a1/b1 alternate
-      v2d a1[PV], b1[PV];
-      sa.load(a1); sb.load(b1); sa.next(); sb.next();    // chunk 1
-      sa.store(As[0], a0); sb.store(Bs[0], b0);
-      __syncthreads();
-      for (int c = 0; c < nchunks; c += 2) {
-        sa.load(a0); sb.load(b0); sa.next(); sb.next();  // chunk c + 2
-        mma_chunk<BT, WM, WN>(As[0], Bs[0], acc, wm, wn, lrow, lk);
-        sa.store(As[1], a1); sb.store(Bs[1], b1);        // chunk c + 1
-        __syncthreads();
-        if (c + 1 >= nchunks) break;
-        sa.load(a1); sb.load(b1); sa.next(); sb.next();  // chunk c + 3
-        mma_chunk<BT, WM, WN>(As[1], Bs[1], acc, wm, wn, lrow, lk);
-        sa.store(As[0], a0); sb.store(Bs[0], b0);        // chunk c + 2
-        __syncthreads();
-      }
     }
   } else {
     // scalar staging with per-element bounds (odd sizes, unaligned operands)
@@ -626,13 +607,13 @@ hipError_t launch_gemm_tasks(const GemmTask* tasks_dev, int ntask, int units,
   // 255, 784 to 1024 tiles 326 / 335, 1089 tiles 413 / 404).
   const bool four = units >= 4096 || (even && units > 768 && units <= 1024);
   if (tile == 128)
-    hipLaunchKernelGGL((k_gemm_tasks<128, 2, 4, 4, 1>), dim3(units), dim3(512), 0, s,
+    hipLaunchKernelGGL((k_gemm_tasks<128, 2, 4, 4>), dim3(units), dim3(512), 0, s,
                        tasks_dev, ntask, partials);
   else if (!four)
-    hipLaunchKernelGGL((k_gemm_tasks<64, 4, 2, 6, 1>), dim3(units), dim3(512), 0, s,
+    hipLaunchKernelGGL((k_gemm_tasks<64, 4, 2, 6>), dim3(units), dim3(512), 0, s,
                        tasks_dev, ntask, partials);
   else
-    hipLaunchKernelGGL((k_gemm_tasks<64, 2, 2, 4, 1>), dim3(units), dim3(256), 0, s,
+    hipLaunchKernelGGL((k_gemm_tasks<64, 2, 2, 4>), dim3(units), dim3(256), 0, s,
                        tasks_dev, ntask, partials);
   return hipGetLastError();
 }

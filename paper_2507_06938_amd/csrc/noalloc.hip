@@ -20,14 +20,12 @@ constexpr int kMaxTiles = (int)(kMaxN / 64);
 constexpr size_t kDescBytes = 256 * 6 + sizeof(PanelTask) * kMaxTiles + 256;
 // scratch layout, in doubles (every region 256-byte aligned)
 constexpr int64_t kDescDoubles = 8192;  // 64 KiB of launch descriptors
-constexpr int64_t kGdDoubles = kMaxN * 64;
-constexpr int64_t kTempDoubles = kMaxN * (kMaxTiles / 2 + 1) * 64;
+constexpr int64_t kGdDoubles = 4096;
+constexpr int64_t kTempDoubles = 4096 * (2 + (int64_t)kMaxTiles * (kMaxTiles - 1) / 2);
 constexpr int64_t kLogDoubles = kMaxN;
 constexpr int64_t kPartDoubles = 256;
 constexpr int64_t kScratchDoubles =
     kDescDoubles + kGdDoubles + kTempDoubles + kLogDoubles + kPartDoubles;
-static_assert(4096 * (2 + (int64_t)kMaxTiles * (kMaxTiles - 1) / 2) <= kTempDoubles,
-              "side ring and accumulators");
 static_assert(kDescBytes <= kDescDoubles * 8 && sizeof(MiscJob) <= 256 &&
                   sizeof(GemmTask) <= 256 && sizeof(SumJob) <= 256,
               "descriptors");
@@ -175,7 +173,7 @@ extern "C" dl_status dl_dpotrf_noalloc(int64_t n, double* A, int64_t lda,
   if (e == hipSuccess) e = launch_potrf_tiles(dpt, 1, s);
   if (e == hipSuccess && nbk > 1) e = launch_gemm_tasks(dt, 1, units, s);
   for (int j = 0; j < nsteps && e == hipSuccess; ++j)
-    e = launch_panel_updates(dst + j, 1, grid[j], s);
+    e = launch_panel_step(dst + j, grid[j], s);
   if (e == hipSuccess && nbk > 1 && inv) e = launch_misc(dpost, 1, s);
   if (e == hipSuccess) e = launch_sums(dsj, 1, s);
   return e == hipSuccess ? DL_OK : DL_EHIP;
