@@ -55,3 +55,24 @@ def test_variances_of_large_blocks(D, nx, nt, nr, two, dense):
         again.factor()
         v2 = again.selinv().cpu()
         assert torch.equal(v2[:wl.N], var) and torch.equal(v2[wl.N:], var)
+
+
+@pytest.mark.parametrize("nx,nt,two", [(38, 2, False), (33, 4, True)])
+def test_forced_tiles_and_splits_of_the_triangles_products(D, nx, nt, two):
+    """Tiles of 128 reach above the 64-wide diagonal tiles, and split pieces are cut
+    without regard to the rows that begin late: the same bits for either tile, and
+    the unsplit variances to the rounding of sums in pieces."""
+    wl = W.scaled("selforce", nx, nt, 1, 2, 500, seed=3)
+    model = D.Model.from_workload(wl)
+    var = {}
+    for tile in (64, 128):
+        for ksplit in (0, 256):
+            ws = D.Workspace(model, selinv=True, two_sided=two)
+            ws.force_tile(tile)
+            ws.force_split(ksplit)
+            ws.assemble(wl.theta)
+            ws.factor()
+            var[tile, ksplit] = ws.selinv().cpu()
+    for ksplit in (0, 256):
+        assert torch.equal(var[64, ksplit], var[128, ksplit])
+    np.testing.assert_allclose(var[64, 256], var[64, 0], rtol=1e-11)
