@@ -58,7 +58,8 @@ def fac_flops(n, b, a):
 # profiles/gemm_block_products_traffic.md):
 #   trsm    [B;R] G^T, 2112 x 2048 x 2048, k < col + 64: 610.6 + 34.6 MB / 8.858 GFLOP
 #   update  SYRK lower 2048^2, K 2048:                  174.6 + 16.8 MB / 8.590 GFLOP
-#   selinv  per recursion step: W = [B;R] G (as trsm), Y = -X W (NN 2112 x 2048 x 2112,
+#   selinv  per recursion step of the general form (the symmetric form, which this mesh
+#           takes, was not counted): W = [B;R] G (as trsm), Y = -X W (NN 2112 x 2048 x 2112,
 #           432.6 + 34.6 MB / 18.27 GFLOP), X_tt -= Y^T W (as update), G^T G (lower,
 #           k >= row, 224.5 + 16.8 MB / 5.727 GFLOP): 1.545 GB / 41.45 GFLOP
 #   other   NN 2048^3: 307.1 + 33.6 MB / 17.18 GFLOP

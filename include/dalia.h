@@ -173,7 +173,11 @@ enum {
                          of Q_c (and Q_p) are stored in FP32 and their
                          TRSM / SYRK / GEMM products run on FP32 matrix
                          cores (FP32 accumulation, subtracted into FP64
-                         diagonal blocks and tips); diagonal-block Cholesky,
+                         diagonal blocks and tips; with one response of
+                         DL_MODEL_SEPARABLE the coupling products are summed
+                         in FP64 from the model's exact entries and the
+                         updates' products added in FP64 every 16 terms);
+                         diagonal-block Cholesky,
                          inverses and log-determinants stay FP64; the mean
                          is refined in FP64 against the sparse Q_c to
                          DL_REFINE_TOL (see below)                         */,
@@ -237,7 +241,8 @@ enum {
 #define DL_REFINE_STEPS_GRAPH 3
 #define DL_INFO_NOTCONV (-1)
 /* info value of a factorisation whose persistent launch gave up
- * waiting for a tile (it never should; f is then -inf). */
+ * waiting for a tile, after 2 s of polling in which time off the card does
+ * not count (it never should; f is then -inf). */
 #define DL_INFO_TIMEOUT (-2)
 
 /* Allocate the dense BTA workspace for Q_p and Q_c of `model`.  All device
@@ -297,8 +302,9 @@ dl_status bta_factor(dl_ws* ws, dl_which which, double* logdet_dev,
  *     keeps the mean in the workspace (dl_ws_mean);
  *   otherwise nrhs >= 1 right-hand sides of N_total doubles each (BTA
  *     order, a batch workspace's instances packed in order), solved in
- *     place one after the other (the workspace's own right-hand side is
- *     overwritten).
+ *     place, without refinement up to four of them in one pass over the factor
+ *     (the same bits as one at a time); the workspace's own right-hand side
+ *     and mean are then the last one's.
  * refine_max < 0: the workspace's default refinement (DL_WS_MIXED: to
  * DL_REFINE_TOL in at most DL_REFINE_MAX corrections; FP64: none).
  * refine_max >= 0 (at most 100): at most refine_max FP64 corrections

@@ -57,7 +57,7 @@ __device__ void gemv_n_body(const GemvN& g, double* xs, double* sh, int* s_last)
   const int len = gemv_slice_len(g.K);
   const int kend = g.tri ? min(g.K, rb * RB + RB) : g.K;
   // A's zeros before its rows' first column are skipped by whole slices and
-  // by whole 128 columns of a slice
+  // by whole stages of a slice
   const int klo = min(g.band.lo(rb * RB, min(RB, g.M - rb * RB), g.K), kend - 1);
   const int sl0 = klo / len, nsl = (kend + len - 1) / len - sl0;
   if (sl < sl0 || sl >= sl0 + nsl) return;

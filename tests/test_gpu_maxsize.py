@@ -1,6 +1,6 @@
 """The largest block the library accepts: one response on a 100 x 100 mesh
-(b = 10000, padded to 10048; the assembly builds a column of a diagonal and
-a sub-diagonal block in LDS, 2 * 10048 + 64 doubles <= 160 KiB).
+(b = 10000, padded to 10048; two columns of blocks and the arrow's, 2 * 10048 +
+64 doubles, may take 160 KiB).
 
 Without observations Q_c = Q_p = tau_u (T (x) Q_s) (+ the fixed effects'
 prior), whose log-determinant and marginal variances have closed forms at
