@@ -118,18 +118,13 @@ struct VStage {
   const double* base;  // operand origin (the safe address of invalid slots)
   const double* p;     // slot 0 of the current chunk
   int64_t step, adv;
-  int64_t jump;        // from chunk `khop` to `kland` of the operand
-  int khop, kland;
   int rl, kq;          // tile-relative row, chunk-relative k of slot 0
   int kc, kend;        // current chunk's first k, k limit
   bool trans;
   unsigned rowok;      // bit j: slot j's row(s) inside the operand
 
   __device__ __forceinline__ void init(const double* X, int64_t ldx, bool tr, int r0, int R,
-                                       int k0, int ke, int tid, int hop, int land) {
-    khop = hop;
-    kland = land;
-    jump = (int64_t)(land - hop) * (tr ? 1 : ldx);
+                                       int k0, int ke, int tid) {
     base = X;
     trans = tr;
     kc = k0;
@@ -165,13 +160,9 @@ struct VStage {
     }
   }
 
-  __device__ __forceinline__ void next() {
-    p += adv;
-    kc += BK;
-    if (kc == khop) {
-      p += jump;
-      kc = kland;
-    }
+  __device__ __forceinline__ void next(int chunks = 1) {
+    p += chunks * adv;
+    kc += chunks * BK;
   }
 
   __device__ __forceinline__ void store(double* __restrict__ S, const v2d (&v)[PV]) const {
@@ -412,16 +403,19 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
   const bool vec_b = vec_operand(T.B, T.ldb, !tb, T.N, kb, ke);
   if (vec_a && vec_b) {
     VStage<BT, NT> sa, sb;
-    int hop = -1, land = 0;
+    // `skip` chunks before chunk `hop` of the rest are passed over.  (Compared in the
+    // loop, where it is a scalar: the operands' own check of every chunk's k took 2% of
+    // a product of 4096 tiles.)
+    int hop = -1, skip = 0;
     if ((T.flags & F_KTAIL) && T.kslices == 1) {
       const int last = n0 + min(BT, T.N - n0) + T.band.reach;  // rows of C up to here
-      hop = (last + BK - 1) / BK * BK;
-      land = T.band.end;
-      if (hop >= land) hop = -1;
-      else nchunks -= (land - hop) / BK;
+      hop = (last + BK - 1) / BK - kb / BK;
+      skip = (T.band.end - kb) / BK - hop;
+      if (skip > 0) nchunks -= skip;
+      else hop = -1;
     }
-    sa.init(T.A, T.lda, ta, m0, T.M, kb, ke, tid, hop, land);
-    sb.init(T.B, T.ldb, !tb, n0, T.N, kb, ke, tid, hop, land);
+    sa.init(T.A, T.lda, ta, m0, T.M, kb, ke, tid);
+    sb.init(T.B, T.ldb, !tb, n0, T.N, kb, ke, tid);
     constexpr int PV = VStage<BT, NT>::PV;
     v2d a0[PV], b0[PV];
     sa.load(a0); sb.load(b0); sa.next(); sb.next();
@@ -429,6 +423,7 @@ __global__ __launch_bounds__(WM * WN * 64, MINW) void k_gemm_tasks(
     __syncthreads();
     for (int c = 0; c < nchunks; ++c) {
       sa.load(a0); sb.load(b0); sa.next(); sb.next();  // chunk c + 1
+      if (c + 2 == hop) { sa.next(skip); sb.next(skip); }
       mma_chunk<BT, WM, WN>(As[c & 1], Bs[c & 1], acc, wm, wn, lrow, lk);
       sa.store(As[(c + 1) & 1], a0); sb.store(Bs[(c + 1) & 1], b0);
       __syncthreads();
