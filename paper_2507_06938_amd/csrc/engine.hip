@@ -388,7 +388,7 @@ struct Inst {
   // two-sided: one spare slot per elimination chain)
   double *Dc = nullptr, *BRc = nullptr, *Pc = nullptr, *GPc = nullptr;
   int64_t ldbr = 0;
-  std::vector<int> slot_final;
+  std::vector<int> slot_final[2];
   // Elimination order.  One-sided: blocks 0..nt-2 forward, then the root
   // block nt-1.  Two-sided: chain A = 0..mid-1 forward and chain B =
   // nt-1..mid+1 backward run concurrently (their steps share launches),
@@ -1021,7 +1021,7 @@ static void seq_factor(dl_ws* W, Inst& I, int w, int nt_max, std::vector<Step>& 
   sl.sum.dst = I.logdet2 + w;
   sl.sum.partial = I.sumpart + w * SUM_BLOCKS;
   q.push_back(sl);
-  if (w == 1) I.slot_final.assign(slot.begin(), slot.begin() + m.nt);
+  I.slot_final[w].assign(slot.begin(), slot.begin() + m.nt);
 }
 
 static Step gn_step(uint64_t key, GemvN g, double bytes, int nrhs) {
@@ -1067,9 +1067,9 @@ static void seq_solve(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q, int n
   const int64_t ldbr = I.ldbr;
   const double b = m.b, a = m.a;
   const int eb = I.eb;
-  auto BRs = [&](int t) { return eoff(I.BRc, (int64_t)I.slot_final[t] * ldbr * bp, eb); };
+  auto BRs = [&](int t) { return eoff(I.BRc, (int64_t)I.slot_final[1][t] * ldbr * bp, eb); };
   auto BRo = [&](int t, int rows) {
-    return eoff(I.BRc, (int64_t)I.slot_final[t] * ldbr * bp + rows, eb);
+    return eoff(I.BRc, (int64_t)I.slot_final[1][t] * ldbr * bp + rows, eb);
   };
   auto G = [&](int t) { return I.Dc + (int64_t)t * bp * bp; };
   const int a32 = I.mixed ? 1 : 0;
@@ -1209,7 +1209,7 @@ static void seq_selinv_s(dl_ws* W, Inst& I, std::vector<Step>& q) {
   double* Uc[2] = {I.SU, I.SUB};
   double* Tc[2] = {I.ST, I.STB};
   auto step = [&](int t, uint64_t mj, const double* Xin, double* Xout, int c, bool root) {
-    const double* CR = I.BRc + (int64_t)I.slot_final[t] * ld * bp;
+    const double* CR = I.BRc + (int64_t)I.slot_final[1][t] * ld * bp;
     const double* G = I.Dc + (int64_t)t * bp * bp;
     double *Z = Zc[c], *U = Uc[c], *T = Tc[c];
     // the root has arrow rows only
@@ -1287,9 +1287,9 @@ static void seq_selinv(dl_ws* W, Inst& I, int nt_max, std::vector<Step>& q) {
   const int64_t ld = I.ldbr;  // bp + ap
   const double b = m.b, a = m.a;
   const int eb = I.eb;
-  auto BRs = [&](int t) { return eoff(I.BRc, (int64_t)I.slot_final[t] * ld * bp, eb); };
+  auto BRs = [&](int t) { return eoff(I.BRc, (int64_t)I.slot_final[1][t] * ld * bp, eb); };
   auto BRo = [&](int t, int rows) {
-    return eoff(I.BRc, (int64_t)I.slot_final[t] * ld * bp + rows, eb);
+    return eoff(I.BRc, (int64_t)I.slot_final[1][t] * ld * bp + rows, eb);
   };
   auto G = [&](int t) { return I.Dc + (int64_t)t * bp * bp; };
   // mixed precision: W = [B;R]G and the products with it run on FP32 MFMA
@@ -2543,7 +2543,7 @@ static dl_status block_job(dl_ws* W, dl_which which, int32_t kind, int32_t t, bo
   } else {
     if (t < 0 || t >= m.nt) return DL_EINVAL;
     const bool fact = W->factored[p ? 0 : 1];
-    const int sl = (!p && fact) ? I.slot_final[t] : t;
+    const int sl = fact ? I.slot_final[p ? 0 : 1][t] : t;
     const int64_t ldbr = p ? bp : I.ldbr;
     double* BRt = eoff(p ? I.Bp : I.BRc, (int64_t)sl * ldbr * bp, I.eb);
     if (kind == 0) {

@@ -597,7 +597,7 @@ hipError_t launch_gemm_tasks(const GemmTask* tasks_dev, int ntask, int units,
   // steps, 110.5 -> 106.7; with four / eight waves an f_obj at 10 x 10, 10 steps 817 /
   // 793 us, at 30 x 30, 12 steps 4036 / 3981); four waves read less LDS, which counts
   // where many tiles follow each other (batch with blocks up to 6075 rows 114.7 / 115.9
-  // ms; one product of 4096 tiles 2361 / 2370 us) and where the last round of four tiles
+  // ms; one product of 4096 tiles 2361 / 2370 us) and where the last fill of four tiles
   // a compute unit is nearly full (products of equal tiles, K = 2048: 729 tiles 262 /
   // 255, 784 to 1024 tiles 326 / 335, 1089 tiles 413 / 404).
   const bool four = units >= 4096 || (even && units > 768 && units <= 1024);

@@ -108,3 +108,35 @@ def test_only_the_lower_triangle_of_a_callers_diagonal_block_counts(D, tile):
         out.append((ld.clone(), ws.solve().clone(), ws.selinv().clone()))
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("family,two", [("separable", False), ("diffusion", False),
+                                        ("diffusion", True)])
+def test_blocks_of_both_factors(D, family, two):
+    """The blocks read back after a factorisation, of Q_c and of a kept Q_p: the
+    inverse G_t of each diagonal block's factor and the coupling B_t G_t^T, against
+    the blocks as they were assembled and a plain elimination in FP64."""
+    wl = W.scaled("blocks", 10, 6, 1, 2, 100, seed=2, model=family)
+    ws = D.Workspace(D.Model.from_workload(wl), keep_qp=True, two_sided=two)
+    ws.assemble(wl.theta)
+    mid = (wl.nt + 1) // 2 if two else wl.nt - 1
+    want = {}
+    for which in (D.DL_QP, D.DL_QC):
+        Dt = [torch.tril(ws.get_block(which, 0, t)).cpu() for t in range(wl.nt)]
+        Dt = [A + torch.tril(A, -1).T for A in Dt]
+        Bt = [ws.get_block(which, 1, t).cpu() for t in range(wl.nt - 1)]
+        order = [(t, t + 1, Bt[t]) for t in range(mid)]
+        order += [(t, t - 1, Bt[t - 1].T) for t in range(wl.nt - 1, mid, -1)]
+        for t, succ, B in order:
+            G = torch.linalg.inv(torch.linalg.cholesky(Dt[t]))
+            C = B @ G.T
+            Dt[succ] = Dt[succ] - C @ C.T
+            want[which, 0, t] = G
+            if t < wl.nt - 1:  # (a last block's coupling is not a block of the caller's)
+                want[which, 1, t] = C
+        want[which, 0, mid] = torch.linalg.inv(torch.linalg.cholesky(Dt[mid]))
+    ws.factor()
+    for (which, kind, t), A in want.items():
+        got = ws.get_block(which, kind, t).cpu()
+        got = torch.tril(got) if kind == 0 else got
+        assert (got - A).abs().max() <= 1e-11 * A.abs().max(), (which, kind, t)
